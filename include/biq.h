@@ -128,7 +128,12 @@ typedef struct {
                             requested before the tables are built (latency; needs
                             tiles_per_split = 1), 2 = gemv8_half only: one row per wave at a
                             time, its 64 lanes on the row's 64 key dwords (few rows per
-                            workgroup)                                                     */
+                            workgroup).  unpack_mfma: 0 = the inputs as 16-bit terms (input_terms),
+                            1 = (the library's choice) block-scaled digits: every 32 consecutive
+                            elements of an input vector share a power of two and are split into five
+                            6-bit floats, exact to 2^-24 of the largest of the 32, contracted with
+                            4-bit weights; inputs holding bf16 values keep one bf16 term.
+                            input_terms must be 3 (or 0) and sizes the workspace                 */
     int xcd_skew;        /* GEMV kernel, row_mode 0, no chunk split, row_blocks a multiple of 8:
                             workgroups on even XCDs take rows_per_wg + xcd_skew rows, those on
                             odd XCDs rows_per_wg - xcd_skew (odd XCDs stream slower)        */
@@ -136,7 +141,8 @@ typedef struct {
                             contracting its own part of the workgroup's key groups; their partial
                             sums are added in LDS (0 is read as 1).  rows_per_wg is then
                             (4 / wave_splits) * 32 * r with r row tiles per wave and plane,
-                            r in {1, 2, 4}, q * r <= 4                                       */
+                            r in {1, 2, 4}, q * r <= 4 (row_mode 1: q * r * batch_tile / 32 <= 8 and
+                            at most 64 key groups per wave)                                  */
     int table_fill;      /* GEMV kernel, fused tables: 0 = every entry from the chunk's pair sums (a direct,
                             GEMM-like fill), 1 = the order of Algorithm 1: a block's first entry, then
                             each further entry of the lower half from an earlier one by adding 2 x_t,
@@ -144,7 +150,7 @@ typedef struct {
                             so that the two build methods Sec. III-B weighs can be timed against each
                             other (the default, 0, is the faster one here)                       */
     int input_terms;     /* unpack_mfma kernel: 16-bit terms every fp32 input is split into for the matrix
-                            cores.  3 (0 is read as 3; what the library chooses): three bf16 terms, an
+                            cores (row_mode 0).  3 (0 is read as 3): three bf16 terms, an
                             exact split - the result is that of an fp32 evaluation of Eq. 2 up to the
                             order of the additions; terms that are zero for all input vectors of a
                             workgroup over a wave's whole part of the row are skipped, so inputs holding
@@ -239,8 +245,8 @@ biq_status biq_query(const uint8_t* K, const float* alpha, const float* LUT, flo
  * For many input vectors (see biq_plan_get / biq_plan_get_lut) the default plan is the
  * unpack_mfma kernel instead: the "GEMM with unpacking" alternative of Sec. IV-B
  * (Algorithm 3), with the sign bits expanded to +-1 in registers and contracted on the
- * matrix cores against X split exactly into three bf16 terms; fp32 accumulation, same
- * tolerance, same determinism.  (biq_plan_get_mfma + biq_gemm_ex give the faster two-term
+ * matrix cores against X in block-scaled digits (see biq_plan.row_mode; rounded to 2^-24 of the
+ * largest of 32 elements), fp32 accumulation, same tolerance, same determinism.  (biq_plan_get_mfma + biq_gemm_ex give the faster two-term
  * variant, see biq_plan.input_terms.)  It uses the first part of the workspace for the split X.
  */
 biq_status biq_gemm(const uint8_t* K, const float* alpha, const float* X, float* Y,

@@ -12,6 +12,7 @@
 #include "biq_query_wide.h"
 #include "biq_quantize.h"
 #include "biq_grouped.h"
+#include "biq_digit_mfma.h"
 
 namespace {
 
@@ -67,18 +68,30 @@ bool plan_finish_unpack(biq_plan& pl, int m, int n, int q, int batch) {
     const int ws = pl.wave_splits;
     if (ws != 1 && ws != 2 && ws != 4) return false;
     // (4 / ws) waves side by side x r row tiles of 32 rows per plane, at most 4 row tiles per wave
+    // (with block-scaled digits, row_mode 1: 8 row x column tiles)
+    const bool digits = pl.row_mode == 1;
     const int per_r = (4 / ws) * 32;
-    if (pl.rows_per_wg % per_r) return false;
+    if (pl.rows_per_wg < 1 || pl.rows_per_wg % per_r) return false;
     const int r = pl.rows_per_wg / per_r;
-    if ((r != 1 && r != 2 && r != 4) || q * r > 4) return false;
-    if (ws == 4 && q * r * (pl.batch_tile / 32) == 8) return false;  // would not fit the register file
-    if (pl.row_mode != 0 || pl.xcd_skew != 0 || pl.tiles_per_split < 1) return false;
+    if (r != 1 && r != 2 && r != 4) return false;
+    if (digits ? q * r * (pl.batch_tile / 32) > kDigitMaxTiles : q * r > 4) return false;
+    if (!digits && ws == 4 && q * r * (pl.batch_tile / 32) == 8) return false;  // would not fit the register file
+    if ((pl.row_mode != 0 && !digits) || pl.xcd_skew != 0 || pl.tiles_per_split < 1) return false;
     const int groups = (int)((biq_key_row_stride(n) + kUnpackGroupBytes - 1) / kUnpackGroupBytes);
     if (pl.tiles_per_split > groups) pl.tiles_per_split = groups;
+    if (digits) {
+        if (pl.input_terms != 3) return false;
+        // a wave looks at the forms of its key groups with one load; 32-bit lane offsets over 32 rows
+        if (ceil_div(pl.tiles_per_split, ws) > 64 || biq_key_row_stride(n) > (1u << 26)) return false;
+    }
     pl.chunk_splits = (groups + pl.tiles_per_split - 1) / pl.tiles_per_split;
     pl.row_blocks = (m + pl.rows_per_wg - 1) / pl.rows_per_wg;
     pl.batch_tiles = (batch + pl.batch_tile - 1) / pl.batch_tile;
     pl.lds_bytes = ws == 1 ? 24 * 1024 : 96 * 1024;   // partial sums of the wave groups, transpose patches (UnpackGeom::LDS_BYTES)
+    if (digits) {                                     // DigitGeom::LDS_BYTES
+        const int nout = r * (pl.batch_tile / 32);
+        pl.lds_bytes = ((4 / ws) * nout * (ws - 1) * 1024 + 4 * 32 * 36 + 4 * 256) * 4;
+    }
     const long long tasks = (long long)pl.row_blocks * pl.chunk_splits * pl.batch_tiles;
     if (tasks > (1ll << 30)) return false;
     // prepared input: 2 bytes per term and (padded column, padded element)
@@ -174,23 +187,27 @@ bool plan_finish(biq_plan& pl, int m, int n, int q, int batch, int mu) {
     return true;
 }
 
-// Where the lookup tables stop paying off (the crossover of Sec. IV-B / Fig. 10): estimated
-// run times of both paths from rates measured on MI355X.  Table lookups: about 13e12 lookups/s
-// for the conflict-free kernels (mu = 8, mu <= 5, mu = 6 up to 4 input vectors); 6.5e12 for the
-// generic one, which also streams keys at no more than about 0.25 TB/s; plus 6 us of launch
-// and table build.  Unpack + MFMA with the exact split: 2 * 3 flop per weight and padded input
-// vector (three bf16 terms) at 1.45e15 flop/s, plus 10 us (input split, launches, combining
-// partial sums).
-bool unpack_mfma_is_faster(int m, int n, int q, int batch, int mu) {
+// Estimated time (us) of the lookup-table plan `pl`, from rates measured on MI355X: where the tables
+// stop paying off (the crossover of Sec. IV-B / Fig. 10).  The kernels with one workgroup per CU: launch,
+// per round of workgroups over the CUs one table build (2 us; half tables 1.3, narrow keys 3) and 65e3
+// lookups per us and CU, 3 us for a second kernel.  (Estimated / measured: 5003 x 3001, 3 planes, 20
+// vectors 24 / 25.7; 16384 x 4096, 4, 32: 74 / 78; 1500 x 6000, 1, 40: 16 / 18.5; mu = 4: 192 x 7070, 2, 192:
+// 35 / 37; 351 x 3264, 4, 77: 17 / 15.5.)  The generic kernel: 6.5e12 lookups/s, keys at no more than
+// 0.25 TB/s, and 0.4 us per partial result a second kernel adds (320 x 12288, mu = 7, 4, 24: 38 / 33).
+double tables_estimate(const biq_plan& pl, int m, int n, int q, int batch, int mu) {
+    const double wgs = (double)pl.row_blocks * pl.chunk_splits * pl.batch_tiles;
+    const double rounds = (double)(long long)((wgs + kNumCu - 1) / kNumCu);
+    const int chunks = ceil_div(n, mu) < pl.chunks_per_tile ? ceil_div(n, mu) : pl.chunks_per_tile;
+    const double second = pl.chunk_splits > 1 ? 3.0 : 0.0;
+    const double rows = pl.rows_per_wg < m ? pl.rows_per_wg : m;
+    if (pl.kernel == KERNEL_GEMM8X2 || pl.kernel == KERNEL_GEMM8X2H)   // (a short row still takes its lanes' time)
+        return 3.4 + rounds * pl.tiles_per_split * ((pl.kernel == KERNEL_GEMM8X2H ? 1.3 : 2.0) +
+                                                    rows * q * pl.chunks_per_tile * 2 / 65e3) + second;
+    if (pl.kernel == KERNEL_WIDE) return 5.0 + rounds * (3.0 + rows * q * chunks * pl.batch_tile / 65e3) + second;
     const double weights = (double)q * m * n;
-    const double lookups = weights / mu * batch;
-    const bool tuned = mu == 8 || mu <= 5 || (mu == 6 && batch <= 4);
-    double t_lut = lookups / (tuned ? 13e12 : 6.5e12);
-    if (!tuned && t_lut < weights / 8 / 0.25e12) t_lut = weights / 8 / 0.25e12;
-    t_lut += 6e-6;
-    const double padded = (double)((batch + 31) / 32) * 32;
-    const double t_mfma = 10e-6 + 6.0 * weights * padded / 1.45e15;
-    return t_mfma < t_lut;
+    double t = weights / mu * batch / 6.5e6;
+    if (t < weights / 8 / 0.25e6) t = weights / 8 / 0.25e6;
+    return 6.0 + t + (pl.chunk_splits > 1 ? 2.0 + 0.4 * pl.chunk_splits : 0.0);
 }
 
 // The mapping of the unpack + MFMA kernel - column tile (32 or 64 input vectors), row tiles per
@@ -252,6 +269,52 @@ bool plan_unpack(biq_plan& pl, int m, int n, int q, int batch, int mu, int terms
     return plan_finish(pl, m, n, q, batch, mu);
 }
 
+// The mapping of the block-scaled matrix-core kernel (row_mode 1): the same candidates, and the same
+// kind of estimate (us; left in `est`).  MFMAs per wave: 5 digits x 4 steps per key group and tile, at
+// 33 clk and an overhead that falls with the tiles of a wave, but no less than 564 clk per step (the keys
+// are requested one key group ahead); 7.7 us for the two dispatches, 1 us per MB of padded X.  Fitted to
+// 1100 timed plans of 24 layer shapes (139 x 12096 .. 16384 x 4096, 7 .. 256 vectors, fp32- and bf16-valued):
+// the estimate's choice is on average 0.5 % and at most 10 % slower than the fastest.
+bool plan_digits(biq_plan& pl, int m, int n, int q, int batch, double& est) {
+    est = 1e30;
+    if (q > 4) return false;
+    pl = biq_plan{};
+    pl.kernel = KERNEL_UNPACK_MFMA;
+    pl.threads = kUnpackThreads;
+    pl.chunks_per_tile = kUnpackGroupBytes;
+    pl.input_terms = 3;
+    pl.row_mode = 1;
+    const int groups = (int)((biq_key_row_stride(n) + kUnpackGroupBytes - 1) / kUnpackGroupBytes);
+    for (int bt = 32; bt <= 64; bt += 32)
+        for (int ws = 1; ws <= 4; ws *= 2)
+            for (int r = 1; r <= 4; r *= 2)
+                for (int S = 1; S <= 16; S *= 2) {
+                    const int ct = bt / 32, tiles = q * r * ct;
+                    if (tiles > kDigitMaxTiles || (S > 1 && S * ws > groups)) continue;
+                    const int rows = (4 / ws) * 32 * r;
+                    const long long wgs = (long long)ceil_div(m, rows) * ceil_div(batch, bt) * S;
+                    if (wgs > 4ll * kNumCu && S > 1) continue;
+                    const int gpw = ceil_div(ceil_div(groups, S), ws);   // key groups per wave
+                    if (gpw > 64) continue;
+                    // workgroups of up to 4 tiles per wave share a CU
+                    double rounds = (double)ceil_div_ll(wgs, kNumCu);
+                    if (tiles <= 4) rounds = 1.0 + (rounds - 1.0) * 0.95;
+                    const double bpad_mb = (double)ceil_div(batch, bt) * bt * 4 / 1e6;   // MB per element of a vector
+                    double step = 165.0 * (1.043 * tiles + 1.011);
+                    if (step < 564.0) step = 564.0;
+                    double t = 7.7 + 0.99 * bpad_mb * n + rounds * (4.0 * gpw * step / 2100.0 + 0.5 * tiles);
+                    if (S > 1) t += 1.5 + 0.304 * (S + 1.0) * bpad_mb * m;
+                    if (t < est) {
+                        est = t;
+                        pl.batch_tile = bt;
+                        pl.wave_splits = ws;
+                        pl.rows_per_wg = rows;
+                        pl.tiles_per_split = ceil_div(groups, S);
+                    }
+                }
+    return est < 1e30 && plan_finish(pl, m, n, q, batch, 8);
+}
+
 // Default mapping.  Algorithm 2 leaves the tile sizes open; the choices here are:
 //  - batch tile: as many input vectors as one lookup can serve with a single wide LDS read
 //  - tile width: the largest power-of-two number of key units whose tables fit the LDS budget
@@ -260,16 +323,11 @@ bool plan_unpack(biq_plan& pl, int m, int n, int q, int batch, int mu, int terms
 //  - rows per workgroup: enough workgroups to fill the 256 CUs several times over
 bool plan_generic(biq_plan& pl, int m, int n, int q, int batch, int mu);
 
-bool plan_tuned(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tables_given) {
+bool plan_tables(biq_plan& pl, int m, int n, int q, int batch, int mu) {
     const int UK = unit_keys(mu);
     const int C = ceil_div(n, mu);
     const int E = 1 << mu;
     pl = biq_plan{};
-    if (!tables_given && q <= 4 && unpack_mfma_is_faster(m, n, q, batch, mu)) {
-        // Many input vectors: the contraction is compute bound and the matrix cores beat the
-        // table lookups (the crossover of Sec. IV-B / Fig. 10); exact input split.
-        return plan_unpack(pl, m, n, q, batch, mu, 3);
-    }
     if (mu == 8 && batch == 1 && q <= 4) {
         // GEMV: workgroups of 1024 threads, 128-chunk tiles, one workgroup per CU when the
         // rows allow it (every further round of workgroups pays the table build again).  With
@@ -447,9 +505,32 @@ bool plan_generic(biq_plan& pl, int m, int n, int q, int batch, int mu) {
 // The library's plan for a shape.  Should the tuned choice not pass plan_finish (a shape outside
 // what its kernel's 32-bit offsets cover), the generic kernel takes the call; false if that
 // fails too (the caller reports BIQ_EUNSUPPORTED, sizes read as 0).
+// Many input vectors: the contraction is compute bound and the matrix cores (block-scaled digits) beat
+// the table lookups, from the estimated times of both.
 bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tables_given = false) {
-    if (plan_tuned(pl, m, n, q, batch, mu, tables_given)) return true;
-    return plan_generic(pl, m, n, q, batch, mu);
+    const bool ok = plan_tables(pl, m, n, q, batch, mu) || plan_generic(pl, m, n, q, batch, mu);
+    if (tables_given || q > 4) return ok;
+    // (no digit plan is estimated below 8.3 us: small calls, where this search would show, skip it)
+    const double tables = ok ? tables_estimate(pl, m, n, q, batch, mu) : 1e30;
+    // (the narrow-key kernel keeps calls below 5e6 multiply-adds: 129 x 5000, 2 planes, 3 vectors at mu = 3
+    // 12.6 us with tables, 12.5 with digits; only mu = 1 would gain there, 25.6 to 12.5)
+    if (tables < 8.3 || (mu == 8 && batch == 1) || (pl.kernel == KERNEL_WIDE && (double)q * m * n * batch < 5e6))
+        return ok;
+    biq_plan d;
+    double est;
+    if (!plan_digits(d, m, n, q, batch, est)) {
+        // rows too long for those plans: the exact three-term split, 2 * 3 flop per weight and padded
+        // input vector at 1.45e9 flop/us
+        est = 10.0 + 6.0 * ((double)q * m * n) * (ceil_div(batch, 32) * 32.0) / 1.45e9;
+        if (est < tables && plan_unpack(d, m, n, q, batch, mu, 3)) {
+            pl = d;
+            return true;
+        }
+    } else if (est < tables) {
+        pl = d;
+        return true;
+    }
+    return ok;
 }
 
 // Bytes of the prepared-input area at the start of the workspace (unpack-MFMA plans only): the
@@ -548,6 +629,35 @@ biq_status run_unpack_mfma(const biq_plan& pl, const uint8_t* K, const float* al
     int* colexp = reinterpret_cast<int*>(reinterpret_cast<char*>(workspace) + plan_xfrag_bytes(pl));
     float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + plan_xf_bytes(pl));
 
+    if (pl.row_mode == 1) {
+        uint8_t* Xd = reinterpret_cast<uint8_t*>(workspace);
+        if (launch_xdigits(CT, X, Xd, colexp, n, batch, groups, pl.batch_tiles, s) != hipSuccess) return BIQ_EHIP;
+        DigitParams dp{};
+        dp.K = K;
+        dp.alpha = alpha;
+        dp.Xd = Xd;
+        dp.form = colexp;
+        dp.out = pl.chunk_splits > 1 ? partial : Y;
+        dp.m = m;
+        dp.batch = batch;
+        dp.stride_bytes = (uint32_t)biq_key_row_stride(n);
+        dp.groups = groups;
+        dp.gps = pl.tiles_per_split;
+        dp.splits = pl.chunk_splits;
+        dp.row_blocks = pl.row_blocks;
+        dp.col_groups = pl.batch_tiles;
+        dp.ntasks = pl.row_blocks * pl.chunk_splits * pl.batch_tiles;
+        dp.tasks_per_xcd = ceil_div(dp.ntasks, kNumXcd);
+        const int grid = dp.tasks_per_xcd * kNumXcd;
+        const int rpw = pl.rows_per_wg / ((4 / pl.wave_splits) * 32);
+        const auto launch = pl.wave_splits == 1 ? launch_digits_ws1
+                          : pl.wave_splits == 2 ? launch_digits_ws2 : launch_digits_ws4;
+        if (launch(q, rpw, CT, dp, grid, pl.lds_bytes, s) != hipSuccess) return BIQ_EHIP;
+        if (pl.chunk_splits > 1 &&
+            launch_reduce_splits(partial, Y, (long long)batch * m, pl.chunk_splits, s) != hipSuccess)
+            return BIQ_EHIP;
+        return BIQ_OK;
+    }
     if (launch_xsplit(pl.input_terms, CT, X, Xf, colexp, n, batch, steps, pl.batch_tiles * pl.batch_tile, s) !=
         hipSuccess)
         return BIQ_EHIP;

@@ -70,6 +70,14 @@ hipError_t launch_xsplit(int terms, int ct, const float* X, mfma_u32x4* Xf, int*
 hipError_t launch_unpack(int terms, int q, int rpw, int ct, int ws, const UnpackParams& up, int grid, int lds,
                          hipStream_t s);
 
+// ---- the same contraction on the block-scaled matrix instructions (unpack_mfma plans with row_mode 1) ----
+struct DigitParams;
+hipError_t launch_xdigits(int ct, const float* X, uint8_t* Xd, int* form, int n, int batch, int groups, int col_groups,
+                          hipStream_t s);
+hipError_t launch_digits_ws1(int q, int rpw, int ct, const DigitParams& p, int grid, int lds, hipStream_t s);
+hipError_t launch_digits_ws2(int q, int rpw, int ct, const DigitParams& p, int grid, int lds, hipStream_t s);
+hipError_t launch_digits_ws4(int q, int rpw, int ct, const DigitParams& p, int grid, int lds, hipStream_t s);
+
 // ---- the small kernels ----
 // Y[i] = sum over the `splits` partial results [splits][count], in a fixed order.
 hipError_t launch_reduce_splits(const float* partial, float* Y, long long count, int splits, hipStream_t s);
