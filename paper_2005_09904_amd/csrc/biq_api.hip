@@ -557,6 +557,20 @@ size_t plan_workspace(const biq_plan& pl, int m, int batch) {
 
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
+// mu = 8, tables in device memory: lookups read the tables where they lie instead of from a copy in LDS
+// (biq_gather.h) if there are few of them.  A copy costs 16-17 us per tile a workgroup walks; the reads,
+// counted per four input vectors, 3.5-4.3 us per million: 4096 x 2048, 2 planes, 4 vectors (2.1 million) 19.4 us
+// with the copy, 11.4 without; 2048 x 4096, 4, 2 (4.2) 20.0 / 19.4; 3000 x 1024, 4, 12 (4.6) 19.3 / 20.5;
+// 4096 x 2000, 4, 8 (8.2) 22.0 / 34.8; one vector, two tiles: 4096 x 4096, 4 planes (8.4) 32.8 / 30.0.
+constexpr long long kGatherLookups = 4200000;
+bool gather_tables(const biq_plan& pl, int m, int q, int batch, int C) {
+    if (pl.kernel != KERNEL_GEMV8 && pl.kernel != KERNEL_GEMV8H && pl.kernel != KERNEL_GEMM8X2 &&
+        pl.kernel != KERNEL_GEMM8X2H)
+        return false;
+    if (pl.row_mode == 0 || (long long)C * batch > (1ll << 20)) return false;   // at most 1 GiB of tables: 32-bit offsets
+    return (long long)m * q * C * ceil_div(batch, 4) <= kGatherLookups * pl.tiles_per_split;
+}
+
 // Kernel parameters of a lookup-table plan.
 void fill_query_params(QueryParams& qp, const biq_plan& pl, const uint8_t* K, const float* alpha, const float* X,
                        const float* LUT, float* out, int m, int n, int q, int batch, int mu) {
@@ -582,6 +596,7 @@ void fill_query_params(QueryParams& qp, const biq_plan& pl, const uint8_t* K, co
     qp.row_mode = pl.row_mode;
     qp.xcd_skew = pl.xcd_skew;
     qp.table_fill = pl.table_fill;
+    qp.gather = LUT && gather_tables(pl, m, q, batch, qp.C) && batch == 1;
 }
 
 // Plan of one problem of a grouped launch: mu = 8, at most 4 planes, a single dispatch without
@@ -725,7 +740,8 @@ biq_status run_query(bool fused, const uint8_t* K, const float* alpha, const flo
     const int grid = qp.tasks_per_xcd * kNumXcd;
 
     hipError_t e;
-    if (pl.kernel == KERNEL_GEMV8) e = launch_gemv8(fused, q, qp, grid, pl.threads, pl.lds_bytes, s);
+    if (!fused && batch > 1 && gather_tables(pl, m, q, batch, qp.C)) e = launch_gather(pl.kernel == KERNEL_GEMM8X2H, q, qp, s);
+    else if (pl.kernel == KERNEL_GEMV8) e = launch_gemv8(fused, q, qp, grid, pl.threads, pl.lds_bytes, s);
     else if (pl.kernel == KERNEL_GEMV8H) e = launch_gemv8h(fused, q, qp, grid, pl.threads, pl.lds_bytes, s);
     else if (pl.kernel == KERNEL_WIDE) e = launch_wide(fused, mu, qp, grid, pl.threads, pl.lds_bytes, s);
     else if (pl.kernel == KERNEL_GEMM8X2H) e = launch_gemm8x2h(fused, q, qp, grid, pl.threads, pl.lds_bytes, s);

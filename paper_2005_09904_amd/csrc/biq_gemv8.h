@@ -18,7 +18,7 @@
 #pragma once
 
 #include "biq_common.h"
-#include "biq_kernels.h"
+#include "biq_gather.h"
 
 namespace biq {
 
@@ -219,6 +219,23 @@ __device__ __forceinline__ void gemv8_body(const QueryParams& p, const int wg) {
     auto lookup16 = [&](const u32x4& k) -> float {
         const uint32_t w[4] = {k.x, k.y, k.z, k.w};
         float a0, a1;
+        if (!FUSED && p.gather) {   // (latency mode: one tile)
+            float v[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const uint32_t e = (uint32_t)((j + rho) & 3);
+                v[j] = gather_entry(p, (uint32_t)(tile0 * kGemvTileChunks + 16 * L + (j & ~3)) + e,
+                                    (w[j >> 2] >> (8 * e)) & 255u);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // all 16 reads before the first use
+            a0 = v[0]; a1 = v[1];
+#pragma unroll
+            for (int j = 2; j < 16; ++j) {
+                if (j & 1) a1 += v[j];
+                else a0 += v[j];
+            }
+            return a0 + a1;
+        }
 #pragma unroll
         for (int td = 0; td < 4; ++td) {
 #pragma unroll
@@ -270,7 +287,7 @@ __device__ __forceinline__ void gemv8_body(const QueryParams& p, const int wg) {
         if constexpr (FUSED) {
             if (x_first) gemv8_job_build(p, lds_bytes, tile * kGemvTileChunks, tid, xf);
             else gemv8_build_tile(p, lds_bytes, tile * kGemvTileChunks, tid, nthreads);
-        } else {
+        } else if (!p.gather) {
             gemv8_copy_tile(p, lds_bytes, tile * kGemvTileChunks, tid, nthreads);
         }
         __syncthreads();

@@ -152,11 +152,30 @@ __device__ __forceinline__ void gemv8h_body(const QueryParams& p, const int wg) 
         base[1][te] = base[0][te] | 0x10000u;
     }
 
+    int tl = tile0;  // the tile being worked on (row_mode 1)
+
     // The 16 lookups of a lane's 16 key bytes, in three phases - all addresses, all reads, all
     // signed additions - so that the 16 LDS reads are in flight together (written lookup by
     // lookup, the compiler keeps at most three in flight and the loop runs at LDS latency).
     auto lookup16 = [&](const u32x4& k) -> float {
         const uint32_t w[4] = {k.x, k.y, k.z, k.w};
+        if (!FUSED && p.gather) {
+            float v[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const uint32_t e = (uint32_t)((j + rho) & 3);
+                v[j] = gather_entry(p, (uint32_t)(tl * kGemvHalfTileChunks + 16 * L + (j & ~3)) + e,
+                                    (w[j >> 2] >> (8 * e)) & 255u);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // all 16 reads before the first use
+            float a0 = 0.0f, a1 = 0.0f;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                if (j & 1) a1 += v[j];
+                else a0 += v[j];
+            }
+            return a0 + a1;
+        }
         uint32_t sg[4], addr[16];
         float v[16];
 #pragma unroll
@@ -222,7 +241,7 @@ __device__ __forceinline__ void gemv8h_body(const QueryParams& p, const int wg) 
         if constexpr (FUSED) {
             if (x_ahead) gemv8h_job_build(p, lds_bytes, tile * kGemvHalfTileChunks, tid, xa);
             else gemv8h_build_tile(p, lds_bytes, tile * kGemvHalfTileChunks, tid, nthreads);
-        } else {
+        } else if (!p.gather) {
             gemv8h_copy_tile(p, lds_bytes, tile * kGemvHalfTileChunks, tid, nthreads);
         }
         __syncthreads();
@@ -236,6 +255,12 @@ __device__ __forceinline__ void gemv8h_body(const QueryParams& p, const int wg) 
                 half_table_prepare(kw[i], idx, sgn);
 #pragma unroll
                 for (int te = 0; te < 4; ++te) {
+                    if (!FUSED && p.gather) {
+                        const uint32_t e = (uint32_t)((te + td1) & 3);
+                        acc += gather_entry(p, (uint32_t)(tile * kGemvHalfTileChunks + 4 * lane) + e,
+                                            (kw[i] >> (8 * e)) & 255u);
+                        continue;
+                    }
                     const uint32_t addr = __builtin_amdgcn_perm(idx, base1[te], sel1[te]) | td_bit15;
                     const float v = lds_read_abs(addr);
                     acc = fmaf(v, half_table_sign(sgn, sgn_sel1[te]), acc);
@@ -252,7 +277,6 @@ __device__ __forceinline__ void gemv8h_body(const QueryParams& p, const int wg) 
         return;
     }
 
-    int tl = tile0;  // the tile being worked on
     // row sums carried from tile to tile (only with several tiles per workgroup): behind the tables
     float* const yacc = reinterpret_cast<float*>(lds_bytes + kGemvHalfTileBytes);
     // LSTM: the workgroup's hidden units [u0, u0 + nunits), one unit (4 gate rows) per step
@@ -344,7 +368,7 @@ __device__ __forceinline__ void gemv8h_body(const QueryParams& p, const int wg) 
             } else {
                 gemv8h_build_tile(p, lds_bytes, tl * kGemvHalfTileChunks, tid, nthreads);
             }
-        } else {
+        } else if (!p.gather) {
             gemv8h_copy_tile(p, lds_bytes, tl * kGemvHalfTileChunks, tid, nthreads);
         }
         BIQ_STAMP(p, 4);

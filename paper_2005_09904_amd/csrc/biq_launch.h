@@ -55,6 +55,9 @@ hipError_t launch_gemv8h(bool fused, int q, const QueryParams& p, int grid, int 
 hipError_t launch_gemm8x2(bool fused, int q, const QueryParams& p, int grid, int threads, int lds, hipStream_t s);
 hipError_t launch_gemm8x2h(bool fused, int q, const QueryParams& p, int grid, int threads, int lds, hipStream_t s);
 
+// few lookups into given tables (mu = 8, several input vectors; half: in the order of gemm8x2_half)
+hipError_t launch_gather(bool half, int q, const QueryParams& p, hipStream_t s);
+
 // ---- fused LSTM cell step (half-table kernels with the cell update as epilogue) ----
 hipError_t launch_lstm8h(int q, const QueryParams& p, int grid, int threads, int lds, hipStream_t s);
 hipError_t launch_lstm8x2h(int q, const QueryParams& p, int grid, int threads, int lds, hipStream_t s);
