@@ -93,9 +93,14 @@ hipError_t launch_build_lut(int mu, const float* X, float* LUT, int n, int batch
 hipError_t launch_quantize(const float* W, uint32_t* K, float* alpha, int m, int n, int q, int stride_dw,
                            hipStream_t s) {
     if (n > kQuantMaxN) return hipErrorInvalidValue;
-#define BIQ_QUANT_CASE(EPT, WPR)                                                                   \
-    hipLaunchKernelGGL((quantize_wave_kernel<EPT, WPR>), dim3((m + (4 / WPR) - 1) / (4 / WPR)),   \
-                       dim3(kQuantThreads), 0, s, W, K, alpha, m, n, q, stride_dw)
+#define BIQ_QUANT_CASE(EPT, WPR)                                                                             \
+    do {                                                                                                     \
+        const dim3 grid((m + (4 / WPR) - 1) / (4 / WPR));                                                    \
+        if (n == 64 * EPT * WPR)                                                                             \
+            hipLaunchKernelGGL((quantize_wave_kernel<EPT, WPR, true>), grid, dim3(kQuantThreads), 0, s, W, K, alpha, m, n, q, stride_dw);  \
+        else                                                                                                 \
+            hipLaunchKernelGGL((quantize_wave_kernel<EPT, WPR, false>), grid, dim3(kQuantThreads), 0, s, W, K, alpha, m, n, q, stride_dw); \
+    } while (0)
     if (n <= 64 * 8) BIQ_QUANT_CASE(8, 1);
     else if (n <= 64 * 16) BIQ_QUANT_CASE(16, 1);
     else if (n <= 64 * 32) BIQ_QUANT_CASE(32, 1);
