@@ -143,7 +143,11 @@ typedef struct {
                             (4 / wave_splits) * 32 * r with r row tiles per wave and plane,
                             r in {1, 2, 4}, q * r <= 4 (row_mode 1: q * r * batch_tile / 32 <= 8 and
                             at most 64 key groups per wave)                                  */
-    int table_fill;      /* GEMV kernel, fused tables: 0 = every entry from the chunk's pair sums (a direct,
+    int table_fill;      /* 2 = no tables (what the library chooses for few input vectors where it is faster;
+                            any kernel but unpack_mfma, any mu, q <= 4): the inputs become 6-bit digits
+                            (see row_mode 1 of unpack_mfma) in LDS and the keys 4-bit weights for the matrix
+                            cores, in one dispatch with a mapping of its own; the other fields describe
+                            the table kernel that biq_query runs for the shape.  GEMV kernel, fused tables: 0 = every entry from the chunk's pair sums (a direct,
                             GEMM-like fill), 1 = the order of Algorithm 1: a block's first entry, then
                             each further entry of the lower half from an earlier one by adding 2 x_t,
                             the upper half by negation.  Same tables up to rounding; kept selectable

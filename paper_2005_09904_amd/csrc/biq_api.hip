@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <math.h>
+
 #include "biq_launch.h"
 // kernel headers: only their geometry constants are used here (no kernel is instantiated in this file)
 #include "biq_gemv8.h"
@@ -13,6 +15,7 @@
 #include "biq_quantize.h"
 #include "biq_grouped.h"
 #include "biq_digit_mfma.h"
+#include "biq_direct.h"
 
 namespace {
 
@@ -116,6 +119,67 @@ inline int plan_lds_bytes(const biq_plan& pl, int mu) {
     return b > (1ll << 30) ? (1 << 30) : (int)b;
 }
 
+// Mapping of the direct kernel (biq_direct.h) for a shape, with its estimated time (us); false if its
+// operands do not fit the LDS.  Candidates: the many-rows instantiation, and one row tile per wave with 1 .. 8
+// groups of waves along the row; as many row steps per workgroup as leave at most 256 workgroups.  A row step costs
+// its chunks (matrix pipe, expansion or LDS of the two waves per SIMD, or the latency of the next keys) and an
+// epilogue; keys stream at 3.3 TB/s; the split of the inputs 1.9 us per 512 blocks.  Fitted to 94 random
+// shapes (128 .. 280000 rows, 128 .. 16000 columns, 1 .. 48 vectors): 13 % rms.
+struct DirectGeom {
+    int vecs, batch_tiles, chunks, ksplit, steps, row_blocks, lds;
+    int uc;                  // chunks requested together
+    bool many;               // the many-rows instantiation
+    double est;
+};
+// Input vectors of one workgroup whose digits fit the LDS beside the exchange buffers.
+int direct_max_vectors(int n) {
+    const long long spare = kLdsPerCu - 2 * kDirectWaves * 15 * 16 * 4;
+    const long long v = spare / direct_lds_bytes(ceil_div(n, 512), 1, 1, false);
+    return (int)(v < kDirectMaxVec ? v : kDirectMaxVec);
+}
+bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
+    if (q > 4 || biq_key_row_stride(n) > (1u << 26)) return false;
+    const long long chunks = ceil_div(n, 512);
+    const int vmax = direct_max_vectors(n);
+    if (vmax == 0) return false;
+    g.chunks = (int)chunks;
+    g.batch_tiles = ceil_div(batch, vmax);
+    g.vecs = ceil_div(batch, g.batch_tiles);
+    g.batch_tiles = ceil_div(batch, g.vecs);
+    if (g.batch_tiles > 65535) return false;
+    const int nt = ceil_div(g.vecs, 3);
+    const double mem = (double)q * m * biq_key_row_stride(n) * g.batch_tiles / 3.3e6;
+    g.est = 1e30;
+    for (int many = 1; many >= 0; --many)
+        for (int ks = 1; ks <= (many ? 1 : kDirectWaves) && (ks == 1 || ks <= g.chunks); ks *= 2) {
+            const int rpw = many ? direct_rpw(q, nt) : 1, uc = many ? direct_uc(nt) : 1;
+            if (many && rpw == 1 && uc == 1) break;      // the few-rows instantiation itself
+            const long long all_steps = ceil_div(m, kDirectWaves / ks * rpw * 16);
+            long long steps = ceil_div_ll(all_steps * g.batch_tiles, kNumCu);
+            if (steps > all_steps) steps = all_steps;
+            const double rounds = (double)ceil_div_ll(ceil_div_ll(all_steps, steps) * g.batch_tiles, kNumCu);
+            const int rt = q * rpw, upg = ceil_div(ceil_div(g.chunks, uc), ks);
+            double clk = 22.0 * rt * (16 * nt > 32 ? 16 * nt : 32);
+            if (clk < 860.0 * nt) clk = 860.0 * nt;
+            if (clk < 742.0) clk = 742.0;
+            const double work =
+                rounds * steps * (upg * uc * clk / 2200.0 + 0.012 * rt * nt + (ks > 1 ? 0.36 : 0.0));
+            // (both together, smoothly: of two mappings that memory bounds, the one with less work)
+            const double t = 1.3 + 0.36 * (nt - 1) + 1.94 * rounds * ceil_div(g.chunks * g.vecs, 4 * kDirectWaves) +
+                             cbrt(work * work * work + mem * mem * mem);
+            if (t < g.est) {
+                g.est = t;
+                g.many = many != 0;
+                g.ksplit = ks;
+                g.uc = uc;
+                g.steps = (int)steps;
+                g.row_blocks = (int)ceil_div_ll(all_steps, steps);
+            }
+        }
+    g.lds = (int)direct_lds_bytes(g.chunks, g.vecs, 1, g.ksplit > 1);
+    return g.est < 1e30;
+}
+
 // Completes the derived fields and checks a plan against the shape and device limits.
 bool plan_finish(biq_plan& pl, int m, int n, int q, int batch, int mu) {
     const int UK = unit_keys(mu);
@@ -123,7 +187,12 @@ bool plan_finish(biq_plan& pl, int m, int n, int q, int batch, int mu) {
     if (pl.kernel < 0 || pl.kernel >= KERNEL_COUNT) return false;
     if (pl.kernel == KERNEL_UNPACK_MFMA) return plan_finish_unpack(pl, m, n, q, batch);
     if (pl.wave_splits != 0 || pl.input_terms != 0) return false;  // unpack_mfma only
-    if (pl.table_fill != 0 && !(pl.table_fill == 1 && pl.kernel == KERNEL_GEMV8 && pl.row_mode == 0)) return false;
+    if (pl.table_fill == 2) {
+        DirectGeom g;
+        if (!direct_geometry(g, m, n, q, batch)) return false;
+    } else if (pl.table_fill != 0 && !(pl.table_fill == 1 && pl.kernel == KERNEL_GEMV8 && pl.row_mode == 0)) {
+        return false;
+    }
     if (pl.threads < 64 || pl.threads > 1024 || pl.threads % 64) return false;
     if (pl.kernel == KERNEL_GEMV8) {
         // mu = 8, one input vector, at most 4 planes; one 128-chunk tile per workgroup
@@ -510,26 +579,54 @@ bool plan_generic(biq_plan& pl, int m, int n, int q, int batch, int mu) {
 bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tables_given = false) {
     const bool ok = plan_tables(pl, m, n, q, batch, mu) || plan_generic(pl, m, n, q, batch, mu);
     if (tables_given || q > 4) return ok;
-    // (no digit plan is estimated below 8.3 us: small calls, where this search would show, skip it)
     const double tables = ok ? tables_estimate(pl, m, n, q, batch, mu) : 1e30;
-    // (the narrow-key kernel keeps calls below 5e6 multiply-adds: 129 x 5000, 2 planes, 3 vectors at mu = 3
-    // 12.6 us with tables, 12.5 with digits; only mu = 1 would gain there, 25.6 to 12.5)
-    if (tables < 8.3 || (mu == 8 && batch == 1) || (pl.kernel == KERNEL_WIDE && (double)q * m * n * batch < 5e6))
+    // Few vectors, no tables: the plan stays the table kernel's (what biq_query runs for the shape), marked
+    // by table_fill = 2.  Fewer than 128 rows (less than one row step of a workgroup) keep the tables, whose sums
+    // biq_query repeats bit for bit.
+    if (mu == 8 && batch == 1) {
+        // One vector (keys from memory): rows beyond one half-table tile whose inputs the table kernels cannot
+        // read 16 bytes at a time (n % 4; 5000 x 3001, 3 planes 11.9 us with tables, 6.4 without; 236 x 4414, 2:
+        // 14.2 / 5.0; 4928 x 9573, 1: 10.3 / 8.2), up to 24 MB of keys.  Others: 16384 x 4096, 2: 8.4 / 8.6;
+        // 452 x 832, 3: 3.9 / 4.6; 15265 x 10112, 4, 77 MB: 22.5 / 28.8.
+        const long long keys = (long long)q * m * (long long)biq_key_row_stride(n);
+        if (ok && m >= 128 && n > 2048 && n % 4 != 0 && keys <= 24000000 && direct_max_vectors(n) > 0)
+            pl.table_fill = 2;
         return ok;
-    biq_plan d;
-    double est;
-    if (!plan_digits(d, m, n, q, batch, est)) {
-        // rows too long for those plans: the exact three-term split, 2 * 3 flop per weight and padded
-        // input vector at 1.45e9 flop/us
-        est = 10.0 + 6.0 * ((double)q * m * n) * (ceil_div(batch, 32) * 32.0) / 1.45e9;
-        if (est < tables && plan_unpack(d, m, n, q, batch, mu, 3)) {
+    }
+    DirectGeom g;
+    const double direct = ok && m >= 128 && direct_geometry(g, m, n, q, batch) ? g.est : 1e30;
+    // (no digit plan is estimated below 8.3 us: small calls, where this search would show, skip it; the
+    // narrow-key kernel keeps calls below 5e6 multiply-adds that direct does not take: 129 x 5000, 2
+    // planes, 3 vectors at mu = 3 12.6 us with tables, 12.5 with digits)
+    // the batched mu = 8 table kernels keep what is not clearly slower (1145 x 7117, 4 planes, 7 vectors 12.0 us with
+    // tables, 12.8 without; 10240 x 1216, 2, 12: 17.5 / 8.6; 32000 x 1024, 3, 6: 18.8 / 7.0) and calls up to 6.5 us
+    // (1541 x 384, 2, 4: 4.3 / 4.6); narrow keys and the generic kernel gain almost always (1790 x 316, mu = 7, 3, 5:
+    // 18.6 / 4.7)
+    const bool tuned = pl.kernel == KERNEL_GEMM8X2 || pl.kernel == KERNEL_GEMM8X2H;
+    // ... except one vector on short rows of one plane or few rows (310460 x 192, 1 plane, mu = 4: 7.5 / 13.9; 982 x
+    // 144, 2: 3.7 / 4.0; but 68544 x 206, 3, mu = 6: 13.6 / 6.5)
+    const bool brief = batch == 1 && n <= 512 && (q == 1 || (long long)m * q < 4096);
+    const bool use_direct = tuned ? tables > 6.5 && direct < 0.8 * tables : !brief && direct < 0.95 * tables;
+    const double few = use_direct ? direct : tables;
+    if (few >= 8.3 && !(pl.kernel == KERNEL_WIDE && (double)q * m * n * batch < 5e6)) {
+        biq_plan d;
+        double est;
+        if (!plan_digits(d, m, n, q, batch, est)) {
+            // rows too long for those plans: the exact three-term split, 2 * 3 flop per weight and padded
+            // input vector at 1.45e9 flop/us
+            est = 10.0 + 6.0 * ((double)q * m * n) * (ceil_div(batch, 32) * 32.0) / 1.45e9;
+            if (est < few && plan_unpack(d, m, n, q, batch, mu, 3)) {
+                pl = d;
+                return true;
+            }
+        } else if (est < (use_direct ? 1.25 * few : few)) {
+            // (a margin against direct's estimate, which is the looser one and misses on the slow side for long
+            // rows with several tiles of vectors: 14464 x 10824, 2 planes, 20 vectors 101 us instead of 36)
             pl = d;
             return true;
         }
-    } else if (est < tables) {
-        pl = d;
-        return true;
     }
+    if (use_direct) pl.table_fill = 2;
     return ok;
 }
 
@@ -705,6 +802,30 @@ biq_status run_unpack_mfma(const biq_plan& pl, const uint8_t* K, const float* al
     return BIQ_OK;
 }
 
+// Few input vectors, no tables (table_fill 2).
+biq_status run_direct(const uint8_t* K, const float* alpha, const float* X, float* out, int m, int n, int q, int batch,
+                      hipStream_t s) {
+    DirectGeom g;
+    if (!direct_geometry(g, m, n, q, batch)) return BIQ_EUNSUPPORTED;
+    DirectParams p{};
+    p.K = K;
+    p.alpha = alpha;
+    p.X = X;
+    p.out = out;
+    p.m = m;
+    p.n = n;
+    p.batch = batch;
+    p.stride_bytes = (uint32_t)biq_key_row_stride(n);
+    p.chunks = g.chunks;
+    p.chunks_inv = (uint32_t)((((uint64_t)1 << 32) + g.chunks - 1) / g.chunks);   // (not used for one chunk)
+    p.vecs = g.vecs;
+    p.log_ksplit = ilog2(g.ksplit);
+    p.units_per_group = ceil_div(ceil_div(g.chunks, g.uc), g.ksplit);
+    p.steps = g.steps;
+    const auto launch = g.many ? launch_direct_many : launch_direct_few;
+    return launch(q, ceil_div(g.vecs, 3), p, dim3(g.row_blocks, g.batch_tiles), g.lds, s) == hipSuccess ? BIQ_OK : BIQ_EHIP;
+}
+
 biq_status run_query(bool fused, const uint8_t* K, const float* alpha, const float* X,
                      const float* LUT, float* Y, int m, int n, int q, int batch, int mu,
                      const biq_plan* user_plan, void* workspace, size_t workspace_bytes,
@@ -730,6 +851,7 @@ biq_status run_query(bool fused, const uint8_t* K, const float* alpha, const flo
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (pl.kernel == KERNEL_UNPACK_MFMA)
         return run_unpack_mfma(pl, K, alpha, X, Y, m, n, q, batch, workspace, s);
+    if (pl.table_fill == 2) return run_direct(K, alpha, X, Y, m, n, q, batch, s);
 
     QueryParams qp{};
     fill_query_params(qp, pl, K, alpha, X, LUT, pl.chunk_splits > 1 ? reinterpret_cast<float*>(workspace) : Y, m, n, q,

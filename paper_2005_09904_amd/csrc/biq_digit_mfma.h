@@ -77,7 +77,7 @@ struct DigitParams {
 
 // A block of 32 elements -> digits, handed to emit(d, 32 six-bit values in operand order) one after the
 // other; returns the block's scale byte (digit d's is 5 d less), 255 (NaN) for a block with Inf or NaN.
-template <typename Emit>
+template <int UNROLL, typename Emit>
 __device__ __forceinline__ uint32_t digit_split(const float (&x)[32], Emit&& emit) {
     uint32_t mb = 0;
 #pragma unroll
@@ -93,8 +93,7 @@ __device__ __forceinline__ uint32_t digit_split(const float (&x)[32], Emit&& emi
         hi[u] = x[e + 4] * norm;
     }
     float scale = 1.0f;
-    // (not unrolled: it runs once per thread, from a cold instruction cache)
-#pragma unroll 1
+#pragma unroll UNROLL
     for (int d = 0; d < kDigits; ++d) {
         const mfma_u32x6 p = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(lo, hi, scale);
         emit(d, p);
@@ -190,7 +189,7 @@ __global__ __launch_bounds__(256 * CT) void xdigits_kernel(const float* __restri
         }
         return;
     }
-    area[kDigitScaleOffset + lane * 4 + s] = (uint8_t)digit_split(x, [&](int d, const mfma_u32x6& p) {
+    area[kDigitScaleOffset + lane * 4 + s] = (uint8_t)digit_split<kDigits>(x, [&](int d, const mfma_u32x6& p) {
         uint8_t* dst = area + s * kDigitStepBytes + d * kDigitBytes;
         mfma_u32x4 p0;
         p0.x = p[0]; p0.y = p[1]; p0.z = p[2]; p0.w = p[3];

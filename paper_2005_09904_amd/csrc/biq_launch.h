@@ -81,6 +81,11 @@ hipError_t launch_digits_ws1(int q, int rpw, int ct, const DigitParams& p, int g
 hipError_t launch_digits_ws2(int q, int rpw, int ct, const DigitParams& p, int grid, int lds, hipStream_t s);
 hipError_t launch_digits_ws4(int q, int rpw, int ct, const DigitParams& p, int grid, int lds, hipStream_t s);
 
+// ---- few input vectors on the block-scaled matrix instructions, one dispatch (plans with table_fill 2) ----
+struct DirectParams;
+hipError_t launch_direct_few(int q, int nt, const DirectParams& p, dim3 grid, int lds, hipStream_t s);
+hipError_t launch_direct_many(int q, int nt, const DirectParams& p, dim3 grid, int lds, hipStream_t s);
+
 // ---- the small kernels ----
 // Y[i] = sum over the `splits` partial results [splits][count], in a fixed order.
 hipError_t launch_reduce_splits(const float* partial, float* Y, long long count, int splits, hipStream_t s);

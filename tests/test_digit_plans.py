@@ -49,3 +49,24 @@ def test_refused_fields_and_long_rows(biq):
     p = biq.biq_plan_get_mfma(4096, 4096, 3, 32, 8, 3)
     assert p.row_mode == 0 and p.input_terms == 3
     assert biq.biq_plan_get(16384, 4096, 2, 128, 8).row_mode == 1
+
+
+def test_direct_plans(biq):
+    """table_fill = 2: which plans take it, where the library chooses it, and that the plan is otherwise the table
+    kernel's, workspace included."""
+    for (m, n, q, b, mu, want) in [(512, 512, 1, 1, 8, 0), (2048, 2048, 2, 1, 8, 0), (5000, 3001, 2, 1, 8, 2), (32000, 1024, 3, 6, 8, 2),
+                                   (1 << 20, 2048, 2, 1, 8, 0), (5003, 3001, 3, 7, 6, 2), (90, 1000, 2, 3, 4, 0),
+                                   (50, 600, 1, 2, 6, 0), (100, 700, 3, 6, 8, 0), (200, 1500, 2, 1, 8, 0)]:
+        p, lut = biq.biq_plan_get(m, n, q, b, mu), biq.biq_plan_get_lut(m, n, q, b, mu)
+        assert p.table_fill == want and lut.table_fill == 0
+        want_fields = dict(lut.as_dict(), table_fill=want)
+        assert p.as_dict() == want_fields
+        assert biq.biq_plan_workspace_bytes(p, m, b) == biq.biq_plan_workspace_bytes(lut, m, b)
+    p = biq.biq_plan_get_lut(300, 700, 5, 2, 8)              # five planes
+    p.table_fill = 2
+    with pytest.raises(biq.BiqError):
+        biq.biq_plan_check(300, 700, 5, 2, 8, p)
+    p = biq.biq_plan_get_lut(300, 42000, 1, 1, 8)            # a vector's digits do not fit the LDS
+    p.table_fill = 2
+    with pytest.raises(biq.BiqError):
+        biq.biq_plan_check(300, 42000, 1, 1, 8, p)
