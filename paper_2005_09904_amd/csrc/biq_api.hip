@@ -893,6 +893,20 @@ biq_status unpack_keys_any(const uint8_t* K, KEY* keys, int m, int n, int q, int
 }
 
 // ---- the allocation-free entry point's scratch buffer -------------------------------------
+// The plan of biq_gemm_noalloc where the digit plan does not fit its buffer (digits and partial sums of
+// wide batches): the tables, or - where a three-term matrix product is faster than they are - that one, from
+// lookups/s (13e12 for the conflict-free kernels, 6.5e12 and no more than 0.25 TB/s of keys for the generic
+// one, plus 6 us) against 2 * 3 flop per weight and padded vector at 1.45e15 flop/s plus 10 us.
+bool plan_small_workspace(biq_plan& pl, int m, int n, int q, int batch, int mu) {
+    const double weights = (double)q * m * n;
+    const bool tuned = mu == 8 || mu <= 5 || (mu == 6 && batch <= 4);
+    double t_lut = weights / mu * batch / (tuned ? 13e12 : 6.5e12);
+    if (!tuned && t_lut < weights / 8 / 0.25e12) t_lut = weights / 8 / 0.25e12;
+    const double t_mfma = 10e-6 + 6.0 * weights * (ceil_div(batch, 32) * 32.0) / 1.45e15;
+    if (q <= 4 && t_mfma < t_lut + 6e-6) return plan_unpack(pl, m, n, q, batch, mu, 3);
+    return plan_default(pl, m, n, q, batch, mu, true);
+}
+
 // Workspace of biq_gemm_noalloc: device memory that belongs to the library's code object, one
 // copy per GPU, held until the process ends.  In host code the array's name is only a handle
 // for hipGetSymbolAddress; the device address is looked up once per device and kept.
@@ -1074,8 +1088,12 @@ biq_status biq_gemm_noalloc(const uint8_t* K, const float* alpha, const float* X
     if (!shape_ok(m, n, q, batch, mu)) return BIQ_EINVAL;
     biq_plan pl;
     if (!plan_default(pl, m, n, q, batch, mu, false)) return BIQ_EUNSUPPORTED;
-    const size_t need = plan_workspace(pl, m, batch);
-    if (need > kScratchBytes) return BIQ_EWORKSPACE;  // beyond the fixed buffer: use biq_gemm with a workspace
+    size_t need = plan_workspace(pl, m, batch);
+    if (need > kScratchBytes) {
+        if (!plan_small_workspace(pl, m, n, q, batch, mu)) return BIQ_EWORKSPACE;   // use biq_gemm with a workspace
+        need = plan_workspace(pl, m, batch);
+        if (need > kScratchBytes) return BIQ_EWORKSPACE;
+    }
     void* ws = nullptr;
     if (need > 0 && scratch_address(&ws) != hipSuccess) return BIQ_EHIP;
     // Every kernel writes the part of the workspace it later reads (split input, partial sums) in

@@ -1,0 +1,24 @@
+"""biq_gemm_noalloc where the digit plan needs more than the fixed buffer: a plan that fits it takes the call."""
+import pytest
+
+from gpu_util import assert_within_tolerance, device_inputs, gpu_pack
+from test_zz_no_alloc import _inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,n,q,b,mu", [(1006, 23448, 1, 207, 5), (2499, 11820, 1, 392, 2)])
+def test_noalloc_takes_a_smaller_plan(oracle, m, n, q, b, mu):
+    import torch
+
+    import paper_2005_09904_amd as biq
+
+    assert biq.biq_workspace_bytes(m, n, q, b, mu) > biq.biq_noalloc_scratch_bytes()
+    print("noalloc m=%d n=%d q=%d b=%d mu=%d" % (m, n, q, b, mu), flush=True)
+    B, alpha, X = _inputs(m, n, q, b, 77)
+    Bd, ad, Xd = device_inputs(B, alpha, X)
+    K = gpu_pack(biq, Bd)
+    Y = torch.full((b, m), float("nan"), dtype=torch.float32, device="cuda")
+    biq.biq_gemm_noalloc(K, ad, Xd, Y, m, n, q, b, mu)
+    torch.cuda.synchronize()
+    assert_within_tolerance(Y[:4].cpu().numpy(), oracle.gemm_dense(B, alpha, X[:4]), alpha, X[:4], "noalloc")
