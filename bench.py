@@ -358,24 +358,26 @@ def main() -> int:
                                      "cfg5_ffn_up_q2_b128", "cfg5_ffn_down_q2_b128"]]
         rows += [CONFIGS["cfg5_ffn_up_q2_b128"].with_mu(6), CONFIGS["cfg5_ffn_up_q2_b128"].with_mu(4)]
         MFMA_F16_PEAK_TFLOPS = 2500.0
+        MFMA_F4_PEAK_TFLOPS = 10000.0
         for w in rows:
             default = biq.biq_plan_get(w.m, w.n, w.q, w.batch, w.mu)
             lut = biq.biq_plan_get_lut(w.m, w.n, w.q, w.batch, w.mu)
-            # the library's choice first; where that is the unpack + MFMA kernel (exact input
-            # split), the lookup-table kernel on the same inputs as a second row and the two-term
+            # the library's choice first; where that is the unpack + MFMA kernel (block-scaled
+            # digits), the lookup-table kernel on the same inputs as a second row and the two-term
             # variant of the matrix-core kernel, which only an explicit plan selects, as a third
             plans = [(None, "fp32")]
             if default.kernel != lut.kernel:
                 plans += [(lut, "fp32"), (biq.biq_plan_get_mfma(w.m, w.n, w.q, w.batch, w.mu, 2), "fp32")]
                 if w.mu == 8:
                     # the library's plan again on fp32 inputs that hold fp16 / bf16 values (activations
-                    # computed in half precision): the exact split has zero third (and second) terms
+                    # computed in half precision): their last digits are zero
                     # there and the kernel skips them
                     plans += [(None, "fp16"), (None, "bf16"),
                               (biq.biq_plan_get_mfma(w.m, w.n, w.q, w.batch, w.mu, 2), "fp16")]
             for plan, x_values in plans:
                 kname = biq.biq_kernel_name((plan or default).kernel)
-                terms = (plan or default).input_terms
+                digits = (plan or default).row_mode == 1      # block-scaled 6-bit digits instead of 16-bit terms
+                terms = 5 if digits else (plan or default).input_terms
                 copies = max(1, min(64, (512 * 1024 * 1024) // w.key_bytes + 1))
                 p = Problem(biq, torch, w, copies, real_first=False, plan=plan, x_values=x_values)
                 steps = 200 if w.lookups < 1e9 else 20
@@ -388,12 +390,12 @@ def main() -> int:
                 s["default_plan"] = plan is None
                 if kname == "unpack_mfma":
                     # dense contraction: 2 flop per weight and input vector, times the 16-bit
-                    # terms of x (3 bf16: exact; 2 fp16: on request), on columns padded to the
+                    # terms of x (3 bf16, or 2 fp16) or its 6-bit digits, on columns padded to the
                     # 32-wide MFMA tile
                     padded = -(-w.batch // 32) * 32
                     s["input_terms"] = terms
                     s["mfma_TFLOPs"] = 2.0 * terms * w.q * w.m * w.n * padded / t.median / 1e12
-                    s["mfma_frac"] = s["mfma_TFLOPs"] / MFMA_F16_PEAK_TFLOPS
+                    s["mfma_frac"] = s["mfma_TFLOPs"] / (MFMA_F4_PEAK_TFLOPS if digits else MFMA_F16_PEAK_TFLOPS)
                     if terms == 2 and x_values == "fp32":
                         kname = "unpack_mfma, 2 input terms"
                     elif x_values != "fp32":
