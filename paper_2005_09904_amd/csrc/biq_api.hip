@@ -664,7 +664,12 @@ bool gather_tables(const biq_plan& pl, int m, int q, int batch, int C) {
     if (pl.kernel != KERNEL_GEMV8 && pl.kernel != KERNEL_GEMV8H && pl.kernel != KERNEL_GEMM8X2 &&
         pl.kernel != KERNEL_GEMM8X2H)
         return false;
-    if (pl.row_mode == 0 || (long long)C * batch > (1ll << 20)) return false;   // at most 1 GiB of tables: 32-bit offsets
+    // 32-bit offsets: at most 1 GiB of tables, and less than 4 GiB up to the end of the last tile, since lanes
+    // address whole tiles and a chunk past the row counts as 0 only while its offset does not wrap (one chunk,
+    // 131072 vectors: chunk 32 would be chunk 0 again); slices of 4 vectors are the grid's z, at most 65535
+    const long long tile_end = (long long)ceil_div(C, pl.chunks_per_tile) * pl.chunks_per_tile;
+    if (pl.row_mode == 0 || (long long)C * batch > (1ll << 20) || tile_end * batch >= (1ll << 22)) return false;
+    if (ceil_div(batch, 4) > 65535) return false;
     return (long long)m * q * C * ceil_div(batch, 4) <= kGatherLookups * pl.tiles_per_split;
 }
 

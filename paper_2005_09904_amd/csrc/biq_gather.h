@@ -15,7 +15,8 @@ namespace biq {
 
 typedef uint32_t gather_u32x4 __attribute__((ext_vector_type(4)));
 // The tables as a buffer: reads past their end, that is of chunks past the last one, return 0, and no
-// condition keeps the reads of a lane from being in flight together.
+// condition keeps the reads of a lane from being in flight together.  (The host admits only calls in which the
+// offsets of a whole last tile stay below 2^32.)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t gather_tables_of(const QueryParams& p) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.LUT), 0, p.C * 1024 * p.batch, 0x00020000);
 }
