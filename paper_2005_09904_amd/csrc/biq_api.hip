@@ -139,6 +139,7 @@ int direct_max_vectors(int n) {
 }
 bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
     if (q > 4 || biq_key_row_stride(n) > (1u << 26)) return false;
+    if (m > (1 << 30)) return false;                 // rows past the end of the last workgroup's steps stay in 32 bits
     const long long chunks = ceil_div(n, 512);
     const int vmax = direct_max_vectors(n);
     if (vmax == 0) return false;

@@ -159,7 +159,7 @@ __global__ __launch_bounds__(kDirectThreads, 1) void direct_kernel(const DirectP
 #pragma unroll
             for (int i = 0; i < Q; ++i) {
                 __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
-                    const_cast<float*>(p.alpha + ((size_t)i * p.m + row0)), 0, (p.m - row0) * 4, 0x00020000);
+                    const_cast<float*>(p.alpha + ((size_t)i * p.m + row0)), 0, min(p.m - row0, 16) * 4, 0x00020000);
                 const mfma_u32x4 v =
                     __builtin_bit_cast(mfma_u32x4, __builtin_amdgcn_raw_buffer_load_b128(src, 16 * kg, 0, 0));
 #pragma unroll

@@ -70,3 +70,16 @@ def test_direct_plans(biq):
     p.table_fill = 2
     with pytest.raises(biq.BiqError):
         biq.biq_plan_check(300, 42000, 1, 1, 8, p)
+
+
+def test_direct_row_limit(biq):
+    """The direct kernel counts rows in 32 bits, those its last row steps have past the end included."""
+    for m, ok in ((1 << 30, True), ((1 << 30) + 1, False), (3 << 29, False)):
+        p = biq.biq_plan_get_lut(m, 100, 1, 3, 8)
+        assert biq.biq_plan_get(m, 100, 1, 3, 8).table_fill in ((0, 2) if ok else (0,))
+        p.table_fill = 2
+        if ok:
+            assert biq.biq_plan_check(m, 100, 1, 3, 8, p).table_fill == 2
+        else:
+            with pytest.raises(biq.BiqError):
+                biq.biq_plan_check(m, 100, 1, 3, 8, p)

@@ -97,3 +97,37 @@ def test_direct_special_values(biq, oracle):
     X[0, 7], X[5, 1199] = np.nan, -np.inf
     Z = _direct(biq, B, alpha, X)
     assert np.isnan(Z[[0, 5]]).all() and np.array_equal(Z[[1, 2, 3, 4, 6]], Y[[1, 2, 3, 4, 6]])
+
+
+def test_direct_most_rows(biq):
+    """2^30 rows, the most the kernel takes: 4 GiB of scales.  Rows at both ends and where byte offsets of scales and keys
+    pass 2^31 and 2^32, against a product in 64 bits."""
+    import torch
+
+    m, n, b = 1 << 30, 20, 2
+    need = 16 * m + 4 * m + 4 * m * b
+    if torch.cuda.mem_get_info()[0] < need + (4 << 30):
+        pytest.skip("needs %d GiB of device memory" % (need >> 30))
+    print("direct", m, n, b, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(30)
+    K = torch.zeros((m, 16), dtype=torch.uint8, device="cuda")
+    K[:, :3] = torch.randint(0, 256, (m, 3), dtype=torch.uint8, device="cuda", generator=g)
+    K[:, 2] &= 15
+    alpha = torch.rand((1, m), device="cuda", generator=g) + 0.5
+    X = torch.randn((b, n), device="cuda", generator=g)
+    Y = torch.full((b, m), float("nan"), device="cuda")
+    plan = biq.biq_plan_get_lut(m, n, 1, b, 8)
+    plan.table_fill = 2
+    plan = biq.biq_plan_check(m, n, 1, b, 8, plan)
+    ws = torch.empty(max(biq.biq_plan_workspace_bytes(plan, m, b), 16), dtype=torch.uint8, device="cuda")
+    biq.biq_gemm_ex(K, alpha, X, Y, m, n, 1, b, 8, plan, workspace=ws)
+    torch.cuda.synchronize()
+    assert not bool(torch.isnan(Y).any())
+    bits = torch.arange(8, dtype=torch.uint8, device="cuda")
+    for first in (0, (1 << 27) - 500, (1 << 28) - 500, (1 << 29) - 500, m - 1000):
+        rows = slice(first, first + 1000)
+        s = ((K[rows, :3, None] >> bits) & 1).reshape(1000, 24)[:, :n].double() * 2 - 1
+        ref = (X.double() @ s.t()) * alpha[:, rows].double()
+        bound = _bound(np.ones((1, 1)), X.cpu().numpy())                       # per vector, for a scale of 1
+        assert bool(((Y[:, rows].double() - ref).abs() <= torch.tensor(bound, device="cuda")[:, None] * alpha[:, rows]).all())
