@@ -46,6 +46,11 @@ inline int unit_keys(int mu) {
 
 inline int ceil_div(int a, int b) { return (int)(((long long)a + b - 1) / b); }
 inline long long ceil_div_ll(long long a, long long b) { return (a + b - 1) / b; }
+// a * b * c of counts up to 2^31 each, 2^61 where it is more (comparisons and quotients stay meaningful)
+inline long long product(long long a, long long b, long long c) {
+    const __int128 p = (__int128)a * b * c;
+    return p < ((__int128)1 << 61) ? (long long)p : 1ll << 61;
+}
 // rows per workgroup from a 64-bit estimate: rounded up to a multiple of `step`, at least `lo`, and
 // never beyond what the 32-bit plan field holds (more rows than m are pointless anyway)
 inline int rows_from(long long want, int step, int lo, int m) {
@@ -88,18 +93,18 @@ bool plan_finish_unpack(biq_plan& pl, int m, int n, int q, int batch) {
         if (ceil_div(pl.tiles_per_split, ws) > 64 || biq_key_row_stride(n) > (1u << 26)) return false;
     }
     pl.chunk_splits = (groups + pl.tiles_per_split - 1) / pl.tiles_per_split;
-    pl.row_blocks = (m + pl.rows_per_wg - 1) / pl.rows_per_wg;
-    pl.batch_tiles = (batch + pl.batch_tile - 1) / pl.batch_tile;
+    pl.row_blocks = ceil_div(m, pl.rows_per_wg);
+    pl.batch_tiles = ceil_div(batch, pl.batch_tile);
     pl.lds_bytes = ws == 1 ? 24 * 1024 : 96 * 1024;   // partial sums of the wave groups, transpose patches (UnpackGeom::LDS_BYTES)
     if (digits) {                                     // DigitGeom::LDS_BYTES
         const int nout = r * (pl.batch_tile / 32);
         pl.lds_bytes = ((4 / ws) * nout * (ws - 1) * 1024 + 4 * 32 * 36 + 4 * 256) * 4;
     }
-    const long long tasks = (long long)pl.row_blocks * pl.chunk_splits * pl.batch_tiles;
+    const long long tasks = product(pl.row_blocks, pl.chunk_splits, pl.batch_tiles);
     if (tasks > (1ll << 30)) return false;
     // prepared input: 2 bytes per term and (padded column, padded element)
-    const long long xf = (long long)pl.batch_tiles * pl.chunk_splits * pl.tiles_per_split *
-                         unpack_group_pieces(pl.batch_tile, pl.input_terms) * 16;
+    const long long xf = product(pl.batch_tiles, (long long)pl.chunk_splits * pl.tiles_per_split,
+                                 unpack_group_pieces(pl.batch_tile, pl.input_terms) * 16);
     if (xf > (1ll << 40)) return false;
     return true;
 }
@@ -252,7 +257,7 @@ bool plan_finish(biq_plan& pl, int m, int n, int q, int batch, int mu) {
     pl.batch_tiles = ceil_div(batch, pl.batch_tile);
     pl.lds_bytes = plan_lds_bytes(pl, mu);
     if (pl.lds_bytes > kLdsPerCu) return false;
-    const long long tasks = (long long)pl.row_blocks * pl.chunk_splits * pl.batch_tiles;
+    const long long tasks = product(pl.row_blocks, pl.chunk_splits, pl.batch_tiles);
     if (tasks > (1ll << 30)) return false;
     return true;
 }
@@ -458,7 +463,7 @@ bool plan_tables(biq_plan& pl, int m, int n, int q, int batch, int mu) {
         return plan_finish(pl, m, n, q, batch, mu);
     }
     if (mu == 8 && batch >= 2 && q <= 4 && C > kGemmTileChunks &&
-        (long long)m * ceil_div(C, kGemmHalfTileChunks) * ceil_div(batch, 2) <= 512ll * kNumCu) {
+        product(m, ceil_div(C, kGemmHalfTileChunks), ceil_div(batch, 2)) <= 512ll * kNumCu) {
         // Small batched calls wider than one full-table tile: half tables (128 chunks x 2 input
         // vectors per workgroup) halve the number of row splits; up to n = 1024 there is none and
         // no second kernel.  One workgroup per CU if the rows allow it, at least 8 rows each;
@@ -484,8 +489,7 @@ bool plan_tables(biq_plan& pl, int m, int n, int q, int batch, int mu) {
         pl.batch_tile = kGemmBT;
         const int tiles = ceil_div(C, kGemmTileChunks);
         const int T = ceil_div(batch, kGemmBT);
-        int rows = ceil_div(m, 64) * 64;
-        if (rows > 4096) rows = 4096;
+        int rows = m > 4096 ? 4096 : ceil_div(m, 64) * 64;
         const long long RT = (long long)ceil_div(m, rows) * T;
         int S = 1;
         if (RT < kNumCu) {
@@ -506,7 +510,7 @@ bool plan_tables(biq_plan& pl, int m, int n, int q, int batch, int mu) {
         pl.rows_per_wg = rows;
         return plan_finish(pl, m, n, q, batch, mu);
     }
-    if ((mu <= 5 || (mu == 6 && batch <= 4)) && 2 * C >= 32 * UK) {
+    if ((mu <= 5 || (mu == 6 && batch <= 4)) && C >= 16 * UK) {
         // Narrow keys, rows at least half a tile wide: 32 lanes per row, conflict-free gathers.
         // (mu = 6 holds one input vector per pass only and re-reads the keys per vector: measured
         // faster than the generic kernel up to 4 input vectors, slower from 16 on.)
@@ -518,7 +522,7 @@ bool plan_tables(biq_plan& pl, int m, int n, int q, int batch, int mu) {
         pl.chunks_per_tile = 32 * UK;
         pl.batch_tile = (128 * 1024) / (32 * UK * E * 4);
         pl.tiles_per_split = 1;
-        const long long units = (long long)m * ceil_div(C, pl.chunks_per_tile) * ceil_div(batch, pl.batch_tile);
+        const long long units = product(m, ceil_div(C, pl.chunks_per_tile), ceil_div(batch, pl.batch_tile));
         const int rows = rows_from(ceil_div_ll(units, kNumCu), 32, 32, m);
         pl.rows_per_wg = rows > (1 << 20) ? (1 << 20) : rows;
         return plan_finish(pl, m, n, q, batch, mu);
@@ -547,9 +551,9 @@ bool plan_generic(biq_plan& pl, int m, int n, int q, int batch, int mu) {
     const int groups = pl.threads / G;
     const int batch_tiles = ceil_div(batch, pl.batch_tile);
     // chunk splits
-    const long long algo_bytes = (long long)q * m * ((n + 7) / 8) + 4ll * q * m + 4ll * n * batch +
-                                 4ll * m * batch;
-    long long max_splits = (2 * algo_bytes) / (4ll * m * batch);
+    const __int128 result_bytes = (__int128)4 * m * batch;
+    const __int128 algo_bytes = (__int128)q * m * ceil_div(n, 8) + 4ll * q * m + (__int128)4 * n * batch + result_bytes;
+    long long max_splits = (long long)((2 * algo_bytes) / result_bytes);
     if (max_splits < 1) max_splits = 1;
     int splits = tiles < max_splits ? tiles : (int)max_splits;
     pl.tiles_per_split = ceil_div(tiles, splits);
@@ -559,7 +563,7 @@ bool plan_generic(biq_plan& pl, int m, int n, int q, int batch, int mu) {
     // CU was up to 2.7x slower on small-batch calls) while each keeps >= 1 row iteration
     const long long row_iters = ceil_div(m, groups);
     const long long want_wgs = 2ll * kNumCu;
-    long long k = (row_iters * splits * batch_tiles) / want_wgs;
+    long long k = product(row_iters, splits, batch_tiles) / want_wgs;
     if (k < 1) k = 1;
     if (k > 64) k = 64;
     if (pl.tiles_per_split > 1) {
@@ -956,7 +960,7 @@ const char* biq_status_str(biq_status status) {
 
 int biq_version(void) { return 100; }
 
-size_t biq_key_row_stride(int n) { return n < 1 ? 0 : (size_t)((n + 127) / 128) * 16; }
+size_t biq_key_row_stride(int n) { return n < 1 ? 0 : ((size_t)n + 127) / 128 * 16; }
 
 size_t biq_packed_bytes(int m, int n, int q) {
     if (m < 1 || n < 1 || q < 1) return 0;
@@ -965,7 +969,7 @@ size_t biq_packed_bytes(int m, int n, int q) {
 
 size_t biq_num_chunks(int n, int mu) {
     if (n < 1 || mu < 1 || mu > kMaxMu) return 0;
-    return (size_t)((n + mu - 1) / mu);
+    return ((size_t)n + mu - 1) / mu;
 }
 
 size_t biq_lut_bytes(int n, int batch, int mu) {
