@@ -13,7 +13,7 @@
 // |error| <= 2^-24 of the block's largest magnitude - half a unit in the last place of that element,
 // what adding the element to any fp32 sum that already holds the largest one would round off - and
 // none for elements whose lowest set bit lies above that (the largest itself, integers, a one-hot
-// vector).  The digits' scales are the instruction's scale operand.
+// vector).  The digits' scales are the instruction's scale operands.
 // Two accumulators per tile, the first digits' and the others': a first digit is an integer below 2^5
 // times its block's scale, so its sum is exact unless the blocks' scales differ widely, and
 // the others' sum is 2^-5 of it, so its fp32 roundings weigh as little.  (One accumulator for all
@@ -24,8 +24,11 @@
 // Time, same order (us per call): 82 -> 47; 86 -> 51; 17 -> 14.3.  Bound by the power the matrix
 // cores may draw: the instruction issues at 33 clk, but in a loop of nothing else the clock falls to
 // 1.3-1.5 GHz, 5.1-5.8 PFLOP/s (bf16: 1.3-1.7 PFLOP/s), so fewer and cheaper instructions are what helps.
-// A block's exponent is clamped at 2^-101 (what is smaller is rounded to 2^-124); a block that
-// holds Inf or NaN gets the scale NaN, and the vector's results are NaN.
+// The whole range of fp32 is covered: a block's scale byte stands for its exponent alone, and what the
+// digits add to it - 2^-5j, which the byte could not hold for blocks below 2^-101 - is the scale of the
+// WEIGHT operand, one constant per digit.  The first digits are summed at half their size: an element next
+// to the largest fp32 rounds up to 2^128.  (The instruction keeps subnormal products and sums.)  A
+// block that holds Inf or NaN gets the scale NaN, and the vector's results are NaN.
 //
 // Inputs that hold bf16 values (all elements of a key group - 256 - of all vectors of a column
 // group) keep the one-term bf16 form: 16 elements per instruction, but one term instead of six.
@@ -76,14 +79,14 @@ struct DigitParams {
 };
 
 // A block of 32 elements -> digits, handed to emit(d, 32 six-bit values in operand order) one after the
-// other; returns the block's scale byte (digit d's is 5 d less), 255 (NaN) for a block with Inf or NaN.
+// other; returns the block's scale byte (digit d counts 2^-5d of it), 255 (NaN) for a block with Inf or NaN.
 template <int UNROLL, typename Emit>
 __device__ __forceinline__ uint32_t digit_split(const float (&x)[32], Emit&& emit) {
     uint32_t mb = 0;
 #pragma unroll
     for (int i = 0; i < 32; ++i) mb = max(mb, __float_as_uint(x[i]) & 0x7fffffffu);
     const bool finite = mb < 0x7f800000u;
-    const int ex = max((int)(mb >> 23), 26);         // 26: the last digit's scale byte stays above 0
+    const int ex = max((int)(mb >> 23), 1);          // (subnormal elements: exponent as 1)
     const float norm = __uint_as_float((uint32_t)max(255 - ex, 1) << 23);   // 2^(128 - ex)
     f32x16 lo, hi;                                   // the 32 elements in operand order, even and odd positions
 #pragma unroll
@@ -209,15 +212,20 @@ __device__ __forceinline__ mfma_u32x4 unpack_nibbles(uint32_t w, uint32_t one8) 
     return d;
 }
 
-// 64 k of one row tile x one column tile: E2M1 weights x E2M3 digit J (scale byte J & 3 of `scale`).
-template <int J>
-__device__ __forceinline__ f32x16 digit_mfma(const mfma_u32x4& a, const mfma_u32x6& b, f32x16 c, uint32_t scale) {
+// Scale bytes of the weights for the digits 0-3 and for digit 4 (see the top of the file).
+constexpr uint32_t kDigitWeightScales = 126u | (127u - 5u) << 8 | (127u - 10u) << 16 | (127u - 15u) << 24;
+constexpr uint32_t kDigitWeightScale4 = 127u - 20u;
+
+// 64 k of one row tile x one column tile: E2M1 weights (scale byte A of `wscale`) x one E2M3 digit (byte B of `scale`).
+template <int A, int B>
+__device__ __forceinline__ f32x16 digit_mfma(const mfma_u32x4& a, const mfma_u32x6& b, f32x16 c, uint32_t wscale,
+                                             uint32_t scale) {
     mfma_i32x8 av = {}, bv = {};
 #pragma unroll
     for (int i = 0; i < 4; ++i) av[i] = (int)a[i];
 #pragma unroll
     for (int i = 0; i < 6; ++i) bv[i] = (int)b[i];
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 4, 2, 0, 127, J & 3, (int)scale);
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 4, 2, A, (int)wscale, B, (int)scale);
 }
 
 // Workgroup = 4 waves; WS of them share a row block along the contraction (each its own part of the
@@ -277,7 +285,7 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
             }
     };
 
-    // first digits, other digits: see the top of the file (bf16 terms: even and odd steps)
+    // first digits at half their size, other digits: see the top of the file (bf16 terms: even and odd steps)
     f32x16 acc[RT][CT], acl[RT][CT];
 #pragma unroll
     for (int t = 0; t < RT; ++t)
@@ -307,8 +315,8 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
     // next step's A operands replace a tile's during the last digit.  The fences
     // keep this order: left alone, the compiler clumps the expansions and drains the loads.
     auto walk_digits = [&](unsigned long long todo) {
-        uint32_t one8 = 0x22222222u;
-        asm volatile("" : "+v"(one8));
+        uint32_t one8 = 0x22222222u, wsc = kDigitWeightScales, wsc4 = kDigitWeightScale4;
+        asm volatile("" : "+v"(one8), "+v"(wsc), "+v"(wsc4));
         mfma_u32x6 b[kDigits][CT];
         uint32_t sc[CT], scn[CT];
         auto area = [&](int g, int c) { return xw + (size_t)(g * CT + c) * kDigitGroupBytes; };
@@ -343,15 +351,8 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
             load_keys(gn, keyn);
             load_scales(gn, scn);
             __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                uint32_t sa[CT], sb[CT];              // scale bytes of digits 0-3 and of digit 4
-#pragma unroll
-                for (int c = 0; c < CT; ++c) {
-                    const uint32_t rep = __builtin_amdgcn_perm(sc[c], sc[c], 0x01010101u * (uint32_t)s);
-                    sa[c] = rep - 0x0f0a0500u;
-                    sb[c] = rep - 0x00000014u;
-                }
+            auto step = [&](auto st) {
+                constexpr int S = decltype(st)::value;
                 auto digit = [&](auto dc) {
                     constexpr int D = decltype(dc)::value;
 #pragma unroll
@@ -359,12 +360,12 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
 #pragma unroll
                         for (int c = 0; c < CT; ++c) {
                             f32x16& sum = D == 0 ? acc[t][c] : acl[t][c];
-                            sum = digit_mfma<D>(a[t], b[D][c], sum, D < 4 ? sa[c] : sb[c]);
+                            sum = digit_mfma<D & 3, S>(a[t], b[D][c], sum, D < 4 ? wsc : wsc4, sc[c]);
                         }
-                        if constexpr (D == kDigits - 1) a[t] = unpack_nibbles(s < 3 ? key[t][(s + 1) & 3] : keyn[t][0], one8);
+                        if constexpr (D == kDigits - 1) a[t] = unpack_nibbles(S < 3 ? key[t][(S + 1) & 3] : keyn[t][0], one8);
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                    load_digit(s < 3 ? g : gn, (s + 1) & 3, D);
+                    load_digit(S < 3 ? g : gn, (S + 1) & 3, D);
                     __builtin_amdgcn_sched_barrier(0);
                 };
                 digit(std::integral_constant<int, 0>{});
@@ -372,7 +373,11 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
                 digit(std::integral_constant<int, 2>{});
                 digit(std::integral_constant<int, 3>{});
                 digit(std::integral_constant<int, 4>{});
-            }
+            };
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+            step(std::integral_constant<int, 2>{});
+            step(std::integral_constant<int, 3>{});
 #pragma unroll
             for (int t = 0; t < RT; ++t) key[t] = keyn[t];
 #pragma unroll
@@ -384,8 +389,8 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
     // ---- bf16 values (key groups as above): one term, 16 steps of 16 elements per key group, fragments seven steps ahead in
     // a ring of eight (see biq_unpack_mfma.h).
     auto walk_bf16 = [&](unsigned long long todo) {
-        uint32_t one2 = 0x3f803f80u;
-        asm volatile("" : "+v"(one2));
+        uint32_t one2 = 0x3f803f80u, half2 = 0x3f003f00u;    // odd steps; even steps, whose sums count twice
+        asm volatile("" : "+v"(one2), "+v"(half2));
         constexpr int R = 8;
         bf16x8 ring[R][CT];
         bf16x8 a[RT];
@@ -397,8 +402,8 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
         auto expand = [&](const mfma_u32x4& k, int st) {
             const uint32_t w = k[(st >> 2) & 3];
             const int ks = st & 3;
-            return ks == 0 ? unpack_step<0, bf16x8>(w, one2) : ks == 1 ? unpack_step<1, bf16x8>(w, one2)
-                 : ks == 2 ? unpack_step<2, bf16x8>(w, one2) : unpack_step<3, bf16x8>(w, one2);
+            return ks == 0 ? unpack_step<0, bf16x8>(w, half2) : ks == 1 ? unpack_step<1, bf16x8>(w, one2)
+                 : ks == 2 ? unpack_step<2, bf16x8>(w, half2) : unpack_step<3, bf16x8>(w, one2);
         };
         int g = ga + __builtin_ctzll(todo);
         load_keys(g, key);
@@ -463,7 +468,7 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
 #pragma unroll
                 for (int i = 0; i < Q; ++i) {
                     const int t = i * RPW + rp;
-                    v = fmaf(scales[t * 32 + 8 * (j >> 2) + 4 * h + (j & 3)], acc[t][c][j] + acl[t][c][j], v);
+                    v = fmaf(scales[t * 32 + 8 * (j >> 2) + 4 * h + (j & 3)], fmaf(2.0f, acc[t][c][j], acl[t][c][j]), v);
                 }
                 acc[rp][c][j] = v;                    // plane 0's accumulator takes the sum
             }

@@ -13,6 +13,10 @@
 // block's scale, so a column's sum is exact unless the magnitudes of its blocks differ by more
 // than about 2^12; the five sums of a vector meet at the very end, smallest first.  Error against fp64:
 // the input rounding (2^-24 of the largest of 32 elements) and a handful of fp32 roundings.
+// All digits of a block share its scale byte, which covers every fp32 exponent; a column's own 2^-5j is
+// put on its finished sums.  The later digits' sums, 2^5j too large until then, are kept from
+// overflowing by weights of +-2^-6: a digit is at most 4, twice the block's largest element at
+// most, so 32 of them are at most 2^6 times that one.  (Inputs below 2^-120: sums rounded to 2^-143.)
 //
 // Bounds.  Matrix pipe: 16 clk per 16 rows x 128 columns x 3 vectors; VALU: 8 instructions per key
 // dword, 32 clk for the 64 lanes' 256 bytes of keys on each of 1024 SIMDs = 17 TB/s of keys, above what
@@ -71,6 +75,8 @@ inline long long direct_lds_bytes(long long chunks, int vecs, int rpw, bool exch
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // 128-bit access, any float address
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
+constexpr int kDirectWeightShift = 6;                // the weights are +-2^-6 (see the top of the file)
+
 // 16 rows x 128 elements x 16 columns; scale byte S of `scale`.
 template <int S>
 __device__ __forceinline__ f32x4v direct_mfma(const mfma_u32x4& a, const mfma_u32x6& b, f32x4v c, uint32_t scale) {
@@ -79,7 +85,7 @@ __device__ __forceinline__ f32x4v direct_mfma(const mfma_u32x4& a, const mfma_u3
     for (int i = 0; i < 4; ++i) av[i] = (int)a[i];
 #pragma unroll
     for (int i = 0; i < 6; ++i) bv[i] = (int)b[i];
-    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(av, bv, c, 4, 2, 0, 127, S, (int)scale);
+    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(av, bv, c, 4, 2, 0, 127 - kDirectWeightShift, S, (int)scale);
 }
 
 // Lanes 32-63 of a <-> lanes 0-31 of b; odd rows of 16 lanes of a <-> even rows of b.
@@ -237,7 +243,7 @@ __global__ __launch_bounds__(kDirectThreads, 1) void direct_kernel(const DirectP
     // this lane's column of column tile nt: digit r % 5 of vector 3 nt + r / 5 (columns without a vector
     // repeat vector 0; their sums are not used)
     uint32_t col_off[NT], sc_off[NT];
-    const uint32_t sc_sub = (uint32_t)(r % 5) * 0x05050505u;
+    const float digit_scale = __uint_as_float((uint32_t)(127 + kDirectWeightShift - 5 * (r % 5)) << 23);
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         const int v = r < 15 && 3 * nt + r / 5 < nv ? 3 * nt + r / 5 : 0;
@@ -272,7 +278,7 @@ __global__ __launch_bounds__(kDirectThreads, 1) void direct_kernel(const DirectP
                 uint32_t sc[NT];
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
-                    sc[nt] = *reinterpret_cast<const uint32_t*>(scales + sc_off[nt] + blk0) - sc_sub;
+                    sc[nt] = *reinterpret_cast<const uint32_t*>(scales + sc_off[nt] + blk0);
                 const uint8_t* dig = digits + blk0 * (kDigits * 24);
                 auto load_b = [&](int st, mfma_u32x6 (&b)[NT]) {
 #pragma unroll
@@ -328,8 +334,28 @@ __global__ __launch_bounds__(kDirectThreads, 1) void direct_kernel(const DirectP
                     float s = 0.0f;
 #pragma unroll
                     for (int i = 0; i < Q; ++i) s = fmaf(-al[i * RPW + rp][e], acc[i * RPW + rp][nt][e], s);
-                    y[rp][nt][e] = (((dpp_shl<4>(s) + dpp_shl<3>(s)) + dpp_shl<2>(s)) + dpp_shl<1>(s)) + s;
+                    y[rp][nt][e] = s * digit_scale;
                 }
+        // (digit by digit over all sums: an exchange has to wait for an operand just written)
+        float part[RPW][NT][4];
+        auto gather_digit = [&](auto tap) {
+            constexpr int N = decltype(tap)::value;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int rp = 0; rp < RPW; ++rp)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float d = N > 0 ? dpp_shl<N>(y[rp][nt][e]) : y[rp][nt][e];
+                        part[rp][nt][e] = N == kDigits - 1 ? d : part[rp][nt][e] + d;
+                    }
+        };
+        gather_digit(std::integral_constant<int, 4>{});
+        gather_digit(std::integral_constant<int, 3>{});
+        gather_digit(std::integral_constant<int, 2>{});
+        gather_digit(std::integral_constant<int, 1>{});
+        gather_digit(std::integral_constant<int, 0>{});
         const bool holder = r == 0 || r == 5 || r == 10;
         if (ksplit == 1) {
 #pragma unroll
@@ -342,12 +368,12 @@ __global__ __launch_bounds__(kDirectThreads, 1) void direct_kernel(const DirectP
                         float* dst = p.out + (size_t)(v0 + v) * p.m + row;
                         if (row + 3 < p.m) {
                             f32x4_a4 t;
-                            t.x = y[rp][nt][0]; t.y = y[rp][nt][1]; t.z = y[rp][nt][2]; t.w = y[rp][nt][3];
+                            t.x = part[rp][nt][0]; t.y = part[rp][nt][1]; t.z = part[rp][nt][2]; t.w = part[rp][nt][3];
                             *reinterpret_cast<f32x4_a4*>(dst) = t;
                         } else {
 #pragma unroll
                             for (int e = 0; e < 3; ++e)
-                                if (row + e < p.m) dst[e] = y[rp][nt][e];
+                                if (row + e < p.m) dst[e] = part[rp][nt][e];
                         }
                     }
                 }
@@ -361,7 +387,7 @@ __global__ __launch_bounds__(kDirectThreads, 1) void direct_kernel(const DirectP
                 for (int nt = 0; nt < NT; ++nt) {
                     float* dst = buf + ((wave * NT + nt) * 3 + r / 5) * 16 + 4 * kg;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) dst[e] = y[0][nt][e];
+                    for (int e = 0; e < 4; ++e) dst[e] = part[0][nt][e];
                 }
             }
             __syncthreads();

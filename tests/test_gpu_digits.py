@@ -109,3 +109,42 @@ def test_digits_hold_what_they_promise(biq, oracle):
     Bd, ad, Xd = device_inputs(Bh, np.ones((1, 64), dtype=np.float32), Xh)
     Y = gpu_gemm(biq, gpu_pack(biq, Bd), ad, Xd, 64, 256, 1, 8, plan=_plan(biq, 1, 32, 1, 1, 1)).cpu().numpy()
     assert np.array_equal(Y, np.repeat(-vals[:, None], 64, axis=1))
+
+
+@pytest.mark.parametrize("exponent", [-105, -110, -120, -126, -135])
+def test_digits_small_inputs(biq, oracle, exponent):
+    """Vectors far below one keep their bits: the bound relative to the elements, and what sums that are subnormal
+    themselves are rounded to (half an instruction's last place, 2^-148, for each of a row's instructions)."""
+    rng = np.random.default_rng(900 - exponent)
+    m, n, q, b = 100, 1300, 2, 40
+    B = (rng.integers(0, 2, size=(q, m, n), dtype=np.int8) * 2 - 1).astype(np.int8)
+    alpha = rng.uniform(0.05, 1.0, size=(q, m)).astype(np.float32)
+    X = rng.standard_normal((b, n))
+    X[::3] *= 2.0 ** exponent
+    X[1::3] *= 2.0 ** exponent * 10.0 ** rng.uniform(-3, 3, size=n)
+    X[2] *= 2.0 ** 100                                  # large vectors among them change nothing
+    X = X.astype(np.float32)
+    Bd, ad, Xd = device_inputs(B, alpha, X)
+    Y = gpu_gemm(biq, gpu_pack(biq, Bd), ad, Xd, m, n, q, 8, plan=_plan(biq, q, 32, 6, 2, 2)).cpu().numpy()
+    least = np.abs(alpha).sum(axis=0).max() * 5 * -(-n // 64) * 2.0 ** -148 + 2.0 ** -149
+    assert np.all(np.abs(Y - oracle.gemm_dense(B, alpha, X)).max(axis=1) <= _bound(alpha, X) + least)
+
+
+def test_digits_largest_inputs(biq, oracle):
+    """The largest fp32 alone in a vector comes back as it is, in either form; sums below it do not overflow."""
+    top = np.finfo(np.float32).max
+    bf16_top = np.float32(2.0 ** 127 * (2 - 2.0 ** -7))
+    m, n = 64, 300
+    B = np.ones((1, m, n), dtype=np.int8)
+    B[0, ::2] = -1
+    alpha = np.full((1, m), 0.5, dtype=np.float32)
+    X = np.zeros((34, n), dtype=np.float32)
+    X[0, 5], X[1, 299], X[2, 17] = top, -top, top * np.float32(0.99)
+    X[3] = top / np.float32(310.0)
+    X[33, 40], X[33, 290] = bf16_top, -bf16_top / 4      # a column group of its own: 16-bit form
+    Bd, ad, Xd = device_inputs(B, alpha, X)
+    Y = gpu_gemm(biq, gpu_pack(biq, Bd), ad, Xd, m, n, 1, 8, plan=_plan(biq, 1, 32, 2, 1, 1)).cpu().numpy()
+    ref = oracle.gemm_dense(B, alpha, X)
+    assert np.isfinite(Y).all()
+    assert np.array_equal(Y[[0, 1, 2, 33]].astype(np.float64), ref[[0, 1, 2, 33]])
+    assert np.all(np.abs(Y - ref).max(axis=1) <= _bound(alpha, X))

@@ -131,3 +131,41 @@ def test_direct_most_rows(biq):
         ref = (X.double() @ s.t()) * alpha[:, rows].double()
         bound = _bound(np.ones((1, 1)), X.cpu().numpy())                       # per vector, for a scale of 1
         assert bool(((Y[:, rows].double() - ref).abs() <= torch.tensor(bound, device="cuda")[:, None] * alpha[:, rows]).all())
+
+
+@pytest.mark.parametrize("exponent", [-105, -110, -118, -126, -135])
+def test_direct_small_inputs(biq, oracle, exponent):
+    """Vectors far below one keep their bits: the bound relative to the elements, and what the kernel's sums are rounded to
+    where they are subnormal (they are formed at 2^-6 of their size: 2^-143 for each instruction of a row)."""
+    rng = np.random.default_rng(700 - exponent)
+    m, n, q, b = 200, 1200, 2, 7
+    B = (rng.integers(0, 2, size=(q, m, n), dtype=np.int8) * 2 - 1).astype(np.int8)
+    alpha = rng.uniform(0.05, 1.0, size=(q, m)).astype(np.float32)
+    X = rng.standard_normal((b, n))
+    X[::3] *= 2.0 ** exponent
+    X[1::3] *= 2.0 ** exponent * 10.0 ** rng.uniform(-3, 3, size=n)
+    X[2] *= 2.0 ** 100                                  # a large vector among them changes nothing
+    X = X.astype(np.float32)
+    Y = _direct(biq, B, alpha, X)
+    least = np.abs(alpha).sum(axis=0).max() * (-(-n // 128) + 2) * 1.04 * 2.0 ** -143
+    assert np.all(np.abs(Y - oracle.gemm_dense(B, alpha, X)).max(axis=1) <= _bound(alpha, X) + least)
+
+
+def test_direct_largest_inputs(biq, oracle):
+    """The largest fp32 alone in a vector comes back as it is; sums below it do not overflow, nor do the sums of
+    later digits, whatever their signs."""
+    top = np.finfo(np.float32).max
+    m, n = 40, 1500
+    B = np.ones((1, m, n), dtype=np.int8)
+    B[0, ::2] = -1
+    alpha = np.full((1, m), 0.5, dtype=np.float32)
+    X = np.zeros((4, n), dtype=np.float32)
+    X[0, 5], X[1, 1499] = top, -top
+    X[2] = top / np.float32(1550.0)
+    X[3, ::32] = top / np.float32(100.0)
+    X[3, X[3] == 0] = top / np.float32(100.0 * 32.1)     # a digit below the largest of the block
+    Y = _direct(biq, B, alpha, X)
+    ref = oracle.gemm_dense(B, alpha, X)
+    assert np.isfinite(Y).all()
+    assert np.array_equal(Y[:2].astype(np.float64), ref[:2])
+    assert np.all(np.abs(Y - ref).max(axis=1) <= _bound(alpha, X))
