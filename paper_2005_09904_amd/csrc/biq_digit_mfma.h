@@ -294,7 +294,7 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[t][c][v] = acl[t][c][v] = 0.0f;
 
-    // the scales of the wave's RT * 32 key rows, a lane's share held until the epilogue
+    // the scales of the wave's RT * 32 key rows: requested here, in LDS from the form votes on
     constexpr int NA = (RT * 32 + 63) / 64;
     float av[NA];
 #pragma unroll
@@ -438,26 +438,34 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
         } while (todo);
     };
 
+    float* const red = reinterpret_cast<float*>(stage_buf);
+    float* const patch = red + G::RED_FLOATS + wave * (32 * G::TP);
+    float* const scales = red + G::RED_FLOATS + 4 * 32 * G::TP + wave * (RT * 32);   // -alpha of the wave's rows
+    auto store_scales = [&] {
+#pragma unroll
+        for (int j = 0; j < NA; ++j)
+            if (64 * j + lane < RT * 32) scales[64 * j + lane] = -av[j];
+    };
     // the wave's key groups (at most 64) by form: first those in digits, then those in bf16
     if (ga < gb) {
         const int cnt = gb - ga;
         const int f = p.form[(size_t)cg * p.groups + ga + min(lane, cnt - 1)];
         const unsigned long long all = cnt < 64 ? (1ull << cnt) - 1 : ~0ull;
         const unsigned long long bf = __builtin_amdgcn_ballot_w64(f == kFormBf16) & all;
+        store_scales();    // they came before the forms, so nothing waits here (held in registers, they spilled)
         if (bf != all) walk_digits(all & ~bf);
         if (bf) walk_bf16(bf);
+    } else {
+        store_scales();
     }
 
     // ---- epilogue: -alpha scale and plane sum (Eq. 2) on the wave's part of the contraction, then the
     // WS parts are added through LDS - output tile o by wave group o % WS, so that all waves take a
     // share of it - and each tile leaves through a transpose patch in 128-byte runs.
+    // (lane numbers counted anew: kept, they would be spilled over the loops)
+    const int elane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    const int eh = elane >> 5, elr = elane & 31;
     const bool vec_ok = ((p.m & 3) == 0) && ((reinterpret_cast<uintptr_t>(p.out) & 15) == 0);
-    float* const red = reinterpret_cast<float*>(stage_buf);
-    float* const patch = red + G::RED_FLOATS + wave * (32 * G::TP);
-    float* const scales = red + G::RED_FLOATS + 4 * 32 * G::TP + wave * (RT * 32);   // -alpha of the wave's rows
-#pragma unroll
-    for (int j = 0; j < NA; ++j)
-        if (64 * j + lane < RT * 32) scales[64 * j + lane] = -av[j];
 #pragma unroll
     for (int rp = 0; rp < RPW; ++rp)
 #pragma unroll
@@ -468,11 +476,13 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
 #pragma unroll
                 for (int i = 0; i < Q; ++i) {
                     const int t = i * RPW + rp;
-                    v = fmaf(scales[t * 32 + 8 * (j >> 2) + 4 * h + (j & 3)], fmaf(2.0f, acc[t][c][j], acl[t][c][j]), v);
+                    v = fmaf(scales[t * 32 + 8 * (j >> 2) + 4 * eh + (j & 3)], fmaf(2.0f, acc[t][c][j], acl[t][c][j]), v);
                 }
                 acc[rp][c][j] = v;                    // plane 0's accumulator takes the sum
             }
-            __builtin_amdgcn_sched_barrier(0);        // (tile by tile: the registers are full)
+            // tile by tile, scales read and sums finished: the registers are full (left to itself, the compiler reads
+            // all scales first and finishes the sums where they are used)
+            asm volatile("" : "+v"(acc[rp][c]) : : "memory");
         }
     if constexpr (WS > 1) {
 #pragma unroll
@@ -480,7 +490,7 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
             const int owner = o % WS;
             if (kg != owner) {
                 const int slot = ((wrow * NOUT + o) * (WS - 1)) + (kg > owner ? kg - 1 : kg);
-                float4* dst = reinterpret_cast<float4*>(red + (size_t)slot * 1024) + lane;
+                float4* dst = reinterpret_cast<float4*>(red + (size_t)slot * 1024) + elane;
                 const f32x16& v = acc[o / CT][o % CT];
 #pragma unroll
                 for (int vq = 0; vq < 4; ++vq) dst[vq * 64] = make_float4(v[4 * vq], v[4 * vq + 1], v[4 * vq + 2], v[4 * vq + 3]);
@@ -497,7 +507,7 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
 #pragma unroll
             for (int j = 0; j < WS - 1; ++j) {
                 const int slot = ((wrow * NOUT + o) * (WS - 1)) + j;
-                const float4* src = reinterpret_cast<const float4*>(red + (size_t)slot * 1024) + lane;
+                const float4* src = reinterpret_cast<const float4*>(red + (size_t)slot * 1024) + elane;
 #pragma unroll
                 for (int vq = 0; vq < 4; ++vq) {
                     const float4 v = src[vq * 64];
@@ -507,12 +517,12 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
         }
 #pragma unroll
         for (int vq = 0; vq < 4; ++vq)
-            *reinterpret_cast<float4*>(patch + lr * G::TP + 8 * vq + 4 * h) =
+            *reinterpret_cast<float4*>(patch + elr * G::TP + 8 * vq + 4 * eh) =
                 make_float4(y[4 * vq], y[4 * vq + 1], y[4 * vq + 2], y[4 * vq + 3]);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int pc = 8 * i + (lane >> 3);
-            const int pr = 4 * (lane & 7);
+            const int pc = 8 * i + (elane >> 3);
+            const int pr = 4 * (elane & 7);
             const float4 v = *reinterpret_cast<const float4*>(patch + pc * G::TP + pr);
             const int col = (cg * CT + c) * 32 + pc;
             const int row = rbase + rp * 32 + pr;

@@ -280,42 +280,63 @@ __global__ __launch_bounds__(kDirectThreads, 1) void direct_kernel(const DirectP
                 for (int nt = 0; nt < NT; ++nt)
                     sc[nt] = *reinterpret_cast<const uint32_t*>(scales + sc_off[nt] + blk0);
                 const uint8_t* dig = digits + blk0 * (kDigits * 24);
-                auto load_b = [&](int st, mfma_u32x6 (&b)[NT]) {
+                auto load_b = [&](int st, int nt, mfma_u32x6& b) {
+                    const mfma_u32x2* src = reinterpret_cast<const mfma_u32x2*>(dig + st * (kDigits * 24) + col_off[nt]);
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) {
-                        const mfma_u32x2* src = reinterpret_cast<const mfma_u32x2*>(dig + st * (kDigits * 24) + col_off[nt]);
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) {
-                            const mfma_u32x2 t = src[i];
-                            b[nt][2 * i] = t.x;
-                            b[nt][2 * i + 1] = t.y;
-                        }
+                    for (int i = 0; i < 3; ++i) {
+                        const mfma_u32x2 t = src[i];
+                        b[2 * i] = t.x;
+                        b[2 * i + 1] = t.y;
                     }
                 };
                 // the next step's operands are read while this one's instructions issue (a step is as
                 // short as the latency of LDS: 16384 x 4096, 2 planes 6.3 -> 6.1 us; steps in a loop that is
                 // not unrolled: 7.4)
-                constexpr int NB = RT * NT <= 12 ? 2 : 1;     // (what the registers hold)
-                mfma_u32x6 b[NB][NT];
-                load_b(0, b[0]);
+                constexpr bool WHOLE = RT * NT <= 12;         // (what the registers hold)
+                // ... otherwise column tile by column tile, two ahead (a whole step at once, spilled keys: 10-15 vectors,
+                // 4 planes)
+                mfma_u32x6 b[WHOLE ? 2 : 1][WHOLE ? NT : 3];
+                if constexpr (WHOLE) {
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) load_b(0, nt, b[0][nt]);
+                } else {
+                    load_b(0, 0, b[0][0]);
+                    load_b(0, 1, b[0][1]);
+                }
                 auto step = [&](auto sc_t) {
                     constexpr int S = decltype(sc_t)::value;
-                    if constexpr (NB == 2 && S < 3) load_b(S + 1, b[(S + 1) & 1]);
-                    if constexpr (NB == 1 && S > 0) load_b(S, b[0]);
+                    if constexpr (WHOLE && S < 3) {
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) load_b(S + 1, nt, b[(S + 1) & 1][nt]);
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                     mfma_u32x4 a[RT];
 #pragma unroll
                     for (int t = 0; t < RT; ++t) a[t] = unpack_nibbles(k[t][c][S], one8);
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
+                    for (int nt = 0; nt < NT; ++nt) {
+                        const int next = S * NT + nt + 2;
+                        if constexpr (!WHOLE) {
+                            if (next < 4 * NT) load_b(next / NT, next % NT, b[0][next % 3]);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        const mfma_u32x6& bn = WHOLE ? b[S & 1][nt] : b[0][(next + 1) % 3];
 #pragma unroll
-                        for (int t = 0; t < RT; ++t)
-                            acc[t][nt] = direct_mfma<S>(a[t], b[S & (NB - 1)][nt], acc[t][nt], sc[nt]);
+                        for (int t = 0; t < RT; ++t) acc[t][nt] = direct_mfma<S>(a[t], bn, acc[t][nt], sc[nt]);
+                    }
                 };
                 step(std::integral_constant<int, 0>{});
                 step(std::integral_constant<int, 1>{});
                 step(std::integral_constant<int, 2>{});
                 step(std::integral_constant<int, 3>{});
+                if constexpr (!WHOLE) {
+                    // (the sums belong here: the compiler would move them behind the condition below, and with them the
+                    // wait for this unit's operands behind the one for the next keys)
+#pragma unroll
+                    for (int t = 0; t < RT; ++t)
+#pragma unroll
+                        for (int nt = 0; nt < NT; ++nt) asm volatile("" : "+v"(acc[t][nt]));
+                }
             }
             if (more)
 #pragma unroll
@@ -356,14 +377,18 @@ __global__ __launch_bounds__(kDirectThreads, 1) void direct_kernel(const DirectP
         gather_digit(std::integral_constant<int, 2>{});
         gather_digit(std::integral_constant<int, 1>{});
         gather_digit(std::integral_constant<int, 0>{});
-        const bool holder = r == 0 || r == 5 || r == 10;
+        // (where the accumulators leave few registers: lane numbers the compiler cannot compute addresses from
+        // ahead of the loop, which it would spill)
+        int er = r, ekg = kg;
+        if constexpr (RT * NT >= 16 || (RPW == 4 && NT > 1)) asm volatile("" : "+v"(er), "+v"(ekg));
+        const bool holder = er == 0 || er == 5 || er == 10;
         if (ksplit == 1) {
 #pragma unroll
             for (int rp = 0; rp < RPW; ++rp) {
-                const int row = tile_row(rs, rp) + 4 * kg;
+                const int row = tile_row(rs, rp) + 4 * ekg;
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
-                    const int v = 3 * nt + r / 5;
+                    const int v = 3 * nt + er / 5;
                     if (holder && v < nv && row < p.m) {
                         float* dst = p.out + (size_t)(v0 + v) * p.m + row;
                         if (row + 3 < p.m) {
@@ -385,7 +410,7 @@ __global__ __launch_bounds__(kDirectThreads, 1) void direct_kernel(const DirectP
             if (holder) {
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
-                    float* dst = buf + ((wave * NT + nt) * 3 + r / 5) * 16 + 4 * kg;
+                    float* dst = buf + ((wave * NT + nt) * 3 + er / 5) * 16 + 4 * ekg;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) dst[e] = part[0][nt][e];
                 }
