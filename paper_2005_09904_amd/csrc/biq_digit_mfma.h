@@ -121,36 +121,24 @@ __global__ __launch_bounds__(256 * CT) void xdigits_kernel(const float* __restri
                                                            int* __restrict__ form, int n, int batch, int groups) {
     extern __shared__ __align__(16) float xs[];      // [32 * CT][kXdigitsPitch], then the waves' votes
     const int g = (int)blockIdx.x % groups, cg = (int)blockIdx.x / groups;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     {
         // wave w reads vectors 8w .. 8w + 7, all requests in flight together
         const int col0 = cg * CT * 32 + wave * 8;
-        const long long e = 256ll * g + 4 * lane;
-        const bool vec = (n & 3) == 0 && ((reinterpret_cast<uintptr_t>(X) & 15) == 0);
-        float4 v[8];
-        if (vec) {
-            // n is a multiple of 4: a piece is inside the vector or past it
-            const long long ec = e < n ? e : 0;
+        // (a buffer per vector: elements past n, and all of a vector past the batch, read as 0.  Reads behind
+        // conditions were waited for one by one: odd n 5.1 -> 3.5 us)
+        typedef float f32x4b __attribute__((ext_vector_type(4)));
+        f32x4b v[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                v[i] = *reinterpret_cast<const float4*>(X + (size_t)min(col0 + i, batch - 1) * n + ec);
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (e >= n || col0 + i >= batch) v[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float* src = X + (size_t)min(col0 + i, batch - 1) * n;
-                const bool ok = col0 + i < batch;
-                v[i].x = ok && e < n ? src[e] : 0.0f;
-                v[i].y = ok && e + 1 < n ? src[e + 1] : 0.0f;
-                v[i].z = ok && e + 2 < n ? src[e + 2] : 0.0f;
-                v[i].w = ok && e + 3 < n ? src[e + 3] : 0.0f;
-            }
+        for (int i = 0; i < 8; ++i) {
+            const int col = min(col0 + i, batch - 1);
+            const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<float*>(X + (size_t)col * n), 0, col0 + i < batch ? n * 4 : 0, 0x00020000);
+            v[i] = __builtin_bit_cast(f32x4b, __builtin_amdgcn_raw_buffer_load_b128(src, 1024 * g + 16 * lane, 0, 0));
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-            *reinterpret_cast<float4*>(xs + (wave * 8 + i) * kXdigitsPitch + 4 * lane) = v[i];
+            *reinterpret_cast<f32x4b*>(xs + (wave * 8 + i) * kXdigitsPitch + 4 * lane) = v[i];
     }
     __syncthreads();
     const int c = wave >> 2, s = wave & 3;           // column tile, step within the key group
@@ -314,7 +302,7 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
     // (two sets, requested two steps ahead, where up to 4 tiles leave room: no faster on 30 shapes).  The
     // next step's A operands replace a tile's during the last digit.  The fences
     // keep this order: left alone, the compiler clumps the expansions and drains the loads.
-    auto walk_digits = [&](unsigned long long todo) {
+    auto walk_digits = [&](unsigned long long todo, bool have_keys) {
         uint32_t one8 = 0x22222222u, wsc = kDigitWeightScales, wsc4 = kDigitWeightScale4;
         asm volatile("" : "+v"(one8), "+v"(wsc), "+v"(wsc4));
         mfma_u32x6 b[kDigits][CT];
@@ -337,7 +325,7 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
             for (int c = 0; c < CT; ++c) v[c] = *reinterpret_cast<const uint32_t*>(area(g, c) + kDigitScaleOffset + lane * 4);
         };
         int g = ga + __builtin_ctzll(todo);
-        load_keys(g, key);
+        if (!have_keys) load_keys(g, key);
         load_scales(g, sc);
 #pragma unroll
         for (int d = 0; d < kDigits; ++d) load_digit(g, 0, d);
@@ -388,7 +376,7 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
 
     // ---- bf16 values (key groups as above): one term, 16 steps of 16 elements per key group, fragments seven steps ahead in
     // a ring of eight (see biq_unpack_mfma.h).
-    auto walk_bf16 = [&](unsigned long long todo) {
+    auto walk_bf16 = [&](unsigned long long todo, bool have_keys) {
         uint32_t one2 = 0x3f803f80u, half2 = 0x3f003f00u;    // odd steps; even steps, whose sums count twice
         asm volatile("" : "+v"(one2), "+v"(half2));
         constexpr int R = 8;
@@ -406,7 +394,7 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
                  : ks == 2 ? unpack_step<2, bf16x8>(w, half2) : unpack_step<3, bf16x8>(w, one2);
         };
         int g = ga + __builtin_ctzll(todo);
-        load_keys(g, key);
+        if (!have_keys) load_keys(g, key);
 #pragma unroll
         for (int j = 0; j + 1 < R; ++j) load_b(g, j, ring[j]);
 #pragma unroll
@@ -450,11 +438,13 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
     if (ga < gb) {
         const int cnt = gb - ga;
         const int f = p.form[(size_t)cg * p.groups + ga + min(lane, cnt - 1)];
+        load_keys(ga, key);    // the first group's keys do not wait for the forms, which mostly are one form anyway
+        __builtin_amdgcn_sched_barrier(0);
         const unsigned long long all = cnt < 64 ? (1ull << cnt) - 1 : ~0ull;
         const unsigned long long bf = __builtin_amdgcn_ballot_w64(f == kFormBf16) & all;
         store_scales();    // they came before the forms, so nothing waits here (held in registers, they spilled)
-        if (bf != all) walk_digits(all & ~bf);
-        if (bf) walk_bf16(bf);
+        if (bf != all) walk_digits(all & ~bf, !(bf & 1));
+        if (bf) walk_bf16(bf, bf == all);
     } else {
         store_scales();
     }
