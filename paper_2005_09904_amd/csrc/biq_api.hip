@@ -129,7 +129,9 @@ inline int plan_lds_bytes(const biq_plan& pl, int mu) {
 // groups of waves along the row; as many row steps per workgroup as leave at most 256 workgroups.  A row step costs
 // its chunks (matrix pipe, expansion or LDS of the two waves per SIMD, or the latency of the next keys) and an
 // epilogue; keys stream at 3.3 TB/s; the split of the inputs 1.9 us per 512 blocks.  Fitted to 94 random
-// shapes (128 .. 280000 rows, 128 .. 16000 columns, 1 .. 48 vectors): 13 % rms.
+// shapes (128 .. 280000 rows, 128 .. 16000 columns, 1 .. 48 vectors): 13 % rms.  The estimate handed on (not the
+// choice of the mapping) has at least 0.85 us per row step where there are several: a step waits for its scales,
+// and short rows have nothing else to do meanwhile (1025348 x 111, 1 plane, 1 vector: 16 us without, measured 34).
 struct DirectGeom {
     int vecs, batch_tiles, chunks, ksplit, steps, row_blocks, lds;
     int uc;                  // chunks requested together
@@ -155,7 +157,7 @@ bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
     if (g.batch_tiles > 65535) return false;
     const int nt = ceil_div(g.vecs, 3);
     const double mem = (double)q * m * biq_key_row_stride(n) * g.batch_tiles / 3.3e6;
-    g.est = 1e30;
+    double best = 1e30;
     for (int many = 1; many >= 0; --many)
         for (int ks = 1; ks <= (many ? 1 : kDirectWaves) && (ks == 1 || ks <= g.chunks); ks *= 2) {
             const int rpw = many ? direct_rpw(q, nt) : 1, uc = many ? direct_uc(nt) : 1;
@@ -168,13 +170,16 @@ bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
             double clk = 22.0 * rt * (16 * nt > 32 ? 16 * nt : 32);
             if (clk < 860.0 * nt) clk = 860.0 * nt;
             if (clk < 742.0) clk = 742.0;
-            const double work =
-                rounds * steps * (upg * uc * clk / 2200.0 + 0.012 * rt * nt + (ks > 1 ? 0.36 : 0.0));
+            double work = rounds * steps * (upg * uc * clk / 2200.0 + 0.012 * rt * nt + (ks > 1 ? 0.36 : 0.0));
+            const double before = 1.3 + 0.36 * (nt - 1) + 1.94 * rounds * ceil_div(g.chunks * g.vecs, 4 * kDirectWaves);
             // (both together, smoothly: of two mappings that memory bounds, the one with less work)
-            const double t = 1.3 + 0.36 * (nt - 1) + 1.94 * rounds * ceil_div(g.chunks * g.vecs, 4 * kDirectWaves) +
-                             cbrt(work * work * work + mem * mem * mem);
-            if (t < g.est) {
-                g.est = t;
+            const double t = before + cbrt(work * work * work + mem * mem * mem);
+            if (t < best) {
+                best = g.est = t;
+                if (steps > 1 && work < 0.85 * rounds * steps) {
+                    work = 0.85 * rounds * steps;
+                    g.est = before + cbrt(work * work * work + mem * mem * mem);
+                }
                 g.many = many != 0;
                 g.ksplit = ks;
                 g.uc = uc;
@@ -183,7 +188,7 @@ bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
             }
         }
     g.lds = (int)direct_lds_bytes(g.chunks, g.vecs, 1, g.ksplit > 1);
-    return g.est < 1e30;
+    return best < 1e30;
 }
 
 // Completes the derived fields and checks a plan against the shape and device limits.
@@ -263,22 +268,36 @@ bool plan_finish(biq_plan& pl, int m, int n, int q, int batch, int mu) {
 }
 
 // Estimated time (us) of the lookup-table plan `pl`, from rates measured on MI355X: where the tables
-// stop paying off (the crossover of Sec. IV-B / Fig. 10).  The kernels with one workgroup per CU: launch,
-// per round of workgroups over the CUs one table build (2 us; half tables 1.3, narrow keys 3) and 65e3
-// lookups per us and CU, 3 us for a second kernel.  (Estimated / measured: 5003 x 3001, 3 planes, 20
-// vectors 24 / 25.7; 16384 x 4096, 4, 32: 74 / 78; 1500 x 6000, 1, 40: 16 / 18.5; mu = 4: 192 x 7070, 2, 192:
-// 35 / 37; 351 x 3264, 4, 77: 17 / 15.5.)  The generic kernel: 6.5e12 lookups/s, keys at no more than
-// 0.25 TB/s, and 0.4 us per partial result a second kernel adds (320 x 12288, mu = 7, 4, 24: 38 / 33).
+// stop paying off (the crossover of Sec. IV-B / Fig. 10).  The mu = 8 kernels with one workgroup per CU: launch,
+// per round of workgroups over the CUs one table build (2 us; half tables 1.3) and 65e3 lookups per us and CU,
+// 3 us for a second kernel.  (Estimated / measured: 5003 x 3001, 3 planes, 20 vectors 24 / 25.7; 16384 x 4096, 4, 32:
+// 74 / 78; 1500 x 6000, 1, 40: 16 / 18.5.)  Narrow keys, fitted to 407 shapes, 10 % rms: 5.5 us per round and the lookups of
+// a whole tile, twice (mu = 5) and 3.2 times (mu = 6) the time where a pass serves one vector only; a second kernel
+// 3 us and 15 us per million partial results.  The generic kernel: 6.5e12 lookups/s, keys at no more than 0.25 TB/s,
+// and 0.4 us per partial result a second kernel adds (320 x 12288, mu = 7, 4, 24: 38 / 33) - but one vector on rows of
+// up to four key units, the fewer lanes of a row the better: 0.1 to 0.3 ps per lookup of a row's whole units, more
+// where the workgroups are fewer than the CUs (310460 x 192, mu = 4, 1 plane 7.3 / 6.8 us; the general rule says 35.8).
 double tables_estimate(const biq_plan& pl, int m, int n, int q, int batch, int mu) {
     const double wgs = (double)pl.row_blocks * pl.chunk_splits * pl.batch_tiles;
     const double rounds = (double)(long long)((wgs + kNumCu - 1) / kNumCu);
-    const int chunks = ceil_div(n, mu) < pl.chunks_per_tile ? ceil_div(n, mu) : pl.chunks_per_tile;
-    const double second = pl.chunk_splits > 1 ? 3.0 : 0.0;
     const double rows = pl.rows_per_wg < m ? pl.rows_per_wg : m;
     if (pl.kernel == KERNEL_GEMM8X2 || pl.kernel == KERNEL_GEMM8X2H)   // (a short row still takes its lanes' time)
         return 3.4 + rounds * pl.tiles_per_split * ((pl.kernel == KERNEL_GEMM8X2H ? 1.3 : 2.0) +
-                                                    rows * q * pl.chunks_per_tile * 2 / 65e3) + second;
-    if (pl.kernel == KERNEL_WIDE) return 5.0 + rounds * (3.0 + rows * q * chunks * pl.batch_tile / 65e3) + second;
+                                                    rows * q * pl.chunks_per_tile * 2 / 65e3) +
+               (pl.chunk_splits > 1 ? 3.0 : 0.0);
+    if (pl.kernel == KERNEL_WIDE) {
+        const double slower = mu == 6 ? 3.2 : mu == 5 ? 2.0 : 1.0;
+        return rounds * (5.5 + slower * rows * q * pl.chunks_per_tile * pl.batch_tile / 65e3) +
+               (pl.chunk_splits > 1 ? 3.0 + 15e-6 * pl.chunk_splits * (double)m * batch : 0.0);
+    }
+    const int units = pl.chunks_per_tile / unit_keys(mu);
+    if (batch == 1 && units <= 4 && pl.chunk_splits == 1 && mu <= 7) {
+        const double ps = mu <= 4   ? (units == 1 ? 0.107 : units == 2 ? 0.152 : 0.25)
+                          : mu == 5 ? 0.18
+                          : mu == 6 ? (units <= 2 ? 0.23 : 0.27)
+                                    : (units == 1 ? 0.20 : 0.30);
+        return 4.2 + ps * 1e-6 * m * q * pl.chunks_per_tile * (wgs < kNumCu ? kNumCu / wgs : 1.0);
+    }
     const double weights = (double)q * m * n;
     double t = weights / mu * batch / 6.5e6;
     if (t < weights / 8 / 0.25e6) t = weights / 8 / 0.25e6;
@@ -347,10 +366,14 @@ bool plan_unpack(biq_plan& pl, int m, int n, int q, int batch, int mu, int terms
 // The mapping of the block-scaled matrix-core kernel (row_mode 1): the same candidates, and the same
 // kind of estimate (us; left in `est`).  MFMAs per wave: 5 digits x 4 steps per key group and tile, at
 // 33 clk and an overhead that falls with the tiles of a wave, but no less than 564 clk per step (the keys
-// are requested one key group ahead); 7.7 us for the two dispatches, 1 us per MB of padded X.  Fitted to
-// 1100 timed plans of 24 layer shapes (139 x 12096 .. 16384 x 4096, 7 .. 256 vectors, fp32- and bf16-valued):
-// the estimate's choice is on average 0.5 % and at most 10 % slower than the fastest.
+// are requested one key group ahead); 7.7 us for the two dispatches, 1 us per MB of padded X, 0.1 per MB of results.
+// What the inputs hold is not known here.  For bf16 values, whose 16-bit weights are expanded per column tile, two
+// column tiles are faster (16384 x 4096, 2 planes, 128 vectors 37.6 us instead of 40.0, three bf16 terms 38.1), for others slower
+// (50.0 instead of 48.1; with fewer than eight tiles per wave 10-25 %): they are chosen for eight tiles and long rows.
+// On 90 shapes (128 .. 16384 columns, 14 .. 256 vectors) the choice is 2.3 % (fp32) and 2.5 % (bf16 values) slower
+// than the fastest of up to 36 mappings on average, 19 % at most (one row step more or less of a short row).
 bool plan_digits(biq_plan& pl, int m, int n, int q, int batch, double& est) {
+    double best = 1e30;
     est = 1e30;
     if (q > 4) return false;
     pl = biq_plan{};
@@ -373,13 +396,16 @@ bool plan_digits(biq_plan& pl, int m, int n, int q, int batch, double& est) {
                     if (gpw > 64) continue;
                     // workgroups of up to 4 tiles per wave share a CU
                     double rounds = (double)ceil_div_ll(wgs, kNumCu);
-                    if (tiles <= 4) rounds = 1.0 + (rounds - 1.0) * 0.95;
+                    if (tiles <= 4) rounds = 1.0 + (rounds - 1.0) * (tiles <= 2 && groups == 1 ? 0.6 : 0.95);
                     const double bpad_mb = (double)ceil_div(batch, bt) * bt * 4 / 1e6;   // MB per element of a vector
                     double step = 165.0 * (1.043 * tiles + 1.011);
                     if (step < 564.0) step = 564.0;
-                    double t = 7.7 + 0.99 * bpad_mb * n + rounds * (4.0 * gpw * step / 2100.0 + 0.5 * tiles);
+                    double t = 7.7 + 0.99 * bpad_mb * n + rounds * (4.0 * gpw * step / 2100.0 + 0.5 * tiles) +
+                               0.4e-6 * m * (double)batch;
                     if (S > 1) t += 1.5 + 0.304 * (S + 1.0) * bpad_mb * m;
-                    if (t < est) {
+                    const double rank = ct == 1 ? t : tiles < kDigitMaxTiles ? 1.05 * t : gpw >= 6 ? 0.99 * t : t;
+                    if (rank < best) {
+                        best = rank;
                         est = t;
                         pl.batch_tile = bt;
                         pl.wave_splits = ws;
@@ -387,7 +413,7 @@ bool plan_digits(biq_plan& pl, int m, int n, int q, int batch, double& est) {
                         pl.tiles_per_split = ceil_div(groups, S);
                     }
                 }
-    return est < 1e30 && plan_finish(pl, m, n, q, batch, 8);
+    return best < 1e30 && plan_finish(pl, m, n, q, batch, 8);
 }
 
 // Default mapping.  Algorithm 2 leaves the tile sizes open; the choices here are:
@@ -598,7 +624,7 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
             pl.table_fill = 2;
         return ok;
     }
-    DirectGeom g;
+    DirectGeom g{};
     const double direct = ok && m >= 128 && direct_geometry(g, m, n, q, batch) ? g.est : 1e30;
     // (no digit plan is estimated below 8.3 us: small calls, where this search would show, skip it; the
     // narrow-key kernel keeps calls below 5e6 multiply-adds that direct does not take: 129 x 5000, 2
@@ -608,10 +634,18 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
     // (1541 x 384, 2, 4: 4.3 / 4.6); narrow keys and the generic kernel gain almost always (1790 x 316, mu = 7, 3, 5:
     // 18.6 / 4.7)
     const bool tuned = pl.kernel == KERNEL_GEMM8X2 || pl.kernel == KERNEL_GEMM8X2H;
-    // ... except one vector on short rows of one plane or few rows (310460 x 192, 1 plane, mu = 4: 7.5 / 13.9; 982 x
-    // 144, 2: 3.7 / 4.0; but 68544 x 206, 3, mu = 6: 13.6 / 6.5)
-    const bool brief = batch == 1 && n <= 512 && (q == 1 || (long long)m * q < 4096);
-    const bool use_direct = tuned ? tables > 6.5 && direct < 0.8 * tables : !brief && direct < 0.95 * tables;
+    // ... except one vector on a few short rows (982 x 144, 2: 3.7 / 4.0; but 68544 x 206, 3, mu = 6: 13.6 / 6.5), and
+    // with a margin against the narrow-key kernel where direct's estimate is the looser one: a single row step (221 x
+    // 3376, 4, 25 at mu = 4 9.9 / 11.8) or one plane (38243 x 14976, 1, 1 31.1 / 34.0; but 19584 x 11456, 2, 1 25.5 / 22.0)
+    const bool brief = batch == 1 && n <= 512 && (long long)m * q < 4096;
+    const double margin = pl.kernel != KERNEL_WIDE ? 0.95 : g.steps == 1 ? 0.85 : q == 1 ? 0.8 : 0.95;
+    const bool use_direct = tuned ? tables > 6.5 && direct < 0.8 * tables : !brief && direct < margin * tables;
+    // (one vector padded to 32 is never the better use of the matrix cores where direct takes it: 310460 x 192, mu = 4
+    // 17 us in digits, 6.8 with tables)
+    if (batch == 1 && (brief || direct < 1e30)) {
+        if (use_direct) pl.table_fill = 2;
+        return ok;
+    }
     const double few = use_direct ? direct : tables;
     if (few >= 8.3 && !(pl.kernel == KERNEL_WIDE && (double)q * m * n * batch < 5e6)) {
         biq_plan d;

@@ -83,3 +83,25 @@ def test_direct_row_limit(biq):
         else:
             with pytest.raises(biq.BiqError):
                 biq.biq_plan_check(m, 100, 1, 3, 8, p)
+
+
+@pytest.mark.parametrize("m,n,q,b,mu", [
+    (310460, 192, 1, 1, 4), (70016, 286, 1, 1, 4), (90816, 128, 1, 1, 6), (300000, 256, 1, 1, 5), (1 << 20, 128, 1, 1, 4),
+    (320782, 131, 2, 1, 6), (367424, 154, 4, 1, 6), (209107, 128, 3, 1, 6), (145712, 512, 1, 1, 4), (65088, 128, 1, 1, 7),
+    (982, 144, 2, 1, 4), (221, 3376, 4, 25, 4), (150, 3086, 2, 51, 4), (38243, 14976, 1, 1, 4)])
+def test_tables_where_they_are_faster(biq, m, n, q, b, mu):
+    """Short rows with one vector and few rows of narrow keys: 1.1 to 5.7 times the tables' time without them.  (What runs is
+    allowed to be the direct kernel for one vector on rows of several key units, never the 32-vector one.)"""
+    p, lut = biq.biq_plan_get(m, n, q, b, mu), biq.biq_plan_get_lut(m, n, q, b, mu)
+    if (m, n) in ((70016, 286), (300000, 256), (145712, 512)):
+        assert p.kernel == lut.kernel
+    else:
+        assert p.as_dict() == lut.as_dict()
+
+
+def test_two_column_tiles_for_long_rows_and_eight_tiles(biq):
+    """Where estimates tie, the mapping that bf16 values prefer (they keep 16-bit weights, expanded per column tile)."""
+    for (m, n, q, b) in [(16384, 4096, 2, 128), (25237, 2972, 4, 37)]:
+        p = biq.biq_plan_get(m, n, q, b, 8)
+        assert p.kernel == 3 and p.row_mode == 1 and p.batch_tile == 64
+    assert biq.biq_plan_get(31424, 512, 2, 104, 8).batch_tile == 32
