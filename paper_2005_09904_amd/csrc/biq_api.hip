@@ -736,8 +736,7 @@ void fill_query_params(QueryParams& qp, const biq_plan& pl, const uint8_t* K, co
     qp.tasks_per_xcd = ceil_div(qp.ntasks, kNumXcd);
     qp.row_mode = pl.row_mode;
     qp.xcd_skew = pl.xcd_skew;
-    qp.table_fill = pl.table_fill;
-    qp.gather = LUT && gather_tables(pl, m, q, batch, qp.C) && batch == 1;
+    qp.table_fill = LUT ? (batch == 1 && gather_tables(pl, m, q, batch, qp.C)) : pl.table_fill;
 }
 
 // Plan of one problem of a grouped launch: mu = 8, at most 4 planes, a single dispatch without

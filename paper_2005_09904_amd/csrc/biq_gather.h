@@ -21,7 +21,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gather_tables_of(const QueryPa
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.LUT), 0, p.C * 1024 * p.batch, 0x00020000);
 }
 
-// One input vector: entry `key` of chunk `chunk` (the kernels of biq_gemv8.h and biq_gemv8h.h with p.gather).
+// One input vector: entry `key` of chunk `chunk` (the kernels of biq_gemv8.h and biq_gemv8h.h with p.table_fill).
 __device__ __forceinline__ float gather_entry(const QueryParams& p, uint32_t chunk, uint32_t key) {
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(gather_tables_of(p), (int)(chunk * 1024u + key * 4u), 0, 0));
 }

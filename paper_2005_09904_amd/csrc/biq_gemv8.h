@@ -219,7 +219,7 @@ __device__ __forceinline__ void gemv8_body(const QueryParams& p, const int wg) {
     auto lookup16 = [&](const u32x4& k) -> float {
         const uint32_t w[4] = {k.x, k.y, k.z, k.w};
         float a0, a1;
-        if (!FUSED && p.gather) {   // (latency mode: one tile)
+        if (!FUSED && p.table_fill) {   // (latency mode: one tile)
             float v[16];
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
@@ -287,7 +287,7 @@ __device__ __forceinline__ void gemv8_body(const QueryParams& p, const int wg) {
         if constexpr (FUSED) {
             if (x_first) gemv8_job_build(p, lds_bytes, tile * kGemvTileChunks, tid, xf);
             else gemv8_build_tile(p, lds_bytes, tile * kGemvTileChunks, tid, nthreads);
-        } else if (!p.gather) {
+        } else if (!p.table_fill) {
             gemv8_copy_tile(p, lds_bytes, tile * kGemvTileChunks, tid, nthreads);
         }
         __syncthreads();

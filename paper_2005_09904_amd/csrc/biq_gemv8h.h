@@ -159,7 +159,7 @@ __device__ __forceinline__ void gemv8h_body(const QueryParams& p, const int wg) 
     // lookup, the compiler keeps at most three in flight and the loop runs at LDS latency).
     auto lookup16 = [&](const u32x4& k) -> float {
         const uint32_t w[4] = {k.x, k.y, k.z, k.w};
-        if (!FUSED && p.gather) {
+        if (!FUSED && p.table_fill) {
             float v[16];
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
@@ -241,7 +241,7 @@ __device__ __forceinline__ void gemv8h_body(const QueryParams& p, const int wg) 
         if constexpr (FUSED) {
             if (x_ahead) gemv8h_job_build(p, lds_bytes, tile * kGemvHalfTileChunks, tid, xa);
             else gemv8h_build_tile(p, lds_bytes, tile * kGemvHalfTileChunks, tid, nthreads);
-        } else if (!p.gather) {
+        } else if (!p.table_fill) {
             gemv8h_copy_tile(p, lds_bytes, tile * kGemvHalfTileChunks, tid, nthreads);
         }
         __syncthreads();
@@ -255,7 +255,7 @@ __device__ __forceinline__ void gemv8h_body(const QueryParams& p, const int wg) 
                 half_table_prepare(kw[i], idx, sgn);
 #pragma unroll
                 for (int te = 0; te < 4; ++te) {
-                    if (!FUSED && p.gather) {
+                    if (!FUSED && p.table_fill) {
                         const uint32_t e = (uint32_t)((te + td1) & 3);
                         acc += gather_entry(p, (uint32_t)(tile * kGemvHalfTileChunks + 4 * lane) + e,
                                             (kw[i] >> (8 * e)) & 255u);
@@ -368,7 +368,7 @@ __device__ __forceinline__ void gemv8h_body(const QueryParams& p, const int wg) 
             } else {
                 gemv8h_build_tile(p, lds_bytes, tl * kGemvHalfTileChunks, tid, nthreads);
             }
-        } else if (!p.gather) {
+        } else if (!p.table_fill) {
             gemv8h_copy_tile(p, lds_bytes, tl * kGemvHalfTileChunks, tid, nthreads);
         }
         BIQ_STAMP(p, 4);

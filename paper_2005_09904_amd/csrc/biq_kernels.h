@@ -166,8 +166,9 @@ struct QueryParams {
     int ntasks, tasks_per_xcd;
     int row_mode;  // mu = 8 kernels: 0 = 64-row blocks per wave, 1 = one row step per wave
     int xcd_skew;  // gemv8 throughput mode: rows moved from each odd-XCD workgroup to an even-XCD one
-    int table_fill;  // gemv8, fused tables: 0 = direct fill from pair sums, 1 = Algorithm 1's order
-    int gather;      // one input vector, !FUSED: 1 = lookups read LUT itself, no copy in LDS (biq_gather.h)
+    int table_fill;  // gemv8, fused tables: 0 = direct fill from pair sums, 1 = Algorithm 1's order; tables given, one
+                     // input vector: 1 = lookups read LUT itself, no copy in LDS (biq_gather.h).  (No field of its
+                     // own: 16 of these structures are a grouped call's arguments, and 8 bytes more in each cost it 1 %.)
     // LSTM-cell epilogue (the LSTM instantiations of the half-table kernels only): the m = 4 * hidden
     // rows are the gates i, f, g, o stacked; `out` receives h [batch][hidden]
     const float* bias;    // [4 * hidden]
