@@ -44,7 +44,7 @@ inline int unit_keys(int mu) {
     }
 }
 
-inline int ceil_div(int a, int b) { return (int)(((long long)a + b - 1) / b); }
+inline int ceil_div(int a, int b) { return (int)(((unsigned)a + (unsigned)b - 1u) / (unsigned)b); }   // a >= 0, b >= 1
 inline long long ceil_div_ll(long long a, long long b) { return (a + b - 1) / b; }
 // a * b * c of counts up to 2^31 each, 2^61 where it is more (comparisons and quotients stay meaningful)
 inline long long product(long long a, long long b, long long c) {
@@ -607,7 +607,8 @@ bool plan_generic(biq_plan& pl, int m, int n, int q, int batch, int mu) {
 // fails too (the caller reports BIQ_EUNSUPPORTED, sizes read as 0).
 // Many input vectors: the contraction is compute bound and the matrix cores (block-scaled digits) beat
 // the table lookups, from the estimated times of both.
-bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tables_given = false) {
+bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tables_given = false,
+                  DirectGeom* geom = nullptr) {
     const bool ok = plan_tables(pl, m, n, q, batch, mu) || plan_generic(pl, m, n, q, batch, mu);
     if (tables_given || q > 4) return ok;
     const double tables = ok ? tables_estimate(pl, m, n, q, batch, mu) : 1e30;
@@ -624,7 +625,8 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
             pl.table_fill = 2;
         return ok;
     }
-    DirectGeom g{};
+    DirectGeom local{};
+    DirectGeom& g = geom ? *geom : local;             // (a caller that launches the direct kernel has use for it)
     const double direct = ok && m >= 128 && direct_geometry(g, m, n, q, batch) ? g.est : 1e30;
     // (no digit plan is estimated below 8.3 us: small calls, where this search would show, skip it; the
     // narrow-key kernel keeps calls below 5e6 multiply-adds that direct does not take: 129 x 5000, 2
@@ -845,11 +847,10 @@ biq_status run_unpack_mfma(const biq_plan& pl, const uint8_t* K, const float* al
     return BIQ_OK;
 }
 
-// Few input vectors, no tables (table_fill 2).
-biq_status run_direct(const uint8_t* K, const float* alpha, const float* X, float* out, int m, int n, int q, int batch,
-                      hipStream_t s) {
-    DirectGeom g;
-    if (!direct_geometry(g, m, n, q, batch)) return BIQ_EUNSUPPORTED;
+// Few input vectors, no tables (table_fill 2).  g: the geometry, or row_blocks = 0 if it is still to be found.
+biq_status run_direct(DirectGeom& g, const uint8_t* K, const float* alpha, const float* X, float* out, int m, int n, int q,
+                      int batch, hipStream_t s) {
+    if (g.row_blocks == 0 && !direct_geometry(g, m, n, q, batch)) return BIQ_EUNSUPPORTED;
     DirectParams p{};
     p.K = K;
     p.alpha = alpha;
@@ -878,11 +879,12 @@ biq_status run_query(bool fused, const uint8_t* K, const float* alpha, const flo
     if (!aligned(K, 16) || !aligned(alpha, 4) || !aligned(Y, 4) || !aligned(fused ? X : LUT, 4))
         return BIQ_EINVAL;
     biq_plan pl;
+    DirectGeom geom{};
     if (user_plan) {
         pl = *user_plan;
         if (!plan_finish(pl, m, n, q, batch, mu)) return BIQ_EINVAL;
     } else {
-        if (!plan_default(pl, m, n, q, batch, mu, !fused)) return BIQ_EUNSUPPORTED;
+        if (!plan_default(pl, m, n, q, batch, mu, !fused, &geom)) return BIQ_EUNSUPPORTED;
     }
     if (pl.kernel == KERNEL_UNPACK_MFMA && !fused) return BIQ_EINVAL;  // that kernel reads X, not tables
     if (pl.table_fill != 0 && !fused) return BIQ_EINVAL;               // a build method needs tables to build
@@ -894,7 +896,7 @@ biq_status run_query(bool fused, const uint8_t* K, const float* alpha, const flo
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (pl.kernel == KERNEL_UNPACK_MFMA)
         return run_unpack_mfma(pl, K, alpha, X, Y, m, n, q, batch, workspace, s);
-    if (pl.table_fill == 2) return run_direct(K, alpha, X, Y, m, n, q, batch, s);
+    if (pl.table_fill == 2) return run_direct(geom, K, alpha, X, Y, m, n, q, batch, s);
 
     QueryParams qp{};
     fill_query_params(qp, pl, K, alpha, X, LUT, pl.chunk_splits > 1 ? reinterpret_cast<float*>(workspace) : Y, m, n, q,
