@@ -131,7 +131,8 @@ typedef struct {
                             workgroup).  unpack_mfma: 0 = the inputs as 16-bit terms (input_terms),
                             1 = (the library's choice) block-scaled digits: every 32 consecutive
                             elements of an input vector share a power of two and are split into five
-                            6-bit floats, exact to 2^-24 of the largest of the 32, contracted with
+                            6-bit floats, exact to 2^-24 of the largest of the 32 (any finite
+                            values, subnormal ones included), contracted with
                             4-bit weights; inputs holding bf16 values keep one bf16 term.
                             input_terms must be 3 (or 0) and sizes the workspace                 */
     int xcd_skew;        /* GEMV kernel, row_mode 0, no chunk split, row_blocks a multiple of 8:
@@ -146,7 +147,9 @@ typedef struct {
     int table_fill;      /* 2 = no tables (what the library chooses for few input vectors where it is faster;
                             any kernel but unpack_mfma, any mu, q <= 4): the inputs become 6-bit digits
                             (see row_mode 1 of unpack_mfma) in LDS and the keys 4-bit weights for the matrix
-                            cores, in one dispatch with a mapping of its own; the other fields describe
+                            cores, in one dispatch with a mapping of its own (sums rounded to 2^-143 where
+                            they are smaller than 2^-120); the other fields, `kernel` and the
+                            workspace among them, describe
                             the table kernel that biq_query runs for the shape.  GEMV kernel, fused tables: 0 = every entry from the chunk's pair sums (a direct,
                             GEMM-like fill), 1 = the order of Algorithm 1: a block's first entry, then
                             each further entry of the lower half from an earlier one by adding 2 x_t,
@@ -172,9 +175,9 @@ typedef struct {
 
 biq_status biq_plan_get(int m, int n, int q, int batch, int mu, biq_plan* plan);
 /* The library's choice among the lookup-table kernels only (Algorithm 2 proper): what biq_query
- * runs, and what biq_gemm runs below the batch size from which it switches to unpacking the
- * keys into the matrix cores (the large-batch regime of Sec. IV-B where a plain GEMM on
- * unpacked weights wins). */
+ * runs, and what biq_gemm runs where it does not expand the keys for the matrix cores instead: for
+ * many input vectors (unpack_mfma, the large-batch regime of Sec. IV-B where a plain GEMM on
+ * unpacked weights wins) or for few (table_fill 2). */
 biq_status biq_plan_get_lut(int m, int n, int q, int batch, int mu, biq_plan* plan);
 /* The library's mapping of the unpack_mfma kernel for a shape (q <= 4, else BIQ_EUNSUPPORTED),
  * whichever side of the crossover the shape is on, for input_terms = 3 or 2 (see biq_plan):
@@ -306,11 +309,17 @@ biq_status biq_lstm_cell(const uint8_t* K, const float* alpha, const float* bias
 /*
  * biq_gemm for callers that cannot allocate or hand over device memory for a workspace: code
  * whose launches are being captured into a HIP graph, serving loops with a fixed memory plan,
- * harnesses that forbid hipMalloc.  Same arguments, plan, kernels and results (bit for bit) as
- * biq_gemm, but the workspace is a fixed buffer of biq_noalloc_scratch_bytes() = 32 MiB of device
+ * harnesses that forbid hipMalloc.  Same arguments as biq_gemm, but the workspace is a fixed buffer
+ * of biq_noalloc_scratch_bytes() = 32 MiB of device
  * memory inside the library's own code object (one copy per GPU, held until the process ends).
- * Nothing is allocated or freed, by the library or by the runtime on its behalf.
- *   - BIQ_EWORKSPACE if biq_workspace_bytes(m, n, q, batch, mu) exceeds that size (no kernel is
+ * Nothing is allocated or freed, by the library or by the runtime on its behalf (no kernel uses
+ * scratch memory).
+ *   - Where the workspace of biq_gemm's plan (biq_plan_get, biq_plan_workspace_bytes) fits that size:
+ *     the same plan, kernels and results, bit for bit.
+ *   - Where it does not (wide batches: prepared inputs, partial sums), a plan that may need less
+ *     takes the call: the tables, or the matrix cores with three 16-bit terms.  Same tolerance, not the
+ *     same bits.
+ *   - BIQ_EWORKSPACE if that one does not fit either (no kernel is
  *     launched; all five benchmark configurations fit): use biq_gemm with a caller workspace.
  *   - Every call on one GPU uses that GPU's single buffer: calls that may overlap in time on one
  *     GPU (different streams, different host threads) race on it and must be serialised by the
