@@ -150,6 +150,28 @@ def summarize(w, t: Timing):
     return row
 
 
+def kernel_label(biq, plan):
+    """What a plan runs: a table kernel's plan marked with table_fill 2 is the direct kernel."""
+    return "direct" if plan.table_fill == 2 else biq.biq_kernel_name(plan.kernel)
+
+
+def compact(value):
+    """The printed line: floats to five significant digits (with the rows cut to ROW_KEYS and FAMILY_KEYS, since a
+    line of more than some 12 KB does not reach every reader whole; the rest is on stderr)."""
+    if isinstance(value, float):
+        return float("%.5g" % value)
+    if isinstance(value, dict):
+        return {k: compact(v) for k, v in value.items()}
+    if isinstance(value, list):
+        return [compact(v) for v in value]
+    return value
+
+
+ROW_KEYS = ("workload", "us_per_call", "effective_GOPS", "kernel", "input_values", "default_plan", "input_terms",
+            "mfma_frac", "lds_frac")
+FAMILY_KEYS = ("workload", "us_per_call", "hbm_frac", "kernel", "dispatches")
+
+
 def read_profiled_traffic(algorithmic_bytes: int):
     """HBM bytes per launch of the roofline kernel from the committed counter summary
     (profiles/gemv8_q2_hbm_regime_counters.md: two rocprofv3 --pmc runs, scaled by a copy of known
@@ -281,7 +303,7 @@ def main() -> int:
         p.touch_all(torch)
         srow = summarize(w, time_steps(torch, p, steps, 5))
         srow["plan"] = (plan or biq.biq_plan_get(w.m, w.n, w.q, w.batch, w.mu)).as_dict()
-        srow["kernel"] = biq.biq_kernel_name(srow["plan"]["kernel"])
+        srow["kernel"] = kernel_label(biq, plan or biq.biq_plan_get(w.m, w.n, w.q, w.batch, w.mu))
         print(json.dumps(srow))
         return 0
 
@@ -330,7 +352,7 @@ def main() -> int:
             # by a copy of known size), not measured in this run
             "traffic": traffic,
             "traffic_source": ("profiles/gemv8_q2_hbm_regime_counters.md @ %s" % traffic_commit) if traffic else None,
-            "kernel": biq.biq_kernel_name(plan.kernel),
+            "kernel": kernel_label(biq, plan),
             "workload": big.name,
             "algorithmic_bytes_per_launch": big.algorithmic_bytes,
             "launch_us": launch_s * 1e6,
@@ -366,18 +388,22 @@ def main() -> int:
             # digits), the lookup-table kernel on the same inputs as a second row and the two-term
             # variant of the matrix-core kernel, which only an explicit plan selects, as a third
             plans = [(None, "fp32")]
-            if default.kernel != lut.kernel:
+            if default.kernel != lut.kernel or default.table_fill == 2:
                 plans += [(lut, "fp32"), (biq.biq_plan_get_mfma(w.m, w.n, w.q, w.batch, w.mu, 2), "fp32")]
                 if w.mu == 8:
                     # the library's plan again on fp32 inputs that hold fp16 / bf16 values (activations
-                    # computed in half precision): their last digits are zero
-                    # there and the kernel skips them
+                    # computed in half precision): bf16 values take one 16-bit term instead of five digits,
+                    # fp16 values the five digits; the two-term variant skips its second term for them
                     plans += [(None, "fp16"), (None, "bf16"),
                               (biq.biq_plan_get_mfma(w.m, w.n, w.q, w.batch, w.mu, 2), "fp16")]
             for plan, x_values in plans:
-                kname = biq.biq_kernel_name((plan or default).kernel)
+                kname = kernel_label(biq, plan or default)
                 digits = (plan or default).row_mode == 1      # block-scaled 6-bit digits instead of 16-bit terms
                 terms = 5 if digits else (plan or default).input_terms
+                if digits and x_values == "bf16":
+                    digits, terms = False, 1
+                elif x_values == "fp16" and terms == 2:
+                    terms = 1
                 copies = max(1, min(64, (512 * 1024 * 1024) // w.key_bytes + 1))
                 p = Problem(biq, torch, w, copies, real_first=False, plan=plan, x_values=x_values)
                 steps = 200 if w.lookups < 1e9 else 20
@@ -389,18 +415,15 @@ def main() -> int:
                 s["kernel"] = kname
                 s["default_plan"] = plan is None
                 if kname == "unpack_mfma":
-                    # dense contraction: 2 flop per weight and input vector, times the 16-bit
-                    # terms of x (3 bf16, or 2 fp16) or its 6-bit digits, on columns padded to the
-                    # 32-wide MFMA tile
+                    # dense contraction: 2 flop per weight and input vector, times the 16-bit terms or 6-bit
+                    # digits of x that are executed, on columns padded to the 32-wide MFMA tile
                     padded = -(-w.batch // 32) * 32
                     s["input_terms"] = terms
                     s["mfma_TFLOPs"] = 2.0 * terms * w.q * w.m * w.n * padded / t.median / 1e12
                     s["mfma_frac"] = s["mfma_TFLOPs"] / (MFMA_F4_PEAK_TFLOPS if digits else MFMA_F16_PEAK_TFLOPS)
-                    if terms == 2 and x_values == "fp32":
-                        kname = "unpack_mfma, 2 input terms"
-                    elif x_values != "fp32":
-                        kname = "unpack_mfma%s, %s-valued inputs" % (", 2 input terms" if terms == 2 else "", x_values)
-                        del s["mfma_TFLOPs"], s["mfma_frac"]    # fewer terms are executed than counted above
+                    two_terms = ", 2 input terms" if (plan or default).input_terms == 2 else ""
+                    if two_terms or x_values != "fp32":
+                        kname = "unpack_mfma%s%s" % (two_terms, "" if x_values == "fp32" else ", %s-valued inputs" % x_values)
                 elif w.batch > 1:
                     # batched table lookups are bounded by gathers from LDS (4 bytes per lookup)
                     s["lds_gather_GBps"] = 4.0 * w.lookups / t.median / 1e9
@@ -422,7 +445,7 @@ def main() -> int:
             default = biq.biq_plan_get(nn, nn, 1, bb, 8)
             lut = biq.biq_plan_get_lut(nn, nn, 1, bb, 8)
             row = {"n": nn, "batch": bb, "paper_v100_us": v100}
-            for tag, plan in (("us", None), ("lut_us", lut if default.kernel != lut.kernel else None)):
+            for tag, plan in (("us", None), ("lut_us", lut if default.kernel != lut.kernel or default.table_fill == 2 else None)):
                 if tag == "lut_us" and plan is None:
                     continue
                 copies = max(2, min(64, (256 * 1024 * 1024) // w.key_bytes + 1))
@@ -430,7 +453,7 @@ def main() -> int:
                 steps = 200 if bb <= 32 else 50
                 p.touch_all(torch)
                 row[tag] = time_steps(torch, p, steps, 5).median * 1e6
-                row["kernel" if tag == "us" else "lut_kernel"] = biq.biq_kernel_name((plan or default).kernel)
+                row["kernel" if tag == "us" else "lut_kernel"] = kernel_label(biq, plan or default)
                 del p
                 torch.cuda.empty_cache()
             grid.append(row)
@@ -619,14 +642,14 @@ def main() -> int:
             plan = biq.biq_plan_get(w.m, w.n, w.q, w.batch, w.mu)
             fam.append({"workload": w.name, "m": w.m, "n": w.n, "key_bytes": w.key_bytes, "us_per_call": s["us_per_call"],
                         "min_us_per_call": s["min_us_per_call"], "achieved_GBps": s["achieved_GBps"],
-                        "hbm_frac": s["hbm_frac"], "kernel": biq.biq_kernel_name(plan.kernel),
-                        "dispatches": 2 if plan.chunk_splits > 1 else 1})
+                        "hbm_frac": s["hbm_frac"], "kernel": kernel_label(biq, plan),
+                        "dispatches": 2 if plan.chunk_splits > 1 and plan.table_fill != 2 else 1})
             log("family %s: %.2f us/call (min %.2f), %.0f GB/s = %.1f%% of HBM peak [%s]" %
                 (w.name, s["us_per_call"], s["min_us_per_call"], s["achieved_GBps"], 100 * s["hbm_frac"],
                  fam[-1]["kernel"]))
             del p
             torch.cuda.empty_cache()
-        out["gemv_b1_family"] = fam
+        out["gemv_b1_family"] = [{k: row[k] for k in FAMILY_KEYS} for row in fam]
 
     cpu = None
     if not args.no_cpu_baseline and prob is not None and prob.host is not None:
@@ -660,10 +683,10 @@ def main() -> int:
         "headline": head_sum,
         "roofline": roof,
         "cpu_baseline": cpu,
-        "workloads": extra,
+        "workloads": [{k: row[k] for k in ROW_KEYS if k in row} for row in extra],
     }
     line.update(out)
-    print(json.dumps(line))
+    print(json.dumps(compact(line), separators=(",", ":")))
     return 0
 
 
