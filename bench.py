@@ -167,9 +167,8 @@ def compact(value):
     return value
 
 
-ROW_KEYS = ("workload", "us_per_call", "effective_GOPS", "kernel", "input_values", "default_plan", "input_terms",
-            "mfma_frac", "lds_frac")
-FAMILY_KEYS = ("workload", "us_per_call", "hbm_frac", "kernel", "dispatches")
+ROW_KEYS = ("workload", "us_per_call", "kernel", "input_values", "default_plan", "input_terms", "mfma_frac", "lds_frac")
+FAMILY_KEYS = ("workload", "us_per_call", "hbm_frac", "kernel")
 
 
 def read_profiled_traffic(algorithmic_bytes: int):
