@@ -72,7 +72,7 @@ def test_digit_parity(biq, oracle, m, n, q, b, bt, gps, ws, r, form):
 
 
 def test_digits_hold_what_they_promise(biq, oracle):
-    """Exact inputs bit for bit; a one-hot vector returns its element; scales from 2^-100 to 2^120 and elements over
+    """Exact inputs bit for bit; a one-hot vector returns its element; scales from 2^-100 to 2^95 and elements over
     twelve orders of magnitude within the bound; Inf and NaN stay in their vector."""
     from paper_2005_09904_amd.workloads import Workload, make_exact_inputs
 
@@ -148,3 +148,30 @@ def test_digits_largest_inputs(biq, oracle):
     assert np.isfinite(Y).all()
     assert np.array_equal(Y[[0, 1, 2, 33]].astype(np.float64), ref[[0, 1, 2, 33]])
     assert np.all(np.abs(Y - ref).max(axis=1) <= _bound(alpha, X))
+
+
+@pytest.mark.parametrize("n,b", [(256, 33), (1001, 40), (1002, 31), (1003, 64), (130, 5)])
+@pytest.mark.parametrize("form", ["fp32", "bf16"])
+def test_digits_inputs_on_odd_addresses(biq, oracle, n, b, form):
+    """Vectors on odd float addresses, NaN in front of the first and behind the last: reads past a vector's end and past
+    the batch count as zero, and no alignment is assumed.  Nothing is written outside the results."""
+    import torch
+
+    m, q = 70, 2
+    print("digits, odd addresses", n, b, form, flush=True)
+    B, alpha, X = _inputs(m, n, q, b, 600 + n)
+    if form == "bf16":
+        X = torch.from_numpy(X).bfloat16().float().numpy()
+    Bd, ad, _ = device_inputs(B, alpha, X)
+    buf = torch.full((b * n + 1 + 512,), float("nan"), device="cuda")
+    Xd = buf[1:1 + b * n].view(b, n)
+    Xd.copy_(torch.from_numpy(X))
+    guard = torch.full((b * m + 1 + 64,), 7.0, device="cuda")
+    Y = guard[1:1 + b * m].view(b, m)
+    plan = biq.biq_plan_check(m, n, q, b, 8, _plan(biq, q, 32, 2, 2, 2))
+    ws = torch.empty(max(biq.biq_plan_workspace_bytes(plan, m, b), 16), dtype=torch.uint8, device="cuda")
+    biq.biq_gemm_ex(gpu_pack(biq, Bd), ad, Xd, Y, m, n, q, b, 8, plan, workspace=ws)
+    torch.cuda.synchronize()
+    assert bool((guard[1 + b * m:] == 7.0).all()) and float(guard[0]) == 7.0
+    ref = oracle.gemm_dense(B, alpha, X)
+    assert np.all(np.abs(Y.cpu().numpy() - ref).max(axis=1) <= _bound(alpha, X))
