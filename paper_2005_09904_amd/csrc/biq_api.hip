@@ -618,7 +618,8 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
     if (mu == 8 && batch == 1) {
         // One vector (keys from memory): rows beyond one half-table tile whose inputs the table kernels cannot
         // read 16 bytes at a time (n % 4; 5000 x 3001, 3 planes 11.9 us with tables, 6.4 without; 236 x 4414, 2:
-        // 14.2 / 5.0; 4928 x 9573, 1: 10.3 / 8.2), up to 24 MB of keys.  Others: 16384 x 4096, 2: 8.4 / 8.6;
+        // 14.2 / 5.0; 4928 x 9573, 1: 10.3 / 8.2), up to 24 MB of keys.  Others: 16384 x 4096, 2: 8.2 / 8.5 (keys on
+        // chip 7.3 / 5.9);
         // 452 x 832, 3: 3.9 / 4.6; 15265 x 10112, 4, 77 MB: 22.5 / 28.8.
         const long long keys = (long long)q * m * (long long)biq_key_row_stride(n);
         if (ok && m >= 128 && n > 2048 && n % 4 != 0 && keys <= 24000000 && direct_max_vectors(n) > 0)

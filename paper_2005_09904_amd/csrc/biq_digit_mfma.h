@@ -21,7 +21,7 @@
 // Relative 2-norm error against fp64, normal inputs, three bf16 terms -> digits: 16384 x 4096, 2
 // planes, 128 vectors 4.2e-7 -> 5.8e-8; 4096 x 16384 5.9e-7 -> 6.6e-8; 4096^2, 3 planes, 32 vectors
 // 2.2e-7 -> 7.4e-8 (the table kernels: 1.1e-7).
-// Time, same order (us per call): 82 -> 47; 86 -> 51; 17 -> 14.3.  Bound by the power the matrix
+// Time, same order (us per call): 77 -> 46; 86 -> 51; 17.2 -> 14.1.  Bound by the power the matrix
 // cores may draw: the instruction issues at 33 clk, but in a loop of nothing else the clock falls to
 // 1.3-1.5 GHz, 5.1-5.8 PFLOP/s (bf16: 1.3-1.7 PFLOP/s), so fewer and cheaper instructions are what helps.
 // The whole range of fp32 is covered: a block's scale byte stands for its exponent alone, and what the
@@ -31,7 +31,9 @@
 // block that holds Inf or NaN gets the scale NaN, and the vector's results are NaN.
 //
 // Inputs that hold bf16 values (all elements of a key group - 256 - of all vectors of a column
-// group) keep the one-term bf16 form: 16 elements per instruction, but one term instead of six.
+// group) keep the one-term bf16 form: 16 elements per instruction, but one term instead of five digits
+// (16384 x 4096, 2 planes, 128 vectors 35.7 us, 4096 x 16384 38.0; there the 8 instructions that expand a row tile's
+// weights bound the loop as much as its matrix instructions do).  Values of fp16 take all five digits.
 // The form is chosen per (column group, key group) by the kernel that prepares the operands; the
 // main kernel walks first the key groups of one form, then those of the other.
 //

@@ -25,8 +25,10 @@
 // elements), one barrier, keys and LDS reads behind each other: 3.5 us and up.  us per call, keys from memory,
 // before -> here: 5003 x 3001, 3 planes, 7 vectors at mu = 6 13.1 (three bf16 terms 16.3) -> 9.2; 5000 x 3001, 3, 1
 // 11.9 -> 6.4; 10240 x 1216, 2, 12 17.6 -> 8.6; 32000 x 1024, 3, 6 18.6 -> 7.0; 1790 x 316, 3, 5 at mu = 7 18.6 -> 4.7.
-// Errors 4-7e-8 instead of 1.0-1.2e-7 (tables).  No faster than the tables: one vector and rows the tables read 16
-// bytes at a time (16384 x 4096, 2: 8.4 / 8.6), small layers with several vectors (919 x 832, 3, 9: 4.4 / 6.7).
+// With 4 planes and 10-15 vectors, keys on chip: 20000 x 700 9.3, 10000 x 2000 10.3.
+// Errors 4-9e-8 instead of 0.8-1.2e-7 (tables).  Not taken for one vector where the tables read rows 16 bytes at a
+// time (16384 x 4096, 2, tables / direct: keys from memory 8.2 / 8.5, on chip 7.3 / 5.9), nor for small layers with several
+// vectors (919 x 832, 3, 9: 4.4 / 6.7).
 // (Two chunks requested together for few rows, too: 8.6 -> 7.8 there, but 5000 x 3001 6.4 -> 7.8.)
 //
 // Layout.  Operand lane 16 * kg + r: row / column r, the 32 elements of one key dword.  A lane loads
