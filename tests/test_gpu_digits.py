@@ -175,3 +175,39 @@ def test_digits_inputs_on_odd_addresses(biq, oracle, n, b, form):
     assert bool((guard[1 + b * m:] == 7.0).all()) and float(guard[0]) == 7.0
     ref = oracle.gemm_dense(B, alpha, X)
     assert np.all(np.abs(Y.cpu().numpy() - ref).max(axis=1) <= _bound(alpha, X))
+
+
+@pytest.mark.parametrize("exponent", [-110, -120, -125, -128])
+def test_digits_small_bf16_values(biq, oracle, exponent):
+    """bf16 values near and below the smallest normal ones: the 16-bit form, whose even steps are summed at half their size."""
+    import torch
+
+    rng = np.random.default_rng(300 - exponent)
+    m, n, q, b = 100, 1300, 2, 40
+    B = (rng.integers(0, 2, size=(q, m, n), dtype=np.int8) * 2 - 1).astype(np.int8)
+    alpha = rng.uniform(0.05, 1.0, size=(q, m)).astype(np.float32)
+    X = (rng.standard_normal((b, n)) * 2.0 ** exponent).astype(np.float32)
+    X = torch.from_numpy(X).bfloat16().float().numpy()
+    Bd, ad, Xd = device_inputs(B, alpha, X)
+    Y = gpu_gemm(biq, gpu_pack(biq, Bd), ad, Xd, m, n, q, 8, plan=_plan(biq, q, 32, 6, 2, 2)).cpu().numpy()
+    least = np.abs(alpha).sum(axis=0).max() * 16 * -(-n // 256) * 2.0 ** -148 + 2.0 ** -149
+    assert np.all(np.abs(Y - oracle.gemm_dense(B, alpha, X)).max(axis=1) <= _bound(alpha, X) + least)
+
+
+@pytest.mark.parametrize("m,n,q,b,bt,gps,ws,r", SHAPES)
+@pytest.mark.parametrize("where", [0, -1])
+def test_digits_one_key_group_in_the_other_form(biq, oracle, m, n, q, b, bt, gps, ws, r, where):
+    """The first or the last key group in digits, all others in bf16, and the other way round."""
+    import torch
+
+    print("digits, one group", m, n, q, b, bt, gps, ws, r, where, flush=True)
+    B, alpha, X = _inputs(m, n, q, b, 41000 + m + n)
+    half = torch.from_numpy(X).bfloat16().float().numpy()
+    groups = -(-n // 256)
+    at = slice(0, 256) if where == 0 else slice((groups - 1) * 256, n)
+    for base, other in ((half, X), (X, half)):
+        Z = base.copy()
+        Z[:, at] = other[:, at]
+        Bd, ad, Zd = device_inputs(B, alpha, Z)
+        Y = gpu_gemm(biq, gpu_pack(biq, Bd), ad, Zd, m, n, q, 8, plan=_plan(biq, q, bt, gps, ws, r)).cpu().numpy()
+        assert np.all(np.abs(Y - oracle.gemm_dense(B, alpha, Z)).max(axis=1) <= _bound(alpha, Z))
