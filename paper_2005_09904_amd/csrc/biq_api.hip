@@ -16,6 +16,7 @@
 #include "biq_grouped.h"
 #include "biq_digit_mfma.h"
 #include "biq_direct.h"
+#include "biq_gather.h"
 
 namespace {
 
@@ -697,10 +698,11 @@ size_t plan_workspace(const biq_plan& pl, int m, int batch) {
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
 // mu = 8, tables in device memory: lookups read the tables where they lie instead of from a copy in LDS
-// (biq_gather.h) if there are few of them.  A copy costs 16-17 us per tile a workgroup walks; the reads,
-// counted per four input vectors, 3.5-4.3 us per million: 4096 x 2048, 2 planes, 4 vectors (2.1 million) 19.4 us
-// with the copy, 11.4 without; 2048 x 4096, 4, 2 (4.2) 20.0 / 19.4; 3000 x 1024, 4, 12 (4.6) 19.3 / 20.5;
-// 4096 x 2000, 4, 8 (8.2) 22.0 / 34.8; one vector, two tiles: 4096 x 4096, 4 planes (8.4) 32.8 / 30.0.
+// (biq_gather.h) if there are few of them.  A copy costs 16-17 us per tile a workgroup walks and the second dispatch of
+// a split row; the reads, counted per four input vectors, 3.7-5 us per million up to 4 vectors, 2.8 up to 8 and 1.8-2.6
+// beyond, where neighbouring lanes share an entry's lines (gather_log_slices).  Copied / in place: 4071 x 1941, 2
+// planes, 5 vectors (4.0 million) 20.1 / 11.0 us; 3345 x 4044, 2, 7 (6.8) 22.3 / 19.6; 2397 x 3767, 4, 7 (9.0) 23.2 / 25.1;
+// 3970 x 2085, 2, 13 (8.3) 40 / 15; one vector, two tiles: 4096 x 4096, 4 planes (8.4) 32.8 / 30.0.
 constexpr long long kGatherLookups = 4200000;
 bool gather_tables(const biq_plan& pl, int m, int q, int batch, int C) {
     if (pl.kernel != KERNEL_GEMV8 && pl.kernel != KERNEL_GEMV8H && pl.kernel != KERNEL_GEMM8X2 &&
@@ -711,8 +713,23 @@ bool gather_tables(const biq_plan& pl, int m, int q, int batch, int C) {
     // 131072 vectors: chunk 32 would be chunk 0 again); slices of 4 vectors are the grid's z, at most 65535
     const long long tile_end = (long long)ceil_div(C, pl.chunks_per_tile) * pl.chunks_per_tile;
     if (pl.row_mode == 0 || (long long)C * batch > (1ll << 20) || tile_end * batch >= (1ll << 22)) return false;
-    if (ceil_div(batch, 4) > 65535) return false;
-    return (long long)m * q * C * ceil_div(batch, 4) <= kGatherLookups * pl.tiles_per_split;
+    if (ceil_div(batch, 4) > 65535 || (batch > 1 && pl.chunk_splits > kGatherSplits)) return false;
+    const int log_slices = batch > 1 ? gather_log_slices(batch) : 0;
+    return (long long)m * q * C * ceil_div(batch, 4) <= (kGatherLookups * pl.tiles_per_split * (2 + log_slices)) >> 1;
+}
+
+// The same for the plans of query_kernel, whose copies cost 12-25 us and whose lookups cost three times those of the
+// other kernels, and of query_wide_kernel (13-15 us), any mu.  Copied / in place: 163 x 223, 4 planes, 14 vectors, mu = 4 12.5 /
+// 5.2 us; 4080 x 1318, 3, 7, 4 (8.1 million) 27.5 / 12.8; 2783 x 3596, 4, 12, 6 (20.0) 45.6 / 37.9; query_wide:
+// 3596 x 1817, 2, 4, 6 (2.2) 13.6 / 10.8; 1547 x 3857, 4, 2, 5 (4.8) 17.3 / 18.4; 2290 x 3782, 4, 3, 3 (11.6) 23.7 / 22.7;
+// 2902 x 3374, 4, 8, 4 (19.6) 23.8 / 39.5.
+constexpr long long kGatherUnitLookups = 20000000;
+bool gather_units(const biq_plan& pl, int m, int q, int batch, int mu, int C) {
+    if (pl.kernel != KERNEL_GENERIC && pl.kernel != KERNEL_WIDE) return false;
+    const long long tile_end = (long long)ceil_div(C, pl.chunks_per_tile) * pl.chunks_per_tile;
+    if (product((long long)C << mu, batch, 1) > (1ll << 28) || product(tile_end << mu, batch, 1) >= (1ll << 30)) return false;
+    if (ceil_div(batch, 4) > 65535 || pl.chunk_splits > kGatherSplits) return false;
+    return product((long long)m * q, C, ceil_div(batch, 4)) <= (pl.kernel == KERNEL_WIDE ? kGatherLookups : kGatherUnitLookups);
 }
 
 // Kernel parameters of a lookup-table plan.
@@ -899,8 +916,12 @@ biq_status run_query(bool fused, const uint8_t* K, const float* alpha, const flo
         return run_unpack_mfma(pl, K, alpha, X, Y, m, n, q, batch, workspace, s);
     if (pl.table_fill == 2) return run_direct(geom, K, alpha, X, Y, m, n, q, batch, s);
 
+    // (given tables, several input vectors or other than mu = 8: read in place, splits added in the same dispatch)
+    const int C = ceil_div(n, mu);
+    const bool units = !fused && gather_units(pl, m, q, batch, mu, C);
+    const bool gather = !fused && batch > 1 && gather_tables(pl, m, q, batch, C);
     QueryParams qp{};
-    fill_query_params(qp, pl, K, alpha, X, LUT, pl.chunk_splits > 1 ? reinterpret_cast<float*>(workspace) : Y, m, n, q,
+    fill_query_params(qp, pl, K, alpha, X, LUT, pl.chunk_splits > 1 && !units && !gather ? reinterpret_cast<float*>(workspace) : Y, m, n, q,
                       batch, mu);
 #ifdef BIQ_TRACE
     if (fused) qp.LUT = reinterpret_cast<const float*>(workspace);  // time stamps of a trace build go here
@@ -908,7 +929,8 @@ biq_status run_query(bool fused, const uint8_t* K, const float* alpha, const flo
     const int grid = qp.tasks_per_xcd * kNumXcd;
 
     hipError_t e;
-    if (!fused && batch > 1 && gather_tables(pl, m, q, batch, qp.C)) e = launch_gather(pl.kernel == KERNEL_GEMM8X2H, q, qp, s);
+    if (units) e = launch_gather_units(mu, qp, pl.kernel == KERNEL_WIDE, s);
+    else if (gather) e = launch_gather(pl.kernel == KERNEL_GEMM8X2H, q, qp, s);
     else if (pl.kernel == KERNEL_GEMV8) e = launch_gemv8(fused, q, qp, grid, pl.threads, pl.lds_bytes, s);
     else if (pl.kernel == KERNEL_GEMV8H) e = launch_gemv8h(fused, q, qp, grid, pl.threads, pl.lds_bytes, s);
     else if (pl.kernel == KERNEL_WIDE) e = launch_wide(fused, mu, qp, grid, pl.threads, pl.lds_bytes, s);
@@ -916,7 +938,7 @@ biq_status run_query(bool fused, const uint8_t* K, const float* alpha, const flo
     else if (pl.kernel == KERNEL_GEMM8X2) e = launch_gemm8x2(fused, q, qp, grid, pl.threads, pl.lds_bytes, s);
     else e = launch_query_generic(fused, mu, pl.batch_tile, qp, grid, pl.threads, pl.lds_bytes, s);
     if (e != hipSuccess) return BIQ_EHIP;
-    if (pl.chunk_splits > 1) {
+    if (pl.chunk_splits > 1 && !units && !gather) {
         const long long count = (long long)batch * m;
         if (launch_reduce_splits(reinterpret_cast<const float*>(workspace), Y, count, pl.chunk_splits, s) !=
             hipSuccess)

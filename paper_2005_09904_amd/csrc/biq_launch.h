@@ -57,6 +57,8 @@ hipError_t launch_gemm8x2h(bool fused, int q, const QueryParams& p, int grid, in
 
 // few lookups into given tables (mu = 8, several input vectors; half: in the order of gemm8x2_half)
 hipError_t launch_gather(bool half, int q, const QueryParams& p, hipStream_t s);
+// ... for the plans of the generic kernel and (ascending) query_wide, any mu
+hipError_t launch_gather_units(int mu, const QueryParams& p, bool ascending, hipStream_t s);
 
 // ---- fused LSTM cell step (half-table kernels with the cell update as epilogue) ----
 hipError_t launch_lstm8h(int q, const QueryParams& p, int grid, int threads, int lds, hipStream_t s);
