@@ -21,10 +21,11 @@ hipError_t launch_reduce_splits(const float* partial, float* Y, long long count,
 hipError_t launch_pack(const int8_t* B, uint32_t* K, long long key_rows, int n, int stride_dw, hipStream_t s) {
     const long long total = key_rows * stride_dw;
     const unsigned grid = (unsigned)((total + 255) / 256);
-    if (n % 16 == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0)
-        hipLaunchKernelGGL(pack_kernel<true>, dim3(grid), dim3(256), 0, s, B, K, key_rows, n, stride_dw);
+    if (total < (1ll << 31) && key_rows * n < (1ll << 32))
+        hipLaunchKernelGGL(pack_kernel<uint32_t>, dim3(grid), dim3(256), 0, s, B, K, (uint32_t)key_rows, n, stride_dw);
     else
-        hipLaunchKernelGGL(pack_kernel<false>, dim3(grid), dim3(256), 0, s, B, K, key_rows, n, stride_dw);
+        hipLaunchKernelGGL(pack_kernel<unsigned long long>, dim3(grid), dim3(256), 0, s, B, K, (unsigned long long)key_rows, n,
+                           stride_dw);
     return hipGetLastError();
 }
 
