@@ -28,6 +28,7 @@ namespace biq {
 
 constexpr int kQuantThreads = 256;
 constexpr int kQuantMaxN = 32768;
+constexpr int kQuantWaveN = 8192;     // longest row of one wave
 
 // Lane i gets lane i ^ 1's / i ^ 2's / i ^ 4's value.
 __device__ __forceinline__ uint32_t quant_xor1(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true); }
@@ -37,15 +38,18 @@ __device__ __forceinline__ uint32_t quant_xor4(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x1B, 0xf, 0xf, true);                 // quad_perm [3,2,1,0]: i ^ 3
 }
 
-// WPR waves per row (1: four rows per workgroup; 4: one row per workgroup), EPT elements per lane:
-// n <= 64 * EPT * WPR.  Lane l of wave w (of the row's WPR waves) holds elements
-// (t * WPR + w) * 256 + 4 l + c, t = 0 .. EPT / 4 - 1, c = 0 .. 3.  FULL: n = 64 * EPT * WPR, no element to mask.
-template <int EPT, int WPR, bool FULL>
+// WPR waves per row (1: four rows per workgroup; 4: one row per workgroup), NT pieces of 256 elements per wave:
+// n <= 256 * NT * WPR.  Lane l of wave w (of the row's WPR waves) holds elements
+// (t * WPR + w) * 256 + 4 l + c, t = 0 .. NT - 1, c = 0 .. 3.  TAIL: the pieces of a wave, the last ones, that may hold
+// fewer than 256 (0: n = 256 * NT * WPR); only their residuals are masked, two of six instructions per element and plane.
+// An instance for nearly every NT: a row of few pieces more than a power of two does not pay for twice as many (777 x 4560, 4 planes,
+// before with 32 pieces: 10.2 -> 6.5 us; 2629 x 4681, 4 23.3 -> 15.0; 7182 x 558, 4 8.4 -> 6.5; 4096^2 as before).
+template <int NT, int WPR, int TAIL>
 __global__ __launch_bounds__(kQuantThreads) void quantize_wave_kernel(const float* __restrict__ W,
                                                                       uint32_t* __restrict__ K,
                                                                       float* __restrict__ alpha, int m,
                                                                       int n, int q, int stride_dw) {
-    constexpr int NT = EPT / 4, NG = (NT + 7) / 8;   // 16-byte pieces of a lane; groups of up to 8 = 32 sign bits
+    constexpr int NG = (NT + 7) / 8;   // groups of up to 8 pieces = 32 sign bits
     __shared__ float wave_sums[2][4];   // WPR = 4: the waves' partial sums, double buffered over the planes
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (the row's buffer lies in scalar registers)
@@ -127,9 +131,9 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_wave_kernel(const floa
 #pragma unroll
         for (int c = 0; c < 4; ++c) s4[c] = 0.0f;
         uint32_t valid[NG];
-        if constexpr (!FULL) {
+        if constexpr (TAIL > 0) {
 #pragma unroll
-            for (int g = 0; g < NG; ++g) {
+            for (int g = (NT - TAIL) / 8; g < NG; ++g) {
                 valid[g] = there[g];
                 // (kept from being turned into one condition per element in scalar registers, outside the loop)
                 asm volatile("" : "+v"(valid[g]));
@@ -141,7 +145,7 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_wave_kernel(const floa
             for (int c = 0; c < 4; ++c) {
                 const uint32_t b = __float_as_uint(r[t][c]);
                 float x = r[t][c] - __uint_as_float((b & 0x80000000u) | (__float_as_uint(a) & 0x7fffffffu));
-                if constexpr (!FULL)    // all ones or zero from the element's bit
+                if (t >= NT - TAIL)     // all ones or zero from the element's bit
                     x = __uint_as_float(__float_as_uint(x) &
                                         (uint32_t)__builtin_amdgcn_sbfe((int)valid[t >> 3], 4 * (t & 7) + c, 1));
                 r[t][c] = x;
