@@ -1,4 +1,7 @@
-"""ctypes binding of libbiq.so: same names as include/biq.h, argument marshalling only.
+"""Binding of libbiq.so: same names as include/biq.h, argument marshalling only.
+
+Sizes, plans and set-up go through ctypes; the operations through csrc/py_calls.cpp, since what ctypes takes
+for a dozen arguments (1.2-2 us) shows beside a launch (2.5 us).
 
 Tensors are torch tensors used purely as device memory; every step of the path runs in the
 library's HIP kernels.  There is no fallback: if the library is missing, loading raises.
@@ -51,11 +54,12 @@ class BiqError(RuntimeError):
 
 
 _lib = None
+_calls = None   # csrc/py_calls.cpp on the functions of _lib
 
 
 def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     """Loads libbiq.so (built in-tree by paper_2005_09904_amd.build). Raises if it is missing."""
-    global _lib
+    global _lib, _calls
     if _lib is not None and path is None:
         return _lib
     path = path or LIB_PATH
@@ -98,8 +102,25 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
         fn = getattr(lib, name)
         fn.restype = res
         fn.argtypes = args
+    from ._calls import Calls
+
+    _calls = Calls({name: ctypes.cast(getattr(lib, name), P).value for name in sig}, _check, _as_int, _current_stream)
     _lib = lib
     return lib
+
+
+def _native():
+    load_library()
+    return _calls
+
+
+def _as_int(value) -> int:
+    """What ctypes takes for an int besides Python's own."""
+    try:
+        value = getattr(value, "_as_parameter_", value)
+        return ctypes.c_int(getattr(value, "value", value) if isinstance(value, ctypes.c_int) else value).value
+    except TypeError as e:
+        raise ctypes.ArgumentError(str(e)) from None
 
 
 def status_str(status: int) -> str:
@@ -115,21 +136,25 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
-_raw_stream = None
+_raw_stream = _device = None
+
+
+def _current_stream() -> Optional[int]:
+    """hipStream_t of torch's current stream.  It is asked for as a number: making the Stream object first takes
+    2.9 us, more than a launch."""
+    global _raw_stream, _device
+    if _device is None:
+        import torch
+
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda device: torch.cuda.current_stream(device).cuda_stream)
+        _device = torch.cuda.current_device
+    return _raw_stream(_device())
 
 
 def _stream(stream) -> Optional[int]:
-    """hipStream_t of a torch stream (default: torch's current stream).  The current one is asked for as a
-    number: making the Stream object first takes 2.9 us, most of what a call costs on the host."""
-    global _raw_stream
-    if stream is not None:
-        return stream.cuda_stream or None
-    if _raw_stream is None:
-        import torch
-
-        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), torch.cuda.current_device
-        _raw_stream = (lambda: raw(device())) if raw else (lambda: torch.cuda.current_stream().cuda_stream)
-    return _raw_stream() or None
+    """hipStream_t of a torch stream (default: torch's current stream)."""
+    return (_current_stream() if stream is None else stream.cuda_stream) or None
 
 
 def _nbytes(t) -> int:
@@ -193,7 +218,7 @@ def biq_kernel_name(kernel: int) -> str:
 # ---- operations (device tensors in, device tensors out) ----------------------------------
 
 def biq_pack(B, K, m: int, n: int, q: int, mu: int, stream=None) -> None:
-    _check(load_library().biq_pack(_ptr(B), _ptr(K), m, n, q, mu, _stream(stream)), "biq_pack")
+    (_calls or _native()).pack(B, K, m, n, q, mu, stream)
 
 
 def biq_unpack_keys16(K, keys, m: int, n: int, q: int, mu: int, stream=None) -> None:
@@ -202,8 +227,7 @@ def biq_unpack_keys16(K, keys, m: int, n: int, q: int, mu: int, stream=None) -> 
 
 
 def biq_quantize(W, K, alpha, m: int, n: int, q: int, stream=None) -> None:
-    _check(load_library().biq_quantize(_ptr(W), _ptr(K), _ptr(alpha), m, n, q, _stream(stream)),
-           "biq_quantize")
+    (_calls or _native()).quantize(W, K, alpha, m, n, q, stream)
 
 
 def biq_unpack_keys(K, keys, m: int, n: int, q: int, mu: int, stream=None) -> None:
@@ -212,20 +236,17 @@ def biq_unpack_keys(K, keys, m: int, n: int, q: int, mu: int, stream=None) -> No
 
 
 def biq_build_lut(X, LUT, n: int, batch: int, mu: int, stream=None) -> None:
-    _check(load_library().biq_build_lut(_ptr(X), _ptr(LUT), n, batch, mu, _stream(stream)),
-           "biq_build_lut")
+    (_calls or _native()).build_lut(X, LUT, n, batch, mu, stream)
 
 
 def biq_query(K, alpha, LUT, Y, m: int, n: int, q: int, batch: int, mu: int, workspace=None,
               stream=None) -> None:
-    _check(load_library().biq_query(_ptr(K), _ptr(alpha), _ptr(LUT), _ptr(Y), m, n, q, batch, mu,
-                                    _ptr(workspace), _nbytes(workspace), _stream(stream)), "biq_query")
+    (_calls or _native()).query(K, alpha, LUT, Y, m, n, q, batch, mu, workspace, stream)
 
 
 def biq_gemm(K, alpha, X, Y, m: int, n: int, q: int, batch: int, mu: int, workspace=None,
              stream=None) -> None:
-    _check(load_library().biq_gemm(_ptr(K), _ptr(alpha), _ptr(X), _ptr(Y), m, n, q, batch, mu,
-                                   _ptr(workspace), _nbytes(workspace), _stream(stream)), "biq_gemm")
+    (_calls or _native()).gemm(K, alpha, X, Y, m, n, q, batch, mu, workspace, stream)
 
 
 def biq_init() -> None:
@@ -237,8 +258,7 @@ def biq_noalloc_scratch_bytes() -> int:
 
 
 def biq_gemm_noalloc(K, alpha, X, Y, m: int, n: int, q: int, batch: int, mu: int, stream=None) -> None:
-    _check(load_library().biq_gemm_noalloc(_ptr(K), _ptr(alpha), _ptr(X), _ptr(Y), m, n, q, batch, mu,
-                                           _stream(stream)), "biq_gemm_noalloc")
+    (_calls or _native()).gemm_noalloc(K, alpha, X, Y, m, n, q, batch, mu, stream)
 
 
 class PreparedGroup:
@@ -251,13 +271,10 @@ class PreparedGroup:
         for d, (K, alpha, X, Y, m, n, q, batch) in zip(self._array, problems):
             d.K, d.alpha, d.X, d.Y = _ptr(K), _ptr(alpha), _ptr(X), _ptr(Y)
             d.m, d.n, d.q, d.batch = m, n, q, batch
-        self._args = (self._array, len(problems), mu, _stream(stream))
-        self._fn = load_library().biq_gemm_grouped
+        self._call = _native().prepare_grouped(ctypes.addressof(self._array), len(problems), mu, stream)
 
     def __call__(self) -> None:
-        status = self._fn(*self._args)
-        if status != BIQ_OK:
-            raise BiqError(status, "biq_gemm_grouped")
+        self._call()
 
 
 def biq_gemm_grouped(problems, mu: int, stream=None) -> None:
@@ -266,8 +283,7 @@ def biq_gemm_grouped(problems, mu: int, stream=None) -> None:
 
 def biq_lstm_cell(K, alpha, bias, X, C_prev, H_out, C_out, hidden: int, n: int, q: int, batch: int, mu: int,
                   stream=None) -> None:
-    _check(load_library().biq_lstm_cell(_ptr(K), _ptr(alpha), _ptr(bias), _ptr(X), _ptr(C_prev), _ptr(H_out),
-                                        _ptr(C_out), hidden, n, q, batch, mu, _stream(stream)), "biq_lstm_cell")
+    (_calls or _native()).lstm_cell(K, alpha, bias, X, C_prev, H_out, C_out, hidden, n, q, batch, mu, stream)
 
 
 class PreparedLstmCell:
@@ -275,14 +291,10 @@ class PreparedLstmCell:
 
     def __init__(self, K, alpha, bias, X, C_prev, H_out, C_out, hidden, n, q, batch, mu, stream=None):
         self._keep = (K, alpha, bias, X, C_prev, H_out, C_out)
-        self._fn = load_library().biq_lstm_cell
-        self._args = (_ptr(K), _ptr(alpha), _ptr(bias), _ptr(X), _ptr(C_prev), _ptr(H_out), _ptr(C_out), hidden, n, q,
-                      batch, mu, _stream(stream))
+        self._call = _native().prepare_lstm_cell(K, alpha, bias, X, C_prev, H_out, C_out, hidden, n, q, batch, mu, stream)
 
     def __call__(self) -> None:
-        status = self._fn(*self._args)
-        if status != BIQ_OK:
-            raise BiqError(status, "biq_lstm_cell")
+        self._call()
 
 
 class PreparedGemm:
@@ -291,21 +303,17 @@ class PreparedGemm:
     The stream is the one given here, or torch's current stream at preparation time."""
 
     def __init__(self, K, alpha, X, Y, m, n, q, batch, mu, workspace=None, stream=None, plan=None):
-        lib = load_library()
         self._keep = (K, alpha, X, Y, workspace, plan)
-        ws_ptr, ws_bytes, st = _ptr(workspace), _nbytes(workspace), _stream(stream)
         if plan is None:
-            self._fn = lib.biq_gemm
-            self._args = (_ptr(K), _ptr(alpha), _ptr(X), _ptr(Y), m, n, q, batch, mu, ws_ptr, ws_bytes, st)
+            self._call = _native().prepare_gemm(K, alpha, X, Y, m, n, q, batch, mu, workspace, stream)
         else:
-            self._fn = lib.biq_gemm_ex
-            self._args = (_ptr(K), _ptr(alpha), _ptr(X), _ptr(Y), m, n, q, batch, mu, ctypes.byref(plan),
-                          ws_ptr, ws_bytes, st)
+            fn, args = load_library().biq_gemm_ex, (
+                _ptr(K), _ptr(alpha), _ptr(X), _ptr(Y), m, n, q, batch, mu, ctypes.byref(plan), _ptr(workspace),
+                _nbytes(workspace), _stream(stream))
+            self._call = lambda: _check(fn(*args), "biq_gemm")
 
     def __call__(self) -> None:
-        status = self._fn(*self._args)
-        if status != BIQ_OK:
-            raise BiqError(status, "biq_gemm")
+        self._call()
 
 
 def biq_gemm_ex(K, alpha, X, Y, m: int, n: int, q: int, batch: int, mu: int, plan: BiqPlan,

@@ -1,4 +1,5 @@
-"""Builds libbiq.so (the HIP kernels and their C ABI) for gfx950 with hipcc, in-tree.
+"""Builds libbiq.so (the HIP kernels and their C ABI) for gfx950 with hipcc, and _calls.so (the calls from
+Python into it, host code), in-tree.
 
 One translation unit per kernel family (csrc/*.hip), compiled side by side and linked into one
 shared library; objects go to paper_2005_09904_amd/_build/ (not tracked)."""
@@ -8,6 +9,7 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
@@ -15,6 +17,8 @@ ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 OBJ_DIR = os.path.join(PKG_DIR, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libbiq.so")
+CALLS_PATH = os.path.join(PKG_DIR, "_calls.so")
+CALLS_SOURCE = os.path.join(CSRC, "py_calls.cpp")
 SOURCES = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 HEADERS = sorted(glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(CSRC, "*.inc"))) + [
     os.path.join(ROOT, "include", "biq.h")]
@@ -30,10 +34,10 @@ HIPCC_FLAGS = [
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB_PATH):
+    if not os.path.exists(LIB_PATH) or not os.path.exists(CALLS_PATH):
         return True
-    built = os.path.getmtime(LIB_PATH)
-    return any(os.path.getmtime(p) > built for p in SOURCES + HEADERS)
+    built = min(os.path.getmtime(LIB_PATH), os.path.getmtime(CALLS_PATH))
+    return any(os.path.getmtime(p) > built for p in SOURCES + HEADERS + [CALLS_SOURCE])
 
 
 def _run(cmd, verbose):
@@ -63,6 +67,10 @@ def build_library(verbose: bool = False, jobs: int | None = None) -> str:
         tmp = LIB_PATH + ".tmp" + tag
         _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", tmp], verbose)
         os.replace(tmp, LIB_PATH)
+        tmp = CALLS_PATH + ".tmp" + tag
+        _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+              inc[0], "-I" + sysconfig.get_paths()["include"], CALLS_SOURCE, "-o", tmp], verbose)
+        os.replace(tmp, CALLS_PATH)
     finally:
         for o in objs:
             if os.path.exists(o):
