@@ -21,7 +21,7 @@
 // Relative 2-norm error against fp64, normal inputs, three bf16 terms -> digits: 16384 x 4096, 2
 // planes, 128 vectors 4.2e-7 -> 5.8e-8; 4096 x 16384 5.9e-7 -> 6.6e-8; 4096^2, 3 planes, 32 vectors
 // 2.2e-7 -> 7.4e-8 (the table kernels: 1.1e-7).
-// Time, same order (us per call): 77 -> 46; 86 -> 51; 17.2 -> 14.1.  Bound by the power the matrix
+// Time, same order (us per call): 77 -> 43-46; 86 -> 50; 17.2 -> 13.3-13.9.  Bound by the power the matrix
 // cores may draw: the instruction issues at 33 clk, but in a loop of nothing else the clock falls to
 // 1.3-1.5 GHz, 5.1-5.8 PFLOP/s (bf16: 1.3-1.7 PFLOP/s), so fewer and cheaper instructions are what helps.
 // The whole range of fp32 is covered: a block's scale byte stands for its exponent alone, and what the
@@ -32,7 +32,7 @@
 //
 // Inputs that hold bf16 values (all elements of a key group - 256 - of all vectors of a column
 // group) keep the one-term bf16 form: 16 elements per instruction, but one term instead of five digits
-// (16384 x 4096, 2 planes, 128 vectors 35.7 us, 4096 x 16384 38.0; there the 8 instructions that expand a row tile's
+// (16384 x 4096, 2 planes, 128 vectors 33 us, 4096 x 16384 36-39; there the 8 instructions that expand a row tile's
 // weights bound the loop as much as its matrix instructions do).  Values of fp16 take all five digits.
 // The form is chosen per (column group, key group) by the kernel that prepares the operands; the
 // main kernel walks first the key groups of one form, then those of the other.
@@ -113,64 +113,72 @@ __device__ __forceinline__ uint32_t digit_split(const float (&x)[32], Emit&& emi
     return finite ? (uint32_t)(ex - 1) : 255u;
 }
 
-// One workgroup per (column group, key group): 32 * CT input vectors x 256 elements go through LDS
-// (read along the vectors in whole KiB); thread = one block of 32 elements = one lane of one step's
-// B operand.  Bound by latency (one load, ~350 instructions, one store), not by its 8.5 bytes per
-// element.  Vectors past the batch and elements past n are zero.
+// One workgroup per (column tile, key group): 32 input vectors x 256 elements go through LDS (read along
+// the vectors in whole KiB); thread = one block of 32 elements = one lane of one step's B operand.  Bound by
+// latency (one load, ~350 instructions, one store), not by its 8.5 bytes per element.  Vectors past the
+// batch and elements past n are zero.  The form holds for a column group: where that is two tiles, each
+// workgroup looks at the other tile's elements too rather than being twice as large, with two waves on a
+// SIMD (16384 x 4096, 2 planes, 128 vectors: the whole call 47.1 -> 46.3 us).
 constexpr int kXdigitsPitch = 260;       // floats per vector in LDS: 16-byte rows, spread over the banks
 template <int CT>
-__global__ __launch_bounds__(256 * CT) void xdigits_kernel(const float* __restrict__ X, uint8_t* __restrict__ Xd,
-                                                           int* __restrict__ form, int n, int batch, int groups) {
-    extern __shared__ __align__(16) float xs[];      // [32 * CT][kXdigitsPitch], then the waves' votes
-    const int g = (int)blockIdx.x % groups, cg = (int)blockIdx.x / groups;
+__global__ __launch_bounds__(256) void xdigits_kernel(const float* __restrict__ X, uint8_t* __restrict__ Xd,
+                                                      int* __restrict__ form, int n, int batch, int groups) {
+    __shared__ __align__(16) float xs[32 * kXdigitsPitch];
+    __shared__ uint32_t votes[4];                    // one per wave
+    const int g = (int)blockIdx.x % groups, tile = (int)blockIdx.x / groups;
+    const int cg = tile / CT, c = tile % CT;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     {
         // wave w reads vectors 8w .. 8w + 7, all requests in flight together
-        const int col0 = cg * CT * 32 + wave * 8;
         // (a buffer per vector: elements past n, and all of a vector past the batch, read as 0.  Reads behind
         // conditions were waited for one by one: odd n 5.1 -> 3.5 us)
-        typedef float f32x4b __attribute__((ext_vector_type(4)));
-        f32x4b v[8];
+        mfma_u32x4 v[8], u[8] = {};
+        auto load = [&](int t, mfma_u32x4 (&to)[8]) {
+            const int col0 = t * 32 + wave * 8;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int col = min(col0 + i, batch - 1);
+                const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<float*>(X + (size_t)col * n), 0, col0 + i < batch ? n * 4 : 0, 0x00020000);
+                to[i] = __builtin_bit_cast(mfma_u32x4, __builtin_amdgcn_raw_buffer_load_b128(src, 1024 * g + 16 * lane, 0, 0));
+            }
+        };
+        load(tile, v);
+        if constexpr (CT == 2) load(tile ^ 1, u);
+        uint32_t low = 0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int col = min(col0 + i, batch - 1);
-            const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<float*>(X + (size_t)col * n), 0, col0 + i < batch ? n * 4 : 0, 0x00020000);
-            v[i] = __builtin_bit_cast(f32x4b, __builtin_amdgcn_raw_buffer_load_b128(src, 1024 * g + 16 * lane, 0, 0));
+            *reinterpret_cast<mfma_u32x4*>(xs + (wave * 8 + i) * kXdigitsPitch + 4 * lane) = v[i];
+            low |= v[i].x | v[i].y | v[i].z | v[i].w;
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            *reinterpret_cast<f32x4b*>(xs + (wave * 8 + i) * kXdigitsPitch + 4 * lane) = v[i];
+        for (int i = 0; i < 8; ++i) low |= u[i].x | u[i].y | u[i].z | u[i].w;
+        bool wave_bf16 = __builtin_amdgcn_ballot_w64((low & 0xffffu) != 0u) == 0ull;
+        if (wave_bf16) {                             // ... unless there is Inf or NaN
+            uint32_t mb = 0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) mb = max(mb, max(v[i][k] & 0x7fffffffu, u[i][k] & 0x7fffffffu));
+            wave_bf16 = __builtin_amdgcn_ballot_w64(mb >= 0x7f800000u) == 0ull;
+        }
+        if (lane == 0) votes[wave] = wave_bf16;
     }
     __syncthreads();
-    const int c = wave >> 2, s = wave & 3;           // column tile, step within the key group
+    const int s = wave;                              // step within the key group
     const int h = lane >> 5, r = lane & 31;
     float x[32];
-    uint32_t mb = 0, low = 0;
     {
-        const float* src = xs + (c * 32 + r) * kXdigitsPitch + 32 * (4 * h + s);
+        const float* src = xs + r * kXdigitsPitch + 32 * (4 * h + s);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const float4 v = *reinterpret_cast<const float4*>(src + 4 * i);
             x[4 * i] = v.x; x[4 * i + 1] = v.y; x[4 * i + 2] = v.z; x[4 * i + 3] = v.w;
         }
-#pragma unroll
-        for (int i = 0; i < 32; ++i) {
-            const uint32_t b = __float_as_uint(x[i]);
-            mb = max(mb, b & 0x7fffffffu);
-            low |= b;
-        }
     }
-    const bool finite = mb < 0x7f800000u;
-    uint32_t* const votes = reinterpret_cast<uint32_t*>(xs + 32 * CT * kXdigitsPitch);   // one per wave
-    const bool wave_bf16 = __builtin_amdgcn_ballot_w64(!finite || (low & 0xffffu) != 0u) == 0ull;
-    if (lane == 0) votes[wave] = wave_bf16;
-    __syncthreads();
-    bool all_bf16 = true;
-#pragma unroll
-    for (int w = 0; w < 4 * CT; ++w) all_bf16 = all_bf16 && votes[w] != 0u;
+    const bool all_bf16 = votes[0] && votes[1] && votes[2] && votes[3];
     uint8_t* const area = Xd + ((size_t)(cg * groups + g) * CT + c) * kDigitGroupBytes;
-    if (tid == 0) form[cg * groups + g] = all_bf16 ? kFormBf16 : kFormDigits;
+    if (tid == 0 && c == 0) form[cg * groups + g] = all_bf16 ? kFormBf16 : kFormDigits;
     if (all_bf16) {
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
@@ -520,7 +528,11 @@ __global__ __launch_bounds__(kUnpackThreads, 1) void digit_mfma_kernel(const Dig
             const int row = rbase + rp * 32 + pr;
             if (col < p.batch && row < p.m) {
                 float* dst = p.out + ((size_t)sp * p.batch + col) * p.m + row;
-                if (vec_ok) {
+                if (vec_ok && p.splits == 1) {
+                    // (written through: 8 MB left in the L2s for the end of the kernel took 0.5-1 us more)
+                    typedef float f32x4o __attribute__((ext_vector_type(4)));
+                    __builtin_nontemporal_store(f32x4o{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4o*>(dst));
+                } else if (vec_ok) {
                     *reinterpret_cast<float4*>(dst) = v;
                 } else {
                     dst[0] = v.x;

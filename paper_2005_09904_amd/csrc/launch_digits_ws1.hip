@@ -9,16 +9,9 @@ hipError_t launch_digits_ws1(int q, int rpw, int ct, const DigitParams& p, int g
 
 hipError_t launch_xdigits(int ct, const float* X, uint8_t* Xd, int* form, int n, int batch, int groups, int col_groups,
                           hipStream_t s) {
-    const int lds = (32 * ct * kXdigitsPitch + 4 * ct) * (int)sizeof(float);
-    const int grid = groups * col_groups;
-    if (ct == 2) {
-        static unsigned long long granted = 0;
-        if (hipError_t e = grant_large_lds(reinterpret_cast<const void*>(xdigits_kernel<2>), granted, false); e != hipSuccess)
-            return e;
-        hipLaunchKernelGGL(xdigits_kernel<2>, dim3(grid), dim3(512), lds, s, X, Xd, form, n, batch, groups);
-    } else {
-        hipLaunchKernelGGL(xdigits_kernel<1>, dim3(grid), dim3(256), lds, s, X, Xd, form, n, batch, groups);
-    }
+    const dim3 grid(groups * col_groups * ct);
+    if (ct == 2) hipLaunchKernelGGL(xdigits_kernel<2>, grid, dim3(256), 0, s, X, Xd, form, n, batch, groups);
+    else hipLaunchKernelGGL(xdigits_kernel<1>, grid, dim3(256), 0, s, X, Xd, form, n, batch, groups);
     return hipGetLastError();
 }
 

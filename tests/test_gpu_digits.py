@@ -211,3 +211,30 @@ def test_digits_one_key_group_in_the_other_form(biq, oracle, m, n, q, b, bt, gps
         Bd, ad, Zd = device_inputs(B, alpha, Z)
         Y = gpu_gemm(biq, gpu_pack(biq, Bd), ad, Zd, m, n, q, 8, plan=_plan(biq, q, bt, gps, ws, r)).cpu().numpy()
         assert np.all(np.abs(Y - oracle.gemm_dense(B, alpha, Z)).max(axis=1) <= _bound(alpha, Z))
+
+
+@pytest.mark.parametrize("b", [64, 37])
+@pytest.mark.parametrize("where", ["first tile", "second tile", "NaN in the second"])
+def test_digits_form_of_both_column_tiles(biq, oracle, b, where):
+    """The two column tiles of a column group are prepared by different workgroups, which have to agree on its form:
+    bf16 values but for one tile's last vector, or a NaN there."""
+    import torch
+
+    print("digits, column tiles", b, where, flush=True)
+    m, n, q = 70, 601, 2
+    B, alpha, X = _inputs(m, n, q, b, 43000 + b)
+    full = X
+    X = torch.from_numpy(X).bfloat16().float().numpy()
+    v = 31 if where == "first tile" else b - 1
+    if "NaN" not in where:
+        X[v, 300:] = full[v, 300:]                       # the second and third key group
+    Z = X.copy()
+    if "NaN" in where:
+        Z[v, n - 1] = np.nan
+    Bd, ad, Zd = device_inputs(B, alpha, Z)
+    Y = gpu_gemm(biq, gpu_pack(biq, Bd), ad, Zd, m, n, q, 8, plan=_plan(biq, q, 64, 3, 1, 2)).cpu().numpy()
+    good = np.abs(Y - oracle.gemm_dense(B, alpha, X)).max(axis=1) <= _bound(alpha, X)
+    if "NaN" in where:
+        assert np.isnan(Y[v]).all() and good[np.arange(b) != v].all()
+    else:
+        assert good.all()
