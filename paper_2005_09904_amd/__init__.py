@@ -1,7 +1,7 @@
 """BiQGEMM lookup-table matrix multiply for AMD MI355X (gfx950).
 
 The product is libbiq.so (HIP kernels behind the C ABI of include/biq.h); this package is the
-thin ctypes binding plus the synthetic workload generator.
+thin binding plus the synthetic workload generator.
 """
 from .binding import (  # noqa: F401
     BIQ_EHIP, BIQ_EINVAL, BIQ_EUNSUPPORTED, BIQ_EWORKSPACE, BIQ_OK, BiqError, BiqPlan, BiqProblem, PreparedGemm, PreparedGroup, PreparedLstmCell, biq_gemm_grouped, biq_lstm_cell,
