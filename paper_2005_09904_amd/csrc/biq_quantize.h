@@ -24,11 +24,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "biq_quantize_shape.h"
+
 namespace biq {
 
 constexpr int kQuantThreads = 256;
-constexpr int kQuantMaxN = 32768;
-constexpr int kQuantWaveN = 8192;     // longest row of one wave
 
 // Lane i gets lane i ^ 1's / i ^ 2's / i ^ 4's value.
 __device__ __forceinline__ uint32_t quant_xor1(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true); }
@@ -41,7 +41,7 @@ __device__ __forceinline__ uint32_t quant_xor4(uint32_t v) {
 // WPR waves per row (1: four rows per workgroup; 4: one row per workgroup), NT pieces of 256 elements per wave:
 // n <= 256 * NT * WPR.  Lane l of wave w (of the row's WPR waves) holds elements
 // (t * WPR + w) * 256 + 4 l + c, t = 0 .. NT - 1, c = 0 .. 3.  TAIL: the pieces of a wave, the last ones, that may hold
-// fewer than 256 (0: n = 256 * NT * WPR); only their residuals are masked, two of six instructions per element and plane.
+// fewer than 256 or lie past the row (0: n = 256 * NT * WPR); only their residuals are masked, two of six instructions per element and plane.
 // An instance for nearly every NT: a row of few pieces more than a power of two does not pay for twice as many (777 x 4560, 4 planes,
 // before with 32 pieces: 10.2 -> 6.5 us; 2629 x 4681, 4 23.3 -> 15.0; 7182 x 558, 4 8.4 -> 6.5; 4096^2 as before).
 template <int NT, int WPR, int TAIL>

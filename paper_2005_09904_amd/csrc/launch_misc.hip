@@ -94,22 +94,21 @@ hipError_t launch_build_lut(int mu, const float* X, float* LUT, int n, int batch
 hipError_t launch_quantize(const float* W, uint32_t* K, float* alpha, int m, int n, int q, int stride_dw,
                            hipStream_t s) {
     if (n > kQuantMaxN) return hipErrorInvalidValue;
-    // 256-element pieces per wave: every count up to 16, even ones beyond (the last two pieces may then be partial)
-    const int wpr = n <= kQuantWaveN ? 1 : 4, pieces = ((n + 255) / 256 + wpr - 1) / wpr;
-    const dim3 grid((m + (4 / wpr) - 1) / (4 / wpr));
-    const bool full = n == pieces * wpr * 256;
+    // 256-element pieces per wave: every count up to 16, even ones beyond (quant_shape)
+    const QuantShape g = quant_shape(n);
+    const dim3 grid((m + (4 / g.waves) - 1) / (4 / g.waves));
 #define BIQ_QUANT_INST(NT, WPR, TAIL) \
     hipLaunchKernelGGL((quantize_wave_kernel<NT, WPR, TAIL>), grid, dim3(kQuantThreads), 0, s, W, K, alpha, m, n, q, stride_dw)
-#define BIQ_QUANT_CASE(NT)                                             \
-    case NT:                                                           \
-        if (wpr == 1 && full) BIQ_QUANT_INST(NT, 1, 0);                \
-        else if (wpr == 1) BIQ_QUANT_INST(NT, 1, (NT > 16 ? 2 : 1));   \
-        else if constexpr (NT > 8) {                                   \
-            if (full) BIQ_QUANT_INST(NT, 4, 0);                        \
-            else BIQ_QUANT_INST(NT, 4, (NT > 16 ? 2 : 1));             \
-        }                                                              \
+#define BIQ_QUANT_CASE(NT)                                                        \
+    case NT:                                                                      \
+        if (g.waves == 1 && g.tail == 0) BIQ_QUANT_INST(NT, 1, 0);                \
+        else if (g.waves == 1) BIQ_QUANT_INST(NT, 1, quant_tail(NT));             \
+        else if constexpr (NT > 8) {                                              \
+            if (g.tail == 0) BIQ_QUANT_INST(NT, 4, 0);                            \
+            else BIQ_QUANT_INST(NT, 4, quant_tail(NT));                           \
+        }                                                                         \
         break;
-    switch (pieces > 16 ? (pieces + 1) / 2 * 2 : pieces) {
+    switch (g.pieces) {
         BIQ_QUANT_CASE(1) BIQ_QUANT_CASE(2) BIQ_QUANT_CASE(3) BIQ_QUANT_CASE(4) BIQ_QUANT_CASE(5) BIQ_QUANT_CASE(6)
         BIQ_QUANT_CASE(7) BIQ_QUANT_CASE(8) BIQ_QUANT_CASE(9) BIQ_QUANT_CASE(10) BIQ_QUANT_CASE(11) BIQ_QUANT_CASE(12)
         BIQ_QUANT_CASE(13) BIQ_QUANT_CASE(14) BIQ_QUANT_CASE(15) BIQ_QUANT_CASE(16) BIQ_QUANT_CASE(18) BIQ_QUANT_CASE(20)
