@@ -702,7 +702,10 @@ inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_
 // a split row; the reads, counted per four input vectors, 3.7-5 us per million up to 4 vectors, 2.8 up to 8 and 1.8-2.6
 // beyond, where neighbouring lanes share an entry's lines (gather_log_slices).  Copied / in place: 4071 x 1941, 2
 // planes, 5 vectors (4.0 million) 20.1 / 11.0 us; 3345 x 4044, 2, 7 (6.8) 22.3 / 19.6; 2397 x 3767, 4, 7 (9.0) 23.2 / 25.1;
-// 3970 x 2085, 2, 13 (8.3) 40 / 15; one vector, two tiles: 4096 x 4096, 4 planes (8.4) 32.8 / 30.0.
+// 3970 x 2085, 2, 13 (8.3) 40 / 15; one vector, two tiles: 4096 x 4096, 4 planes (8.4) 32.8 / 30.0.  Tables of very long rows lie
+// beyond the L2s, and shared lines save less: more than 64 splits: 64 x 131072, 1, 4 (1.0) 53 / 51; 183 x 90112, 1, 3 (2.1)
+// 62 / 51; 30 x 174080, 3, 8 (3.9) 101 / 79; but up to 4 vectors 66 x 201728, 2, 4 (3.3) 93 / 102; 78 x 97113, 4, 4 (3.8)
+// 66 / 83; and 66 x 120657, 3, 7 (6.0) 72 / 89.
 constexpr long long kGatherLookups = 4200000;
 bool gather_tables(const biq_plan& pl, int m, int q, int batch, int C) {
     if (pl.kernel != KERNEL_GEMV8 && pl.kernel != KERNEL_GEMV8H && pl.kernel != KERNEL_GEMM8X2 &&
@@ -713,9 +716,12 @@ bool gather_tables(const biq_plan& pl, int m, int q, int batch, int C) {
     // 131072 vectors: chunk 32 would be chunk 0 again); slices of 4 vectors are the grid's z, at most 65535
     const long long tile_end = (long long)ceil_div(C, pl.chunks_per_tile) * pl.chunks_per_tile;
     if (pl.row_mode == 0 || (long long)C * batch > (1ll << 20) || tile_end * batch >= (1ll << 22)) return false;
-    if (ceil_div(batch, 4) > 65535 || (batch > 1 && pl.chunk_splits > kGatherSplits)) return false;
+    if (ceil_div(batch, 4) > 65535) return false;
     const int log_slices = batch > 1 ? gather_log_slices(batch) : 0;
-    return (long long)m * q * C * ceil_div(batch, 4) <= (kGatherLookups * pl.tiles_per_split * (2 + log_slices)) >> 1;
+    const long long limit = batch > 1 && pl.chunk_splits > kGatherSplits
+                                ? (log_slices ? kGatherLookups : kGatherLookups * 3 / 4)
+                                : (kGatherLookups * pl.tiles_per_split * (2 + log_slices)) >> 1;
+    return (long long)m * q * C * ceil_div(batch, 4) <= limit;
 }
 
 // The same for the plans of query_kernel, whose copies cost 12-25 us and whose lookups cost three times those of the
@@ -916,12 +922,15 @@ biq_status run_query(bool fused, const uint8_t* K, const float* alpha, const flo
         return run_unpack_mfma(pl, K, alpha, X, Y, m, n, q, batch, workspace, s);
     if (pl.table_fill == 2) return run_direct(geom, K, alpha, X, Y, m, n, q, batch, s);
 
-    // (given tables, several input vectors or other than mu = 8: read in place, splits added in the same dispatch)
+    // (given tables, several input vectors or other than mu = 8: read in place, splits added in the same dispatch where
+    // they don't need the chip's other CUs)
     const int C = ceil_div(n, mu);
     const bool units = !fused && gather_units(pl, m, q, batch, mu, C);
     const bool gather = !fused && batch > 1 && gather_tables(pl, m, q, batch, C);
+    const bool waves = gather && gather_in_waves(pl.kernel == KERNEL_GEMM8X2H ? 8 : 4, m, q, batch, pl.chunk_splits);
+    const bool parts = pl.chunk_splits > 1 && !units && !waves;
     QueryParams qp{};
-    fill_query_params(qp, pl, K, alpha, X, LUT, pl.chunk_splits > 1 && !units && !gather ? reinterpret_cast<float*>(workspace) : Y, m, n, q,
+    fill_query_params(qp, pl, K, alpha, X, LUT, parts ? reinterpret_cast<float*>(workspace) : Y, m, n, q,
                       batch, mu);
 #ifdef BIQ_TRACE
     if (fused) qp.LUT = reinterpret_cast<const float*>(workspace);  // time stamps of a trace build go here
@@ -930,7 +939,7 @@ biq_status run_query(bool fused, const uint8_t* K, const float* alpha, const flo
 
     hipError_t e;
     if (units) e = launch_gather_units(mu, qp, pl.kernel == KERNEL_WIDE, s);
-    else if (gather) e = launch_gather(pl.kernel == KERNEL_GEMM8X2H, q, qp, s);
+    else if (gather) e = launch_gather(pl.kernel == KERNEL_GEMM8X2H, q, qp, waves, s);
     else if (pl.kernel == KERNEL_GEMV8) e = launch_gemv8(fused, q, qp, grid, pl.threads, pl.lds_bytes, s);
     else if (pl.kernel == KERNEL_GEMV8H) e = launch_gemv8h(fused, q, qp, grid, pl.threads, pl.lds_bytes, s);
     else if (pl.kernel == KERNEL_WIDE) e = launch_wide(fused, mu, qp, grid, pl.threads, pl.lds_bytes, s);
@@ -938,7 +947,7 @@ biq_status run_query(bool fused, const uint8_t* K, const float* alpha, const flo
     else if (pl.kernel == KERNEL_GEMM8X2) e = launch_gemm8x2(fused, q, qp, grid, pl.threads, pl.lds_bytes, s);
     else e = launch_query_generic(fused, mu, pl.batch_tile, qp, grid, pl.threads, pl.lds_bytes, s);
     if (e != hipSuccess) return BIQ_EHIP;
-    if (pl.chunk_splits > 1 && !units && !gather) {
+    if (parts) {
         const long long count = (long long)batch * m;
         if (launch_reduce_splits(reinterpret_cast<const float*>(workspace), Y, count, pl.chunk_splits, s) !=
             hipSuccess)

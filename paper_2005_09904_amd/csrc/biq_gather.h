@@ -12,6 +12,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "biq_gather_rule.h"
 #include "biq_kernels.h"
 
 namespace biq {
@@ -53,27 +54,18 @@ __device__ __forceinline__ float lane_xor(float v) {
     else return __shfl_xor(v, OFF, kWave);
 }
 
-constexpr int kGatherVec = 4;      // input vectors of a lane's read
-constexpr int kGatherWaves = 8;    // most waves of a workgroup
-constexpr int kGatherSplits = 64;  // most splits of a row (32 KiB of LDS with 8 lanes per row)
-
-// The slices of up to four vectors an entry is read in, of one lane each: 1, 2 or 4 of them (2^log_slices) on
-// neighbouring lanes, which then share the entry's cache lines (a wave's reads cost the address unit a line each:
-// 1024 x 1024, 2 planes, 8 vectors 3.8 -> 3.1 us on the GPU; 3317 x 480, 2, 15 9.3 -> 5.6), the rest in the grid's y.
-inline int gather_log_slices(int batch) { return batch > 2 * kGatherVec ? 2 : batch > kGatherVec ? 1 : 0; }
-
 // This lane's first vector.  From 4 vectors on every slice is whole: the last one starts earlier and computes some
 // vectors again (fewer vectors: the read goes on into the next entry, what it brings is not stored).
 __device__ __forceinline__ int gather_first_vector(const QueryParams& p, int slice) {
     return max(0, min(slice * kGatherVec, p.batch - kGatherVec));
 }
 
-// The splits of a row go to the waves of a workgroup (wave w: splits w, w + waves, ...), which leave their sums in
+// MULTI: the splits of a row go to the waves of a workgroup (wave w: splits w, w + waves, ...), which leave their sums in
 // LDS, [split][slot of the row and slice][VEC], to be added in the order of reduce_splits_kernel: a dispatch less
 // than the copying kernels need.
 template <bool MULTI, int VEC>
 __device__ __forceinline__ void gather_finish(const QueryParams& p, float* red, int slots, int slot, bool holder, int row,
-                                              int b0, float (&y)[VEC]) {
+                                              int b0, float (&y)[VEC], float* out) {
     if (MULTI) {
         __syncthreads();
         if (threadIdx.x >= 64) return;
@@ -86,12 +78,13 @@ __device__ __forceinline__ void gather_finish(const QueryParams& p, float* red, 
     if (!holder || row >= p.m) return;
 #pragma unroll
     for (int c = 0; c < VEC; ++c)
-        if (b0 + c < p.batch) p.out[(size_t)(b0 + c) * p.m + row] = y[c];
+        if (b0 + c < p.batch) out[(size_t)(b0 + c) * p.m + row] = y[c];
 }
 
 // HALF (the order of gemm8x2h): 8 lanes of 16 chunks per row, tiles of 128 chunks; otherwise (gemm8x2, latency
 // mode) 4 lanes, tiles of 64.
-// MULTI: rows of several splits.
+// MULTI: rows of several splits in the waves of a workgroup; otherwise the grid's z is the split, and p.out takes the
+// splits' sums one after the other.
 template <int Q, bool HALF, int LOG_SLICES, bool MULTI>
 __global__ __launch_bounds__(MULTI ? 64 * kGatherWaves : 64) void gather8_kernel(const QueryParams p) {
     constexpr int LANES = HALF ? 8 : 4, SL = 1 << LOG_SLICES, ROWS = 64 / (LANES * SL);
@@ -108,7 +101,8 @@ __global__ __launch_bounds__(MULTI ? 64 * kGatherWaves : 64) void gather8_kernel
     const int slot = rsub * SL + (lane & (SL - 1));
     const uint32_t stride_bytes = (uint32_t)p.stride_dw * 4u;
     float y[kGatherVec];
-    for (int sp = MULTI ? wave : 0; sp < (MULTI ? p.splits : 1); sp += (int)blockDim.x >> 6) {
+    const int sp0 = MULTI ? wave : (int)blockIdx.z;
+    for (int sp = sp0; sp < (MULTI ? p.splits : sp0 + 1); sp += (int)blockDim.x >> 6) {
     const uint32_t want = (uint32_t)(sp * LANES * 16 + 16 * L);
     const uint32_t seg = want < stride_bytes ? want : 0u;      // past the row: keys of chunks that count as 0
     gather_u32x4 k[Q];
@@ -165,7 +159,8 @@ __global__ __launch_bounds__(MULTI ? 64 * kGatherWaves : 64) void gather8_kernel
 #pragma unroll
         for (int c = 0; c < kGatherVec; ++c) gather_lds[(sp * ROWS * SL + slot) * kGatherVec + c] = y[c];
     }
-    gather_finish<MULTI>(p, gather_lds, ROWS * SL, slot, L == 0, row0 + rsub, b0, y);
+    gather_finish<MULTI>(p, gather_lds, ROWS * SL, slot, L == 0, row0 + rsub, b0, y,
+                         MULTI ? p.out : p.out + (size_t)sp0 * p.batch * p.m);
 }
 
 // Any mu, for the plans of query_kernel and (ascending) query_wide_kernel: G lanes of one key unit each per row,
@@ -274,8 +269,8 @@ __global__ __launch_bounds__(64 * kGatherWaves) void gather_units_kernel(const Q
 #pragma unroll
         for (int c = 0; c < VEC; ++c) gather_lds[(sp * slots + slot) * VEC + c] = total[c];
     }
-    if (p.splits > 1) gather_finish<true>(p, gather_lds, slots, slot, L == 0, row_want, b0, total);
-    else gather_finish<false>(p, gather_lds, slots, slot, L == 0, row_want, b0, total);
+    if (p.splits > 1) gather_finish<true>(p, gather_lds, slots, slot, L == 0, row_want, b0, total, p.out);
+    else gather_finish<false>(p, gather_lds, slots, slot, L == 0, row_want, b0, total, p.out);
 }
 
 }  // namespace biq

@@ -55,8 +55,9 @@ hipError_t launch_gemv8h(bool fused, int q, const QueryParams& p, int grid, int 
 hipError_t launch_gemm8x2(bool fused, int q, const QueryParams& p, int grid, int threads, int lds, hipStream_t s);
 hipError_t launch_gemm8x2h(bool fused, int q, const QueryParams& p, int grid, int threads, int lds, hipStream_t s);
 
-// few lookups into given tables (mu = 8, several input vectors; half: in the order of gemm8x2_half)
-hipError_t launch_gather(bool half, int q, const QueryParams& p, hipStream_t s);
+// few lookups into given tables (mu = 8, several input vectors; half: in the order of gemm8x2_half; waves: the splits
+// of a row are added in the workgroup, otherwise p.out holds their sums one after the other)
+hipError_t launch_gather(bool half, int q, const QueryParams& p, bool waves, hipStream_t s);
 // ... for the plans of the generic kernel and (ascending) query_wide, any mu
 hipError_t launch_gather_units(int mu, const QueryParams& p, bool ascending, hipStream_t s);
 

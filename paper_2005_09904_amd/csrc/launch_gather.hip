@@ -9,8 +9,9 @@ namespace {
 template <bool HALF, int LOG_SLICES, bool MULTI>
 hipError_t launch_gather_q(int q, const QueryParams& p, hipStream_t s) {
     const int rows = 64 / ((HALF ? 8 : 4) << LOG_SLICES), slices = (p.batch + kGatherVec - 1) / kGatherVec;
-    const dim3 grid((unsigned)((p.m + rows - 1) / rows), (unsigned)((slices + (1 << LOG_SLICES) - 1) >> LOG_SLICES));
-    const dim3 threads(64 * (p.splits < kGatherWaves ? p.splits : kGatherWaves));
+    const dim3 grid((unsigned)((p.m + rows - 1) / rows), (unsigned)((slices + (1 << LOG_SLICES) - 1) >> LOG_SLICES),
+                    MULTI ? 1u : (unsigned)p.splits);
+    const dim3 threads(MULTI ? 64 * (p.splits < kGatherWaves ? p.splits : kGatherWaves) : 64);
     const int lds = MULTI ? p.splits * (HALF ? 8 : 16) * kGatherVec * 4 : 0;
     switch (q) {
         case 1: hipLaunchKernelGGL((gather8_kernel<1, HALF, LOG_SLICES, MULTI>), grid, threads, lds, s, p); break;
@@ -23,8 +24,7 @@ hipError_t launch_gather_q(int q, const QueryParams& p, hipStream_t s) {
 }
 
 template <bool HALF>
-hipError_t launch_gather_half(int q, const QueryParams& p, hipStream_t s) {
-    const bool multi = p.splits > 1;
+hipError_t launch_gather_half(int q, const QueryParams& p, bool multi, hipStream_t s) {
     switch (gather_log_slices(p.batch)) {
         case 0: return multi ? launch_gather_q<HALF, 0, true>(q, p, s) : launch_gather_q<HALF, 0, false>(q, p, s);
         case 1: return multi ? launch_gather_q<HALF, 1, true>(q, p, s) : launch_gather_q<HALF, 1, false>(q, p, s);
@@ -56,8 +56,8 @@ hipError_t launch_gather_mu(const QueryParams& p, bool ascending, hipStream_t s)
 
 }  // namespace
 
-hipError_t launch_gather(bool half, int q, const QueryParams& p, hipStream_t s) {
-    return half ? launch_gather_half<true>(q, p, s) : launch_gather_half<false>(q, p, s);
+hipError_t launch_gather(bool half, int q, const QueryParams& p, bool waves, hipStream_t s) {
+    return half ? launch_gather_half<true>(q, p, waves, s) : launch_gather_half<false>(q, p, waves, s);
 }
 
 hipError_t launch_gather_units(int mu, const QueryParams& p, bool ascending, hipStream_t s) {

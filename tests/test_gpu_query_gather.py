@@ -11,6 +11,10 @@ SHAPES = [
     (17, 129, 4, 6), (513, 2048, 3, 1), (40, 2049, 2, 1), (333, 1000, 4, 1), (100, 3000, 1, 1), (2050, 2050, 2, 9),
     (4096, 2056, 4, 8),                 # copied: 8.4 million reads
     (5000, 1024, 4, 1), (9000, 1024, 4, 1),   # 2.6 million: in place; 4.6: copied
+    # rows of many splits: in the waves of a workgroup, up to 8 of them and in turns (11, 25, 40)
+    (1, 8192, 1, 64), (5, 11264, 1, 9), (17, 25600, 1, 16), (1, 40960, 1, 13),
+    # ... and in workgroups of their own: few rows, the last row of a workgroup alone, odd lengths, more splits than waves hold
+    (64, 16384, 2, 8), (9, 40001, 2, 4), (128, 40000, 2, 4), (3, 20000, 4, 3), (11, 35841, 2, 17), (64, 131072, 1, 4), (2, 66560, 3, 5),
 ]
 
 
@@ -40,3 +44,23 @@ def test_query_equals_the_fused_kernel_bit_for_bit(m, n, q, b):
     biq.biq_gemm_ex(K, alpha, X, Yf, m, n, q, b, 8, biq.biq_plan_get_lut(m, n, q, b, 8), workspace=ws)
     torch.cuda.synchronize()
     assert torch.equal(Y, Yf) and bool((guard[b * m:] == 7.0).all())
+
+
+@pytest.mark.parametrize("m,n,q,b,apart", [(64, 4096, 2, 8, False), (17, 25600, 1, 16, False), (64, 16384, 2, 8, True), (16, 65536, 2, 4, True)])
+def test_splits_of_few_rows_have_workgroups_of_their_own(m, n, q, b, apart):
+    """Then, and only then, their sums pass through the workspace."""
+    import torch
+
+    import paper_2005_09904_amd as biq
+
+    print("query splits", m, n, q, b, flush=True)
+    K = torch.zeros(biq.biq_packed_bytes(m, n, q), dtype=torch.uint8, device="cuda")
+    alpha = torch.ones((q, m), device="cuda")
+    LUT = torch.ones((biq.biq_num_chunks(n, 8) << 8) * b, device="cuda")
+    ws = torch.full((biq.biq_workspace_bytes(m, n, q, b, 8),), 0xA5, dtype=torch.uint8, device="cuda")
+    Y = torch.empty((b, m), device="cuda")
+    biq.biq_query(K, alpha, LUT, Y, m, n, q, b, 8, workspace=ws)
+    torch.cuda.synchronize()
+    assert bool((Y == q * biq.biq_num_chunks(n, 8)).all())
+    splits = biq.biq_plan_get_lut(m, n, q, b, 8).chunk_splits
+    assert splits > 1 and bool((ws[:4 * splits * b * m].view(torch.float32) == q * 128).all()) == apart
