@@ -735,6 +735,10 @@ bool gather_units(const biq_plan& pl, int m, int q, int batch, int mu, int C) {
     const long long tile_end = (long long)ceil_div(C, pl.chunks_per_tile) * pl.chunks_per_tile;
     if (product((long long)C << mu, batch, 1) > (1ll << 28) || product(tile_end << mu, batch, 1) >= (1ll << 30)) return false;
     if (ceil_div(batch, 4) > 65535 || pl.chunk_splits > kGatherSplits) return false;
+    const int keys = unit_keys(mu);
+    if (gather_units_crowd(gather_units_shape(ilog2(pl.chunks_per_tile / keys), m, batch, pl.chunk_splits), batch, pl.chunk_splits,
+                           pl.tiles_per_split, q, keys, ((long long)C << mu) * batch * 4))
+        return false;
     return product((long long)m * q, C, ceil_div(batch, 4)) <= (pl.kernel == KERNEL_WIDE ? kGatherLookups : kGatherUnitLookups);
 }
 

@@ -177,8 +177,7 @@ __global__ __launch_bounds__(64 * kGatherWaves) void gather_units_kernel(const Q
     const int slice = VEC == 1 ? 0 : ((int)blockIdx.y << log_slices) + (lane & ((1 << log_slices) - 1));
     const int b0 = VEC == 1 ? 0 : gather_first_vector(p, slice);
     const int L = (lane >> log_slices) & (p.G - 1);
-    // 2^log_splits splits of a row side by side in a wave (few rows: more workgroups, 187 x 2894, 4 planes, 15 vectors at
-    // mu = 7, where a row of a tile is one lane, 19.4 -> 7.2 us, copied 26.5)
+    // 2^log_splits splits of a row side by side in a wave (gather_units_shape)
     const int lane_split = (lane >> (log_slices + p.log2G)) & ((1 << log_splits) - 1);
     const int log_lanes = p.log2G + log_slices + log_splits;      // lanes of a row: at most 64
     const int row_want = (int)(blockIdx.x << (6 - log_lanes)) + (lane >> log_lanes);

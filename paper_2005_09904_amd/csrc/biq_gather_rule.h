@@ -33,4 +33,41 @@ constexpr bool gather_in_waves(int row_lanes, int m, int q, int batch, int split
     return lines <= (log_slices == 2 && (q == 1 || groups >= 80) ? 10240 : splits <= 4 ? 4096 : 3584);
 }
 
+// Any mu: how gather_units_kernel lays out a call.  2^log_splits splits of a row sit side by side in a wave where rows are
+// few (more workgroups: 187 x 2894, 4 planes, 15 vectors at mu = 7, where a row of a tile is one lane, 19.4 -> 7.2 us, copied 26.5).
+struct GatherUnits { int log_slices, log_splits; long long blocks, slice_blocks; };
+constexpr GatherUnits gather_units_shape(int log_lanes, int m, int batch, int splits) {
+    GatherUnits g{gather_log_slices(batch), 0, 0, 0};
+    if (g.log_slices + log_lanes > 6) g.log_slices = 6 - log_lanes;
+    const long long slices = (batch + kGatherVec - 1) / kGatherVec;
+    g.slice_blocks = (slices + (1 << g.log_slices) - 1) >> g.log_slices;
+    while (log_lanes + g.log_slices + g.log_splits < 6 && (2 << g.log_splits) <= splits &&
+           m * g.slice_blocks < (kGatherCus * 64ll) >> (log_lanes + g.log_slices + g.log_splits))
+        ++g.log_splits;
+    const int rows = 64 >> (log_lanes + g.log_slices + g.log_splits);
+    g.blocks = ((long long)m + rows - 1) / rows;
+    return g;
+}
+
+// Where reading in place takes longer than copying the tables to LDS (15-25 us): the splits of a row share the waves of a workgroup, so
+// that few long rows leave most of the chip idle.  Counted in cache lines that a CU reads one after the other (keys_per_lane: of one
+// tile and plane), a line costs 0.3-0.45 ns as long as the tables fit the 4 MB of an XCD's L2, 1.1-1.3 ns beyond.  Several vectors,
+// copied / in place, us: 655 x 6055, 4 planes, 2 vectors, mu = 4 (32768 lines) 22 / 14; 4 x 37436, 2, 7, 2 (40960) 24 / 17;
+// 26 x 79841, 2, 4, 3 (53248) 26 / 30; 13 x 66339, 4, 5, 3 (90112) 26 / 43; tables beyond the L2: 4 x 53398, 1, 3, 5 (12288) 19 / 8; 77 x
+// 119417, 1, 3, 6 (20480) 28 / 32; 4 x 100000, 2, 4, 6 (34816) 22 / 41; 10 x 124685, 4, 5, 5 (102400) 24 / 138.  A full chip hides those
+// reads, while its copies cost up to 50 us (2674 x 11220, 2, 4, 7 (57344) 48 / 40), but for one vector copies stay at 15-25 us, more where
+// rows are many and have one plane: 7 x 46503, 2, 1, 3 (32768) 15 / 11; 587 x 13830, 5, 1, 8 (40960) 18 / 26; 1898 x 20280, 3, 1, 7
+// (73728) 32 / 50; 2200 x 10761, 5, 1, 7 (143360) 19 / 48; 14328 x 4164, 1, 1, 7 (43008) 35 / 18.  Tables in a CU's own cache cost 0.1-0.2 ns a
+// line: 2528 x 995, 5, 1, 1 (81920) 37 / 19; 11743 x 1463, 2, 1, 2 (98304) 21 / 25; 5389 x 1446, 5, 1, 2 (122880) 25 / 30.
+constexpr bool gather_units_crowd(const GatherUnits& g, int batch, int splits, int tiles_per_split, int q, int keys_per_lane,
+                                  long long table_bytes) {
+    const long long groups = g.blocks * g.slice_blocks;
+    if (groups >= kGatherCus && batch > 1) return false;
+    const long long turns = (splits + (1 << g.log_splits) - 1) >> g.log_splits;
+    const long long lines = ((groups + kGatherCus - 1) / kGatherCus * turns * tiles_per_split * q * keys_per_lane * 64) >> g.log_slices;
+    if (table_bytes > 4000000) return lines > 16384;
+    if (batch > 1) return lines > 40960;
+    return lines > (table_bytes <= 16000 ? 98304 : q == 1 ? 49152 : 32768);
+}
+
 }  // namespace biq

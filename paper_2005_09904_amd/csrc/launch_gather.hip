@@ -34,22 +34,15 @@ hipError_t launch_gather_half(int q, const QueryParams& p, bool multi, hipStream
 
 template <int MU>
 hipError_t launch_gather_mu(const QueryParams& p, bool ascending, hipStream_t s) {
-    int log_slices = gather_log_slices(p.batch);
-    if (log_slices + p.log2G > 6) log_slices = 6 - p.log2G;
-    const int slices = (p.batch + kGatherVec - 1) / kGatherVec, ygrid = (slices + (1 << log_slices) - 1) >> log_slices;
-    int log_splits = 0;
-    while (p.log2G + log_slices + log_splits < 6 && (2 << log_splits) <= p.splits &&
-           (long long)p.m * ygrid < (256ll * 64) >> (p.log2G + log_slices + log_splits))
-        ++log_splits;
-    const int rows = 64 >> (p.log2G + log_slices + log_splits);
-    const dim3 grid((unsigned)((p.m + rows - 1) / rows), (unsigned)ygrid);
-    const int waves = (p.splits + (1 << log_splits) - 1) >> log_splits;
+    const GatherUnits g = gather_units_shape(p.log2G, p.m, p.batch, p.splits);
+    const dim3 grid((unsigned)g.blocks, (unsigned)g.slice_blocks);
+    const int waves = (p.splits + (1 << g.log_splits) - 1) >> g.log_splits;
     const dim3 threads(64 * (waves < kGatherWaves ? waves : kGatherWaves));
-    const int lds = p.splits > 1 ? p.splits * (64 >> (p.log2G + log_splits)) * (p.batch == 1 ? 1 : kGatherVec) * 4 : 0;
+    const int lds = p.splits > 1 ? p.splits * (64 >> (p.log2G + g.log_splits)) * (p.batch == 1 ? 1 : kGatherVec) * 4 : 0;
     if (p.batch == 1)
-        hipLaunchKernelGGL((gather_units_kernel<MU, 1>), grid, threads, lds, s, p, 0, log_splits, (int)ascending);
+        hipLaunchKernelGGL((gather_units_kernel<MU, 1>), grid, threads, lds, s, p, 0, g.log_splits, (int)ascending);
     else
-        hipLaunchKernelGGL((gather_units_kernel<MU, kGatherVec>), grid, threads, lds, s, p, log_slices, log_splits,
+        hipLaunchKernelGGL((gather_units_kernel<MU, kGatherVec>), grid, threads, lds, s, p, g.log_slices, g.log_splits,
                            (int)ascending);
     return hipGetLastError();
 }

@@ -1,4 +1,5 @@
-"""csrc/biq_gather_rule.h: rows whose splits would crowd a few CUs give them workgroups of their own."""
+"""csrc/biq_gather_rule.h: rows whose splits would crowd a few CUs give them workgroups of their own
+(mu = 8) or are copied (any mu)."""
 import os
 import subprocess
 
@@ -33,3 +34,28 @@ def test_splits_in_waves_or_apart(tmp_path):
             assert waves                              # the chip is full either way: a dispatch less
         seen.add((lanes, share, waves))
     assert len(seen) == 12
+
+
+def test_units_of_few_long_rows(tmp_path):
+    rows = _run(tmp_path, """
+    for (int lanes = 0; lanes <= 6; ++lanes)
+        for (int m = 1; m <= 20000; m = m * 3 / 2 + 1)
+            for (int b = 1; b <= 300; b = b * 2 + (b == 2))
+                for (int s = 1; s <= 64; s = s * 5 / 4 + 1) {
+                    const GatherUnits g = gather_units_shape(lanes, m, b, s);
+                    std::printf("%d %d %d %d %d %d %lld %lld %d %d %d\\n", lanes, m, b, s, g.log_slices, g.log_splits, g.blocks, g.slice_blocks,
+                                gather_units_crowd(g, b, s, 1, 2, 32, 16000), gather_units_crowd(g, b, s, 1, 2, 32, 4000000),
+                                gather_units_crowd(g, b, s, 1, 2, 32, 4000001));
+                }""")
+    for lanes, m, b, s, slices, splits, blocks, slice_blocks, crowd_l1, crowd_l2, crowd_beyond in rows:
+        row = lanes + slices + splits
+        assert row <= 6 and (1 << splits) <= s
+        assert blocks * (64 >> row) >= m > (blocks - 1) * (64 >> row)
+        assert slice_blocks << slices >= -(-b // 4) > (slice_blocks - 1) << slices
+        # LDS: the sums of every split, 16 bytes each
+        assert s * (64 >> (lanes + splits)) * 16 <= 65536
+        groups = blocks * slice_blocks
+        lines = -(-groups // 256) * -(-s // (1 << splits)) * 2 * 32 * 64 >> slices
+        idle = groups < 256 or b == 1
+        assert crowd_l1 == (idle and lines > (98304 if b == 1 else 40960)) and crowd_beyond == (idle and lines > 16384)
+        assert crowd_l2 == (idle and lines > (32768 if b == 1 else 40960))

@@ -12,6 +12,9 @@ SHAPES = [
     (400, 1000, 6, 2, 8),                 # more planes than the mu = 8 kernels hold
     (2000, 3072, 4, 3, 6), (2200, 3072, 4, 4, 6),      # query_wide: 4.1 million reads in place, 4.5 copied
     (4096, 2000, 4, 14, 5), (4096, 1500, 4, 14, 5),    # generic: 26 million copied, 19.7 in place
+    # few long rows: in place up to what a workgroup reads, copied beyond
+    (4, 53398, 1, 3, 5), (31, 11428, 4, 4, 7), (4, 100000, 2, 4, 6), (10, 124685, 4, 5, 5), (176, 76222, 4, 1, 7),
+    (4200, 10240, 1, 12, 10),             # the most LDS: 64 splits, a lane per row
 ]
 
 
@@ -40,3 +43,24 @@ def test_query_equals_the_fused_kernel_bit_for_bit(m, n, q, b, mu):
     biq.biq_gemm_ex(K, alpha, X, Yf, m, n, q, b, mu, biq.biq_plan_get_lut(m, n, q, b, mu), workspace=ws)
     torch.cuda.synchronize()
     assert torch.equal(Y, Yf) and bool((guard[b * m:] == 7.0).all())
+
+
+@pytest.mark.parametrize("m,n,q,b,mu,copied", [(4, 53398, 1, 3, 5, False), (4, 100000, 2, 4, 6, True), (176, 76222, 4, 1, 7, True)])
+def test_few_long_rows_are_copied(m, n, q, b, mu, copied):
+    """Then, and only then, the sums of the splits pass through the workspace."""
+    import torch
+
+    import paper_2005_09904_amd as biq
+
+    print("query few long rows", m, n, q, b, mu, flush=True)
+    K = torch.zeros(biq.biq_packed_bytes(m, n, q), dtype=torch.uint8, device="cuda")
+    alpha = torch.ones((q, m), device="cuda")
+    LUT = torch.ones((biq.biq_num_chunks(n, mu) << mu) * b, device="cuda")
+    ws = torch.full((biq.biq_workspace_bytes(m, n, q, b, mu),), 0xA5, dtype=torch.uint8, device="cuda")
+    Y = torch.empty((b, m), device="cuda")
+    biq.biq_query(K, alpha, LUT, Y, m, n, q, b, mu, workspace=ws)
+    torch.cuda.synchronize()
+    assert bool((Y == q * biq.biq_num_chunks(n, mu)).all())
+    p = biq.biq_plan_get_lut(m, n, q, b, mu)
+    assert p.chunk_splits > 1
+    assert bool((ws[:4 * b * m].view(torch.float32) == q * p.tiles_per_split * p.chunks_per_tile).all()) == copied
