@@ -12,7 +12,7 @@ import ctypes
 import os
 from typing import Optional
 
-from .build import LIB_PATH
+from .build import CALLS_PATH, LIB_PATH
 
 BIQ_OK, BIQ_EINVAL, BIQ_EUNSUPPORTED, BIQ_EWORKSPACE, BIQ_EHIP = 0, -1, -2, -3, -4
 
@@ -63,10 +63,11 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     if _lib is not None and path is None:
         return _lib
     path = path or LIB_PATH
-    if not os.path.exists(path):
-        raise FileNotFoundError(
-            "%s not found: build it first (python -m paper_2005_09904_amd.build); "
-            "there is no CPU fallback" % path)
+    for needed in (path, CALLS_PATH):
+        if not os.path.exists(needed):
+            raise FileNotFoundError(
+                "%s not found: build it first (python -m paper_2005_09904_amd.build); "
+                "there is no CPU fallback" % needed)
     lib = ctypes.CDLL(path)
     I, P, Z = ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t
     PL = ctypes.POINTER(BiqPlan)

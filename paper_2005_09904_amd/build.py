@@ -1,5 +1,5 @@
-"""Builds libbiq.so (the HIP kernels and their C ABI) for gfx950 with hipcc, and _calls.so (the calls from
-Python into it, host code), in-tree.
+"""Builds libbiq.so (the HIP kernels and their C ABI) for gfx950 with hipcc, and the extension module _calls (the calls
+from Python into it, host code; needs g++ and this interpreter's headers), in-tree.
 
 One translation unit per kernel family (csrc/*.hip), compiled side by side and linked into one
 shared library; objects go to paper_2005_09904_amd/_build/ (not tracked)."""
@@ -17,7 +17,8 @@ ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 OBJ_DIR = os.path.join(PKG_DIR, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libbiq.so")
-CALLS_PATH = os.path.join(PKG_DIR, "_calls.so")
+# (named for the interpreter it is built for: another one finds none, rather than one with other object layouts)
+CALLS_PATH = os.path.join(PKG_DIR, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 CALLS_SOURCE = os.path.join(CSRC, "py_calls.cpp")
 SOURCES = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 HEADERS = sorted(glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(CSRC, "*.inc"))) + [
@@ -47,7 +48,7 @@ def _run(cmd, verbose):
     # the host pass warns that it does not know the packed-fp32 feature; that is expected
     out = "\n".join(l for l in proc.stdout.splitlines() if "packed-fp32-ops" not in l)
     if proc.returncode != 0:
-        raise RuntimeError("hipcc failed: %s\n%s" % (" ".join(cmd), out))
+        raise RuntimeError("%s failed: %s\n%s" % (cmd[0], " ".join(cmd), out))
     if verbose and out.strip():
         print(out)
 

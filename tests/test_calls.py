@@ -92,3 +92,22 @@ def test_what_is_no_integer_or_tensor_is_refused(recorded):
     with pytest.raises(TypeError):
         b.PreparedGemm(t, t, t, t, 1, 1, 1, 1, 8)._call(1)
     assert not seen
+
+
+def test_the_module_is_the_running_interpreters(recorded, monkeypatch):
+    """Its file name carries the interpreter's tag, so that another interpreter builds its own."""
+    import sysconfig
+
+    import paper_2005_09904_amd._calls as calls
+    from paper_2005_09904_amd import build
+
+    b, _, _, _ = recorded
+    suffix = sysconfig.get_config_var("EXT_SUFFIX")
+    assert os.path.samefile(calls.__file__, build.CALLS_PATH) and build.CALLS_PATH.endswith("_calls" + suffix)
+    assert sys.implementation.cache_tag.replace("-", "") in suffix.replace("-", "") and not build.is_stale()
+    other = build.CALLS_PATH[:-len(suffix)] + ".cpython-399-x86_64-linux-gnu.so"      # what another one looks for
+    monkeypatch.setattr(build, "CALLS_PATH", other)
+    monkeypatch.setattr(b, "CALLS_PATH", other)
+    assert build.is_stale()
+    with pytest.raises(FileNotFoundError, match="cpython-399"):
+        b.load_library(build.LIB_PATH)
