@@ -45,3 +45,16 @@ def test_no_kernel_uses_scratch():
     spilled = {n: k[".private_segment_fixed_size"] for n, k in found.items() if k[".private_segment_fixed_size"]
                or k.get(".uses_dynamic_stack")}
     assert not spilled
+
+
+def test_gather8_without_a_loop_over_splits_is_compiled_without_one():
+    """Where the grid holds the splits, the compiler has to see that a wave has one of them: kept as a loop, the addresses of all
+    its reads stay in registers, as many as where a wave does have several."""
+    from paper_2005_09904_amd.build import LIB_PATH
+
+    with open(LIB_PATH, "rb") as f:
+        vgprs = {k[".name"]: k[".vgpr_count"] for elf in code_objects(f.read()) for k in kernels(elf) if "gather8_kernel" in k[".name"]}
+    single = [n for n in vgprs if "ELb0EEEv" in n]
+    assert len(single) == 24 and len(vgprs) == 48        # planes, both orders, slices on neighbouring lanes
+    for n in single:
+        assert vgprs[n] < 0.9 * vgprs[n.replace("ELb0EEEv", "ELb1EEEv")], (n, vgprs[n])
