@@ -713,7 +713,7 @@ bool gather_tables(const biq_plan& pl, int m, int q, int batch, int C) {
         return false;
     // 32-bit offsets: at most 1 GiB of tables, and less than 4 GiB up to the end of the last tile, since lanes
     // address whole tiles and a chunk past the row counts as 0 only while its offset does not wrap (one chunk,
-    // 131072 vectors: chunk 32 would be chunk 0 again); slices of 4 vectors are the grid's z, at most 65535
+    // 131072 vectors: chunk 32 would be chunk 0 again); slices of 4 vectors are the grid's y, at most 65535
     const long long tile_end = (long long)ceil_div(C, pl.chunks_per_tile) * pl.chunks_per_tile;
     if (pl.row_mode == 0 || (long long)C * batch > (1ll << 20) || tile_end * batch >= (1ll << 22)) return false;
     if (ceil_div(batch, 4) > 65535) return false;

@@ -32,8 +32,8 @@
 //
 // Inputs that hold bf16 values (all elements of a key group - 256 - of all vectors of a column
 // group) keep the one-term bf16 form: 16 elements per instruction, but one term instead of five digits
-// (16384 x 4096, 2 planes, 128 vectors 33 us, 4096 x 16384 36-39; there the 8 instructions that expand a row tile's
-// weights bound the loop as much as its matrix instructions do).  Values of fp16 take all five digits.
+// (16384 x 4096, 2 planes, 128 vectors 33 us, 4096 x 16384 36-39: of 63 thousand clocks the vector ALU, which expands the
+// weights, issues 40 and the matrix pipe is busy 33; what keeps the two from overlapping is not known).  Values of fp16 take all five digits.
 // The form is chosen per (column group, key group) by the kernel that prepares the operands; the
 // main kernel walks first the key groups of one form, then those of the other.
 //

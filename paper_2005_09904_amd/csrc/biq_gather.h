@@ -5,7 +5,7 @@
 // reads its entry where it lies; the tables stay in L2.  Bound by the address unit: one cache line per
 // lane and lookup, up to four input vectors of an entry in one read.  Same lookups in the same order of the sums as
 // the kernel that copies (and as the fused one): the same bits.  Time, copy -> here: 1024 x 1024, 2 planes, 8
-// vectors 17.8 -> 4.2 us, 4096 x 1000, 4, 5: 34 -> 18, one vector: 2000 x 1800, 2 planes 16.8 -> 5.3.  (Reads behind
+// vectors 17.8 -> 3.4 us, 4096 x 1000, 4, 5: 34 -> 11, one vector: 2000 x 1800, 2 planes 16.8 -> 5.1.  (Reads behind
 // conditions on the last chunk and the last vectors were waited for one by one: 7.3 us for the first.)
 #pragma once
 

@@ -5,12 +5,15 @@ namespace biq {
 
 constexpr int kGatherVec = 4;      // input vectors of a lane's read
 constexpr int kGatherWaves = 8;    // most waves of a workgroup
-constexpr int kGatherSplits = 64;  // most splits of a row (32 KiB of LDS with 8 lanes per row)
+// Most splits of a row that a workgroup adds.  Their sums lie in LDS, 16 bytes for each of up to 64 rows and slices: with one
+// lane per row 64 KiB, the most that a launch gets without asking for more.
+constexpr int kGatherSplits = 64;
+static_assert(kGatherSplits * 64 * kGatherVec * 4 <= 65536, "LDS of a workgroup");
 constexpr int kGatherCus = 256;
 
 // The slices of up to four vectors an entry is read in, of one lane each: 1, 2 or 4 of them (2^log_slices) on
 // neighbouring lanes, which then share the entry's cache lines (a wave's reads cost the address unit a line each:
-// 1024 x 1024, 2 planes, 8 vectors 3.8 -> 3.1 us on the GPU; 3317 x 480, 2, 15 9.3 -> 5.6), the rest in the grid's y.
+// 1024 x 1024, 2 planes, 8 vectors 3.8 -> 3.1 us on the GPU; 3317 x 480, 2, 15 9.3 -> 4.8), the rest in the grid's y.
 constexpr int gather_log_slices(int batch) { return batch > 2 * kGatherVec ? 2 : batch > kGatherVec ? 1 : 0; }
 
 // mu = 8: the splits of a row in the waves of one workgroup, which adds them, or in workgroups of their own and added by
