@@ -84,9 +84,11 @@ struct DigitParams {
 // other; returns the block's scale byte (digit d counts 2^-5d of it), 255 (NaN) for a block with Inf or NaN.
 template <int UNROLL, typename Emit>
 __device__ __forceinline__ uint32_t digit_split(const float (&x)[32], Emit&& emit) {
-    uint32_t mb = 0;
+    // (the maximum that NaN passes on: two elements an instruction)
+    float mx = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 32; ++i) mb = max(mb, __float_as_uint(x[i]) & 0x7fffffffu);
+    for (int i = 0; i < 32; ++i) mx = __builtin_elementwise_maximum(mx, __builtin_fabsf(x[i]));
+    const uint32_t mb = __float_as_uint(mx) & 0x7fffffffu;
     const bool finite = mb < 0x7f800000u;
     const int ex = max((int)(mb >> 23), 1);          // (subnormal elements: exponent as 1)
     const float norm = __uint_as_float((uint32_t)max(255 - ex, 1) << 23);   // 2^(128 - ex)
