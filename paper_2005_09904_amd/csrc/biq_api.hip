@@ -130,13 +130,15 @@ inline int plan_lds_bytes(const biq_plan& pl, int mu) {
 // groups of waves along the row; as many row steps per workgroup as leave at most 256 workgroups.  A row step costs
 // its chunks (matrix pipe, expansion or LDS of the two waves per SIMD, or the latency of the next keys) and an
 // epilogue; keys stream at 3.3 TB/s; the split of the inputs 1.9 us per 512 blocks.  Fitted to 94 random
-// shapes (128 .. 280000 rows, 128 .. 16000 columns, 1 .. 48 vectors): 13 % rms.  The estimate handed on (not the
-// choice of the mapping) has at least 0.85 us per row step where there are several: a step waits for its scales,
-// and short rows have nothing else to do meanwhile (1025348 x 111, 1 plane, 1 vector: 16 us without, measured 34).
+// shapes (128 .. 280000 rows, 128 .. 16000 columns, 1 .. 48 vectors): 13 % rms; one vector on more than 2048 columns to
+// 2300 times of 298 shapes: 7 % rms, the mapping chosen 0.2 % slower in the mean than the best.  The estimate handed on
+// (not the choice of the mapping) has at least 0.85 us per row step where there are several: a step waits for its scales,
+// and short rows have nothing else to do meanwhile (1025348 x 111, 1 plane, 1 vector: 16 us without, measured 34).  All
+// are 8 % below what a replayed graph takes with keys from memory.
 struct DirectGeom {
     int vecs, batch_tiles, chunks, ksplit, steps, row_blocks, lds;
     int uc;                  // chunks requested together
-    bool many;               // the many-rows instantiation
+    int kind;                // DirectKind
     double est;
 };
 // Input vectors of one workgroup whose digits fit the LDS beside the exchange buffers.
@@ -157,22 +159,37 @@ bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
     g.batch_tiles = ceil_div(batch, g.vecs);
     if (g.batch_tiles > 65535) return false;
     const int nt = ceil_div(g.vecs, 3);
-    const double mem = (double)q * m * biq_key_row_stride(n) * g.batch_tiles / 3.3e6;
     double best = 1e30;
-    for (int many = 1; many >= 0; --many)
-        for (int ks = 1; ks <= (many ? 1 : kDirectWaves) && (ks == 1 || ks <= g.chunks); ks *= 2) {
-            const int rpw = many ? direct_rpw(q, nt) : 1, uc = many ? direct_uc(nt) : 1;
-            if (many && rpw == 1 && uc == 1) break;      // the few-rows instantiation itself
+    for (int kind : {DIRECT_MANY, DIRECT_LINES, DIRECT_FEW}) {
+        if (!direct_has_kind(kind, q, nt)) continue;
+        const int rpw = kind == DIRECT_MANY ? direct_rpw(q, nt) : 1, uc = kind == DIRECT_FEW ? 1 : direct_uc(nt);
+        // one vector on wide rows: costs of their own, and beyond 256 row tiles several groups of waves along whole lines,
+        // too (332 shapes: up to there those take 1.01 to 1.2 times as long, 0.97 with four row steps and 0.84 with five
+        // and more; with 2 to 6 vectors, 110 shapes, 1 % less at most)
+        const bool one = batch == 1 && n > 2048 && kind != DIRECT_MANY;
+        if (kind == DIRECT_LINES && (one ? m <= 16 * kNumCu : direct_rpw(q, nt) > 1)) continue;
+        const double rate = !one ? 3.3e6 : uc == 2 ? 4.35e6 : 3.72e6;
+        const double mem = (double)q * m * biq_key_row_stride(n) * g.batch_tiles / rate;
+        for (int ks = 1; ks <= (kind == DIRECT_FEW || (one && uc == 2) ? kDirectWaves : 1) && (ks - 1) * uc < g.chunks; ks *= 2) {
             const long long all_steps = ceil_div(m, kDirectWaves / ks * rpw * 16);
             long long steps = ceil_div_ll(all_steps * g.batch_tiles, kNumCu);
             if (steps > all_steps) steps = all_steps;
             const double rounds = (double)ceil_div_ll(ceil_div_ll(all_steps, steps) * g.batch_tiles, kNumCu);
             const int rt = q * rpw, upg = ceil_div(ceil_div(g.chunks, uc), ks);
-            double clk = 22.0 * rt * (16 * nt > 32 ? 16 * nt : 32);
-            if (clk < 860.0 * nt) clk = 860.0 * nt;
-            if (clk < 742.0) clk = 742.0;
-            double work = rounds * steps * (upg * uc * clk / 2200.0 + 0.012 * rt * nt + (ks > 1 ? 0.36 : 0.0));
-            const double before = 1.3 + 0.36 * (nt - 1) + 1.94 * rounds * ceil_div(g.chunks * g.vecs, 4 * kDirectWaves);
+            double clk, row_step, before;                // a chunk; the rest of a row step; what comes ahead of the first
+            if (one) {
+                clk = 727.0 * q;
+                const double least = uc == 2 ? 818.0 : 1132.0;
+                if (clk < least) clk = least;
+                row_step = ks > 1 ? 0.57 : 0.53;
+                before = 2.54 + 1.87 * g.chunks / (4 * kDirectWaves);
+            } else {
+                clk = 22.0 * rt * (16 * nt > 32 ? 16 * nt : 32);
+                if (clk < 860.0 * nt) clk = 860.0 * nt;
+                row_step = 0.012 * rt * nt + (ks > 1 ? 0.36 : 0.0);
+                before = 1.3 + 0.36 * (nt - 1) + 1.94 * rounds * ceil_div(g.chunks * g.vecs, 4 * kDirectWaves);
+            }
+            double work = rounds * steps * (upg * uc * clk / 2200.0 + row_step);
             // (both together, smoothly: of two mappings that memory bounds, the one with less work)
             const double t = before + cbrt(work * work * work + mem * mem * mem);
             if (t < best) {
@@ -181,13 +198,14 @@ bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
                     work = 0.85 * rounds * steps;
                     g.est = before + cbrt(work * work * work + mem * mem * mem);
                 }
-                g.many = many != 0;
+                g.kind = kind;
                 g.ksplit = ks;
                 g.uc = uc;
                 g.steps = (int)steps;
                 g.row_blocks = (int)ceil_div_ll(all_steps, steps);
             }
         }
+    }
     g.lds = (int)direct_lds_bytes(g.chunks, g.vecs, 1, g.ksplit > 1);
     return best < 1e30;
 }
@@ -274,7 +292,9 @@ bool plan_finish(biq_plan& pl, int m, int n, int q, int batch, int mu) {
 // 3 us for a second kernel.  (Estimated / measured: 5003 x 3001, 3 planes, 20 vectors 24 / 25.7; 16384 x 4096, 4, 32:
 // 74 / 78; 1500 x 6000, 1, 40: 16 / 18.5.)  Narrow keys, fitted to 407 shapes, 10 % rms: 5.5 us per round and the lookups of
 // a whole tile, twice (mu = 5) and 3.2 times (mu = 6) the time where a pass serves one vector only; a second kernel
-// 3 us and 15 us per million partial results.  The generic kernel: 6.5e12 lookups/s, keys at no more than 0.25 TB/s,
+// 3 us and 15 us per million partial results.  One vector in half tables, fitted to 275 shapes, 7 % rms: 0.8 us and a row's
+// planes at 11 ns per tile, 2.4 us more where rows of the input are not read 16 bytes at a time, keys at 6.7 TB/s, a second
+// kernel 1 us, 0.27 us per split and 13 us per million partial results.  The generic kernel: 6.5e12 lookups/s, keys at no more than 0.25 TB/s,
 // and 0.4 us per partial result a second kernel adds (320 x 12288, mu = 7, 4, 24: 38 / 33) - but one vector on rows of
 // up to four key units, the fewer lanes of a row the better: 0.1 to 0.3 ps per lookup of a row's whole units, more
 // where the workgroups are fewer than the CUs (310460 x 192, mu = 4, 1 plane 7.3 / 6.8 us; the general rule says 35.8).
@@ -290,6 +310,15 @@ double tables_estimate(const biq_plan& pl, int m, int n, int q, int batch, int m
         const double slower = mu == 6 ? 3.2 : mu == 5 ? 2.0 : 1.0;
         return rounds * (5.5 + slower * rows * q * pl.chunks_per_tile * pl.batch_tile / 65e3) +
                (pl.chunk_splits > 1 ? 3.0 + 15e-6 * pl.chunk_splits * (double)m * batch : 0.0);
+    }
+    if (pl.kernel == KERNEL_GEMV8H) {
+        const double rq = rows * q, tiles = pl.tiles_per_split;
+        const double walk = rounds * (pl.row_mode == 2 ? 0.011 * rq + (n % 4 ? 2.7 : 0.0)
+                                                       : tiles * (0.8 + 0.011 * rq + (n % 4 ? 2.4 : 0.0)) +
+                                                             (tiles > 1 ? 0.42 * q : 0.0) + (tiles > 2 ? 0.5 * q : 0.0));
+        const double mem = (double)q * m * biq_key_row_stride(n) / 6.7e6;
+        return 3.3 + cbrt(walk * walk * walk + mem * mem * mem) +
+               (pl.chunk_splits > 1 ? 1.06 + pl.chunk_splits * (0.27 + 13e-6 * m) : 0.0);
     }
     const int units = pl.chunks_per_tile / unit_keys(mu);
     if (batch == 1 && units <= 4 && pl.chunk_splits == 1 && mu <= 7) {
@@ -612,23 +641,24 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
                   DirectGeom* geom = nullptr) {
     const bool ok = plan_tables(pl, m, n, q, batch, mu) || plan_generic(pl, m, n, q, batch, mu);
     if (tables_given || q > 4) return ok;
-    const double tables = ok ? tables_estimate(pl, m, n, q, batch, mu) : 1e30;
     // Few vectors, no tables: the plan stays the table kernel's (what biq_query runs for the shape), marked
     // by table_fill = 2.  Fewer than 128 rows (less than one row step of a workgroup) keep the tables, whose sums
     // biq_query repeats bit for bit.
+    DirectGeom local{};
+    DirectGeom& g = geom ? *geom : local;             // (a caller that launches the direct kernel has use for it)
     if (mu == 8 && batch == 1) {
-        // One vector (keys from memory): rows beyond one half-table tile whose inputs the table kernels cannot
-        // read 16 bytes at a time (n % 4; 5000 x 3001, 3 planes 11.9 us with tables, 6.4 without; 236 x 4414, 2:
-        // 14.2 / 5.0; 4928 x 9573, 1: 10.3 / 8.2), up to 24 MB of keys.  Others: 16384 x 4096, 2: 8.2 / 8.5 (keys on
-        // chip 7.3 / 5.9);
-        // 452 x 832, 3: 3.9 / 4.6; 15265 x 10112, 4, 77 MB: 22.5 / 28.8.
-        const long long keys = (long long)q * m * (long long)biq_key_row_stride(n);
-        if (ok && m >= 128 && n > 2048 && n % 4 != 0 && keys <= 24000000 && direct_max_vectors(n) > 0)
+        // One vector: rows beyond one half-table tile, i.e. where the tables take several builds or a second dispatch, if
+        // direct is estimated well below them (298 shapes, 128 .. 128128 rows, 2049 .. 40900 columns, keys from memory: 193
+        // of them, 23 % less in the mean over all, two longer by 4 %; the better one of the two everywhere: 24 %).  Tables /
+        // direct: 256 x 5952, 3 planes 9.3 / 5.9; 4096 x 4096, 2 6.7 / 5.0; 4096 x 11008, 2 12.6 / 7.9; 16384 x 4096, 2 8.7 /
+        // 7.7; 5000 x 3001, 3 11.9 / 6.4; but 11008 x 4096, 3 8.9 / 8.9; 1088 x 9288, 4 8.3 / 9.7; 234 x 32722, 4 12.4 / 19.4;
+        // 36294 x 3136, 2 12.7 / 15.4.  The full-table kernel (33 MB of keys and more) keeps its calls: 47993 x 6847, 3 35 / 40.
+        if (ok && m >= 128 && n > 2048 && pl.kernel == KERNEL_GEMV8H && direct_geometry(g, m, n, q, 1) &&
+            g.est < 0.865 * tables_estimate(pl, m, n, q, 1, mu))
             pl.table_fill = 2;
         return ok;
     }
-    DirectGeom local{};
-    DirectGeom& g = geom ? *geom : local;             // (a caller that launches the direct kernel has use for it)
+    const double tables = ok ? tables_estimate(pl, m, n, q, batch, mu) : 1e30;
     const double direct = ok && m >= 128 && direct_geometry(g, m, n, q, batch) ? g.est : 1e30;
     // (no digit plan is estimated below 8.3 us: small calls, where this search would show, skip it; the
     // narrow-key kernel keeps calls below 5e6 multiply-adds that direct does not take: 129 x 5000, 2
@@ -894,7 +924,7 @@ biq_status run_direct(DirectGeom& g, const uint8_t* K, const float* alpha, const
     p.log_ksplit = ilog2(g.ksplit);
     p.units_per_group = ceil_div(ceil_div(g.chunks, g.uc), g.ksplit);
     p.steps = g.steps;
-    const auto launch = g.many ? launch_direct_many : launch_direct_few;
+    const auto launch = g.kind == DIRECT_MANY ? launch_direct_many : g.kind == DIRECT_LINES ? launch_direct_lines : launch_direct_few;
     return launch(q, ceil_div(g.vecs, 3), p, dim3(g.row_blocks, g.batch_tiles), g.lds, s) == hipSuccess ? BIQ_OK : BIQ_EHIP;
 }
 

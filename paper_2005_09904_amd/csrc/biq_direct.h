@@ -26,10 +26,11 @@
 // before -> here: 5003 x 3001, 3 planes, 7 vectors at mu = 6 13.1 (three bf16 terms 16.3) -> 9.2; 5000 x 3001, 3, 1
 // 11.9 -> 6.4; 10240 x 1216, 2, 12 17.6 -> 8.6; 32000 x 1024, 3, 6 18.6 -> 7.0; 1790 x 316, 3, 5 at mu = 7 18.6 -> 4.7.
 // With 4 planes and 10-15 vectors, keys on chip: 20000 x 700 9.3, 10000 x 2000 10.3.
-// Errors 4-9e-8 instead of 0.8-1.2e-7 (tables).  Not taken for one vector where the tables read rows 16 bytes at a
-// time (16384 x 4096, 2, tables / direct: keys from memory 8.2 / 8.5, on chip 7.3 / 5.9), nor for small layers with several
-// vectors (919 x 832, 3, 9: 4.4 / 6.7).
-// (Two chunks requested together for few rows, too: 8.6 -> 7.8 there, but 5000 x 3001 6.4 -> 7.8.)
+// Errors 4-9e-8 instead of 0.8-1.2e-7 (tables).  One vector, 2 planes, tables / direct: 4096 x 4096 6.7 / 5.0, 16384 x 4096
+// 8.7 / 7.7 (keys on chip 7.2 / 5.4).  Not taken for one vector where a table workgroup covers the row (2048 x 2048, 2:
+// 4.0 / 4.6), nor for small layers with several vectors (919 x 832, 3, 9: 4.4 / 6.7).
+// (Two chunks requested together with one row tile per wave, several groups of waves: 16384 x 4096 8.3 -> 7.7 us, but
+// 5000 x 3001 6.4 -> 7.8: only where a workgroup has several row steps.)
 //
 // Layout.  Operand lane 16 * kg + r: row / column r, the 32 elements of one key dword.  A lane loads
 // 16 key bytes, [64 j + 16 kg, +16) of its row ("chunk" j = 512 elements): four lanes cover 64
@@ -46,11 +47,16 @@ namespace biq {
 constexpr int kDirectThreads = 512;
 constexpr int kDirectWaves = kDirectThreads / 64;
 constexpr int kDirectMaxVec = 15;                 // vectors of a workgroup: five column tiles
-// The mapping for many rows: more row tiles per wave share a step's operands in LDS, and two chunks
-// requested together (128 bytes per row: a whole line) keep 8 KiB per wave in flight.  What fits the
-// registers beside RT x NT accumulators.
+// The mappings: one row tile per wave and one chunk at a time (few rows); one row tile and two chunks requested
+// together, 128 bytes per row: a whole line (lines); more row tiles per wave, which share a step's operands in LDS, and
+// two chunks where the registers hold them beside RT x NT accumulators (many rows).
+enum DirectKind { DIRECT_FEW, DIRECT_MANY, DIRECT_LINES };
 constexpr int direct_rpw(int q, int nt) { return q == 1 ? (nt <= 2 ? 4 : 2) : q == 2 && nt <= 3 ? 2 : 1; }
 constexpr int direct_uc(int nt) { return nt <= 2 ? 2 : 1; }
+constexpr bool direct_has_kind(int kind, int q, int nt) {
+    return kind == DIRECT_FEW || (kind == DIRECT_MANY ? direct_rpw(q, nt) > 1
+                                                      : nt == 1 || (direct_rpw(q, nt) == 1 && direct_uc(nt) == 2));
+}
 
 struct DirectParams {
     const uint8_t* K;        // [q][m][stride]

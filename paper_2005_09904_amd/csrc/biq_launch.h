@@ -87,6 +87,7 @@ hipError_t launch_digits_ws4(int q, int rpw, int ct, const DigitParams& p, int g
 // ---- few input vectors on the block-scaled matrix instructions, one dispatch (plans with table_fill 2) ----
 struct DirectParams;
 hipError_t launch_direct_few(int q, int nt, const DirectParams& p, dim3 grid, int lds, hipStream_t s);
+hipError_t launch_direct_lines(int q, int nt, const DirectParams& p, dim3 grid, int lds, hipStream_t s);
 hipError_t launch_direct_many(int q, int nt, const DirectParams& p, dim3 grid, int lds, hipStream_t s);
 
 // ---- the small kernels ----

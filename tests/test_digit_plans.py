@@ -72,6 +72,17 @@ def test_direct_plans(biq):
         biq.biq_plan_check(300, 42000, 1, 1, 8, p)
 
 
+@pytest.mark.parametrize("m,n,q,direct", [
+    (4096, 4096, 2, True), (16384, 4096, 2, True), (256, 5952, 3, True), (4096, 11008, 2, True), (128, 2052, 2, True),
+    (4096, 2048, 2, False), (127, 4096, 2, False), (1088, 9288, 4, False), (234, 32722, 4, False), (36294, 3136, 2, False),
+    (47993, 6847, 3, False), (256, 42000, 1, False), (4096, 4096, 5, False)])
+def test_one_vector_plans(biq, m, n, q, direct):
+    """One vector on wide rows: tables or none by the estimates of both; the plan is the table kernel's in any case."""
+    p, lut = biq.biq_plan_get(m, n, q, 1, 8), biq.biq_plan_get_lut(m, n, q, 1, 8)
+    assert p.as_dict() == dict(lut.as_dict(), table_fill=2 if direct else 0)
+    assert biq.biq_plan_workspace_bytes(p, m, 1) == biq.biq_plan_workspace_bytes(lut, m, 1)
+
+
 def test_direct_row_limit(biq):
     """The direct kernel counts rows in 32 bits, those its last row steps have past the end included."""
     for m, ok in ((1 << 30, True), ((1 << 30) + 1, False), (3 << 29, False)):

@@ -76,6 +76,37 @@ def test_direct_parity(biq, oracle, m, n, q, b, mu):
     assert np.all(np.abs(Y[:, rows] - ref).max(axis=1) <= _bound(alpha[:, rows], X))
 
 
+@pytest.mark.parametrize("m,n,q", [
+    # whole lines of keys, 1 .. 8 groups of waves along the row; even and odd numbers of chunks, a last row tile of one row
+    # and a last row step that only some workgroups have
+    (16763, 2153, 3), (16513, 2590, 1), (8399, 2083, 1), (8677, 2591, 4), (4222, 3086, 1), (4193, 3772, 2), (8290, 7253, 2),
+    (8427, 15021, 1), (4097, 2049, 3),
+    # ... and one chunk at a time, up to 256 row tiles
+    (4096, 2049, 1), (4081, 4096, 2), (257, 5951, 3), (128, 2052, 4)])
+def test_one_vector_on_wide_rows(biq, oracle, m, n, q):
+    """The mappings of one vector beyond the table workgroups' rows: against the oracle, and against the table kernels."""
+    import torch
+
+    print("wide rows", m, n, q, flush=True)
+    rng = np.random.default_rng(53000 + m + n)
+    X = rng.standard_normal((1, n), dtype=np.float32)
+    B = (rng.integers(0, 2, size=(q, m, n), dtype=np.int8) * 2 - 1).astype(np.int8)
+    alpha = rng.uniform(0.05, 1.0, size=(q, m)).astype(np.float32)
+    Y = _direct(biq, B, alpha, X)
+    rows = np.unique(np.r_[0:min(m, 200), max(0, m // 2 - 100):min(m, m // 2 + 100), max(0, m - 200):m])
+    ref = oracle.gemm_dense(B[:, rows], alpha[:, rows], X)
+    assert_within_tolerance(Y[:, rows], ref, alpha[:, rows], X, "wide rows")
+    assert np.all(np.abs(Y[:, rows] - ref).max(axis=1) <= _bound(alpha[:, rows], X))
+    # every row against the table kernels: both are within the bound, theirs rounds each of n / 8 partial sums
+    Bd, ad, Xd = device_inputs(B, alpha, X)
+    plan = biq.biq_plan_get_lut(m, n, q, 1, 8)
+    ws = torch.empty(max(biq.biq_plan_workspace_bytes(plan, m, 1), 16), dtype=torch.uint8, device="cuda")
+    T = torch.empty((1, m), device="cuda")
+    biq.biq_gemm_ex(gpu_pack(biq, Bd, 8), ad, Xd, T, m, n, q, 1, 8, plan, workspace=ws)
+    limit = _bound(alpha, X) + 2.0 ** -24 * np.abs(alpha).sum(axis=0).max() * np.abs(X).sum() * (-(-n // 8) + 24)
+    assert np.abs(Y - T.cpu().numpy()).max() <= limit[0]
+
+
 def test_direct_special_values(biq, oracle):
     """Exact inputs bit for bit; wide dynamic range within the bound; zeros; Inf and NaN stay in their vector."""
     from paper_2005_09904_amd.workloads import Workload, make_exact_inputs
