@@ -61,6 +61,13 @@ inline int rows_from(long long want, int step, int lo, int m) {
     if (r < lo) r = lo;
     return (int)r;
 }
+// ... with `each` workgroups per block of rows (splits of a row, tiles of input vectors): no more workgroups than CUs where
+// that is possible.  A few more of them are a second round, which builds tables again, on a few CUs (rows shared out as
+// m * each / cus: 7 % of the table plans; 150 of those, table kernels 30 % less with this: 10240 x 11353, 4 planes, 1 vector
+// 33.0 -> 21.6 us, 356 x 4141, 3, 24 13.9 -> 9.4, 384 x 519, 4, 51 9.4 -> 5.6).
+inline int rows_one_round(int m, long long each, int cus, int step, int lo) {
+    return rows_from(each <= cus ? ceil_div_ll(m, cus / each) : ceil_div_ll(product(m, each, 1), cus), step, lo, m);
+}
 inline int ilog2(int v) { int l = 0; while ((1 << (l + 1)) <= v) ++l; return l; }
 
 // 16-byte pieces of prepared input per key group (16 MFMA steps): column tiles x terms x 64 lanes
@@ -287,10 +294,11 @@ bool plan_finish(biq_plan& pl, int m, int n, int q, int batch, int mu) {
 }
 
 // Estimated time (us) of the lookup-table plan `pl`, from rates measured on MI355X: where the tables
-// stop paying off (the crossover of Sec. IV-B / Fig. 10).  The mu = 8 kernels with one workgroup per CU: launch,
-// per round of workgroups over the CUs one table build (2 us; half tables 1.3) and 65e3 lookups per us and CU,
-// 3 us for a second kernel.  (Estimated / measured: 5003 x 3001, 3 planes, 20 vectors 24 / 25.7; 16384 x 4096, 4, 32:
-// 74 / 78; 1500 x 6000, 1, 40: 16 / 18.5.)  Narrow keys, fitted to 407 shapes, 10 % rms: 5.5 us per round and the lookups of
+// stop paying off (the crossover of Sec. IV-B / Fig. 10).  The batched mu = 8 kernels, fitted to 330 shapes, 7 % rms (half
+// tables 5 %): per round of workgroups over the CUs and tile the lookups of its rows and two input vectors, more where rows
+// of the input are not read 16 bytes at a time, keys at 4.5 TB/s, a second kernel with 0.24 us per split.  (Estimated /
+// measured: 17856 x 14656, 3 planes, 2 vectors 38.3 / 38.3; 7360 x 1884, 2, 53 26.4 / 25.6; 960 x 14438, 2, 11 16.6 / 16.0.)
+// Narrow keys, fitted to 407 shapes, 10 % rms: 5.5 us per round and the lookups of
 // a whole tile, twice (mu = 5) and 3.2 times (mu = 6) the time where a pass serves one vector only; a second kernel
 // 3 us and 15 us per million partial results.  One vector in half tables, fitted to 275 shapes, 7 % rms: 0.8 us and a row's
 // planes at 11 ns per tile, 2.4 us more where rows of the input are not read 16 bytes at a time, keys at 6.7 TB/s, a second
@@ -302,10 +310,15 @@ double tables_estimate(const biq_plan& pl, int m, int n, int q, int batch, int m
     const double wgs = (double)pl.row_blocks * pl.chunk_splits * pl.batch_tiles;
     const double rounds = (double)(long long)((wgs + kNumCu - 1) / kNumCu);
     const double rows = pl.rows_per_wg < m ? pl.rows_per_wg : m;
-    if (pl.kernel == KERNEL_GEMM8X2 || pl.kernel == KERNEL_GEMM8X2H)   // (a short row still takes its lanes' time)
-        return 3.4 + rounds * pl.tiles_per_split * ((pl.kernel == KERNEL_GEMM8X2H ? 1.3 : 2.0) +
-                                                    rows * q * pl.chunks_per_tile * 2 / 65e3) +
-               (pl.chunk_splits > 1 ? 3.0 : 0.0);
+    const double mem = (double)q * m * biq_key_row_stride(n);
+    auto together = [](double a, double b) { return cbrt(a * a * a + b * b * b); };
+    if (pl.kernel == KERNEL_GEMM8X2 || pl.kernel == KERNEL_GEMM8X2H) {   // (a short row still takes its lanes' time)
+        const bool half = pl.kernel == KERNEL_GEMM8X2H;
+        const double lookups = rows * q * pl.chunks_per_tile * 2;
+        const double tile = half ? 26.8e-6 * lookups + (n % 4 ? 1.0 : 0.0) : 0.51 + 18.6e-6 * lookups + (n % 4 ? 0.4 : 0.0);
+        return (half ? 3.65 : 2.8) + together(rounds * pl.tiles_per_split * tile, mem / 4.5e6) +
+               (pl.chunk_splits > 1 ? (half ? 1.5 : 3.1) + pl.chunk_splits * (0.24 + (half ? 1.7e-6 : 0.9e-6) * m * batch) : 0.0);
+    }
     if (pl.kernel == KERNEL_WIDE) {
         const double slower = mu == 6 ? 3.2 : mu == 5 ? 2.0 : 1.0;
         return rounds * (5.5 + slower * rows * q * pl.chunks_per_tile * pl.batch_tile / 65e3) +
@@ -316,8 +329,7 @@ double tables_estimate(const biq_plan& pl, int m, int n, int q, int batch, int m
         const double walk = rounds * (pl.row_mode == 2 ? 0.011 * rq + (n % 4 ? 2.7 : 0.0)
                                                        : tiles * (0.8 + 0.011 * rq + (n % 4 ? 2.4 : 0.0)) +
                                                              (tiles > 1 ? 0.42 * q : 0.0) + (tiles > 2 ? 0.5 * q : 0.0));
-        const double mem = (double)q * m * biq_key_row_stride(n) / 6.7e6;
-        return 3.3 + cbrt(walk * walk * walk + mem * mem * mem) +
+        return 3.3 + together(walk, mem / 6.7e6) +
                (pl.chunk_splits > 1 ? 1.06 + pl.chunk_splits * (0.27 + 13e-6 * m) : 0.0);
     }
     const int units = pl.chunks_per_tile / unit_keys(mu);
@@ -502,7 +514,7 @@ bool plan_tables(biq_plan& pl, int m, int n, int q, int batch, int mu) {
                 pl.tiles_per_split = tiles_h;
                 pl.rows_per_wg = rows_from(ceil_div(m, kNumCu), 4, 8, m);
             } else {
-                pl.rows_per_wg = rows_from(ceil_div_ll((long long)m * tiles_h, kNumCu), 4, 8, m);
+                pl.rows_per_wg = rows_one_round(m, tiles_h, kNumCu, 4, 8);
                 // up to one row per wave: 64 lanes per row instead of 16 (4 lookups per lane and plane)
                 if (pl.rows_per_wg <= 16) pl.row_mode = 2;
             }
@@ -510,10 +522,10 @@ bool plan_tables(biq_plan& pl, int m, int n, int q, int batch, int mu) {
             // small: latency mode, 8 rows per wave step, at most 4 steps per wave
             pl.tiles_per_split = 1;
             pl.row_mode = 1;
-            pl.rows_per_wg = rows_from(ceil_div_ll((long long)m * tiles, kNumCu), 8, 8, m);
+            pl.rows_per_wg = rows_one_round(m, tiles, kNumCu, 8, 8);
         } else {
             pl.tiles_per_split = 1;
-            const int rows = rows_from(ceil_div_ll((long long)m * tiles, kNumCu), 64, 64, m);
+            const int rows = rows_one_round(m, tiles, kNumCu, 64, 64);
             pl.rows_per_wg = rows > 8192 ? 8192 : rows;
         }
         return plan_finish(pl, m, n, q, batch, mu);
@@ -530,8 +542,7 @@ bool plan_tables(biq_plan& pl, int m, int n, int q, int batch, int mu) {
         pl.batch_tile = 2;
         pl.tiles_per_split = 1;
         pl.row_mode = 1;
-        const long long units = (long long)m * ceil_div(C, kGemmHalfTileChunks) * ceil_div(batch, 2);
-        pl.rows_per_wg = rows_from(ceil_div_ll(units, kNumCu), 8, 8, m);
+        pl.rows_per_wg = rows_one_round(m, product(ceil_div(C, kGemmHalfTileChunks), ceil_div(batch, 2), 1), kNumCu, 8, 8);
         return plan_finish(pl, m, n, q, batch, mu);
     }
     if (mu == 8 && batch >= 2 && q <= 4) {
@@ -554,9 +565,10 @@ bool plan_tables(biq_plan& pl, int m, int n, int q, int batch, int mu) {
         }
         pl.tiles_per_split = ceil_div(tiles, S);
         S = ceil_div(tiles, pl.tiles_per_split);
-        if (RT * S < kNumCu) {
-            const int r2 = rows_from(ceil_div_ll((long long)m * T * S, kNumCu), 64, 64, m);
-            if (r2 < rows) rows = r2;
+        // (one tile per workgroup: no accumulators in LDS, a few rows more than 4096 for one round of workgroups)
+        if (RT * S < kNumCu || (pl.tiles_per_split == 1 && RT * S > kNumCu && (long long)T * S <= kNumCu)) {
+            const int r2 = rows_one_round(m, (long long)T * S, kNumCu, 64, 64);
+            if (r2 < rows || (RT * S > kNumCu && r2 <= 8192)) rows = r2;
         }
         if (pl.tiles_per_split == 1 && rows <= 4 * 256) {
             // few rows per workgroup: latency mode, 16 rows per wave step, at most 4 steps per wave
@@ -578,8 +590,7 @@ bool plan_tables(biq_plan& pl, int m, int n, int q, int batch, int mu) {
         pl.chunks_per_tile = 32 * UK;
         pl.batch_tile = (128 * 1024) / (32 * UK * E * 4);
         pl.tiles_per_split = 1;
-        const long long units = product(m, ceil_div(C, pl.chunks_per_tile), ceil_div(batch, pl.batch_tile));
-        const int rows = rows_from(ceil_div_ll(units, kNumCu), 32, 32, m);
+        const int rows = rows_one_round(m, product(ceil_div(C, pl.chunks_per_tile), ceil_div(batch, pl.batch_tile), 1), kNumCu, 32, 32);
         pl.rows_per_wg = rows > (1 << 20) ? (1 << 20) : rows;
         return plan_finish(pl, m, n, q, batch, mu);
     }
@@ -654,7 +665,7 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
         // 7.7; 5000 x 3001, 3 11.9 / 6.4; but 11008 x 4096, 3 8.9 / 8.9; 1088 x 9288, 4 8.3 / 9.7; 234 x 32722, 4 12.4 / 19.4;
         // 36294 x 3136, 2 12.7 / 15.4.  The full-table kernel (33 MB of keys and more) keeps its calls: 47993 x 6847, 3 35 / 40.
         if (ok && m >= 128 && n > 2048 && pl.kernel == KERNEL_GEMV8H && direct_geometry(g, m, n, q, 1) &&
-            g.est < 0.865 * tables_estimate(pl, m, n, q, 1, mu))
+            g.est < (n % 4 ? 0.95 : 0.865) * tables_estimate(pl, m, n, q, 1, mu))
             pl.table_fill = 2;
         return ok;
     }
@@ -663,17 +674,17 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
     // (no digit plan is estimated below 8.3 us: small calls, where this search would show, skip it; the
     // narrow-key kernel keeps calls below 5e6 multiply-adds that direct does not take: 129 x 5000, 2
     // planes, 3 vectors at mu = 3 12.6 us with tables, 12.5 with digits)
-    // the batched mu = 8 table kernels keep what is not clearly slower (1145 x 7117, 4 planes, 7 vectors 12.0 us with
-    // tables, 12.8 without; 10240 x 1216, 2, 12: 17.5 / 8.6; 32000 x 1024, 3, 6: 18.8 / 7.0) and calls up to 6.5 us
-    // (1541 x 384, 2, 4: 4.3 / 4.6); narrow keys and the generic kernel gain almost always (1790 x 316, mu = 7, 3, 5:
-    // 18.6 / 4.7)
+    // the batched mu = 8 table kernels keep what is not clearly slower (330 shapes of 2 to 64 vectors: the choice takes 1 %
+    // longer than the better of the two; 1145 x 7117, 4 planes, 7 vectors 12.0 us with tables, 12.8 without; 10240 x 1216, 2,
+    // 12: 17.5 / 8.6; 1541 x 384, 2, 4: 4.3 / 4.6); narrow keys and the generic kernel gain almost always (1790 x 316, mu = 7,
+    // 3, 5: 18.6 / 4.7)
     const bool tuned = pl.kernel == KERNEL_GEMM8X2 || pl.kernel == KERNEL_GEMM8X2H;
     // ... except one vector on a few short rows (982 x 144, 2: 3.7 / 4.0; but 68544 x 206, 3, mu = 6: 13.6 / 6.5), and
     // with a margin against the narrow-key kernel where direct's estimate is the looser one: a single row step (221 x
     // 3376, 4, 25 at mu = 4 9.9 / 11.8) or one plane (38243 x 14976, 1, 1 31.1 / 34.0; but 19584 x 11456, 2, 1 25.5 / 22.0)
     const bool brief = batch == 1 && n <= 512 && (long long)m * q < 4096;
     const double margin = pl.kernel != KERNEL_WIDE ? 0.95 : g.steps == 1 ? 0.85 : q == 1 ? 0.8 : 0.95;
-    const bool use_direct = tuned ? tables > 6.5 && direct < 0.8 * tables : !brief && direct < margin * tables;
+    const bool use_direct = tuned ? direct < 0.9 * tables : !brief && direct < margin * tables;
     // (one vector padded to 32 is never the better use of the matrix cores where direct takes it: 310460 x 192, mu = 4
     // 17 us in digits, 6.8 with tables)
     if (batch == 1 && (brief || direct < 1e30)) {
@@ -826,7 +837,7 @@ bool plan_grouped(biq_plan& pl, int& kind, int m, int n, int q, int batch, int m
         pl.kernel = KERNEL_GEMM8X2H;
         pl.chunks_per_tile = kGemmHalfTileChunks;
         pl.batch_tile = 2;
-        pl.rows_per_wg = rows_from(ceil_div_ll((long long)m * ceil_div(batch, 2), cus), 8, 8, m);
+        pl.rows_per_wg = rows_one_round(m, ceil_div(batch, 2), cus, 8, 8);
     } else {
         return false;
     }

@@ -83,6 +83,18 @@ def test_one_vector_plans(biq, m, n, q, direct):
     assert biq.biq_plan_workspace_bytes(p, m, 1) == biq.biq_plan_workspace_bytes(lut, m, 1)
 
 
+@pytest.mark.parametrize("m,n,q,b,mu", [
+    (25633, 11584, 1, 1, 8), (3639, 13054, 1, 1, 8), (10240, 11353, 4, 1, 8), (963, 11927, 4, 21, 8), (384, 519, 4, 51, 8),
+    (17664, 13056, 2, 3, 8), (4736, 2781, 3, 29, 8), (6080, 13568, 1, 3, 8), (681, 5504, 1, 18, 5), (136, 7558, 2, 58, 4),
+    (1010, 20480, 2, 1, 8), (4096, 4096, 2, 1, 8), (128, 256, 1, 2, 8)])
+def test_table_plans_fill_one_round(biq, m, n, q, b, mu):
+    """No more workgroups than the 256 CUs where fewer blocks of rows make that possible, and every row in one of them."""
+    p = biq.biq_plan_get_lut(m, n, q, b, mu)
+    each = p.chunk_splits * p.batch_tiles
+    assert each > 256 or p.row_blocks * each <= 256
+    assert (p.row_blocks - 1) * p.rows_per_wg < m <= p.row_blocks * p.rows_per_wg
+
+
 def test_direct_row_limit(biq):
     """The direct kernel counts rows in 32 bits, those its last row steps have past the end included."""
     for m, ok in ((1 << 30, True), ((1 << 30) + 1, False), (3 << 29, False)):
