@@ -316,7 +316,8 @@ double tables_estimate(const biq_plan& pl, int m, int n, int q, int batch, int m
         const bool half = pl.kernel == KERNEL_GEMM8X2H;
         const double lookups = rows * q * pl.chunks_per_tile * 2;
         const double tile = half ? 26.8e-6 * lookups + (n % 4 ? 1.0 : 0.0) : 0.51 + 18.6e-6 * lookups + (n % 4 ? 0.4 : 0.0);
-        return (half ? 3.65 : 2.8) + together(rounds * pl.tiles_per_split * tile, mem / 4.5e6) +
+        const double turns = rounds * pl.tiles_per_split;    // (the first one's tables are built beside the dispatch)
+        return (half ? 3.65 : 2.8) + together(turns * tile + (turns - 1) * (half ? 1.3 : 1.5), mem / 4.5e6) +
                (pl.chunk_splits > 1 ? (half ? 1.5 : 3.1) + pl.chunk_splits * (0.24 + (half ? 1.7e-6 : 0.9e-6) * m * batch) : 0.0);
     }
     if (pl.kernel == KERNEL_WIDE) {
@@ -568,7 +569,7 @@ bool plan_tables(biq_plan& pl, int m, int n, int q, int batch, int mu) {
         // (one tile per workgroup: no accumulators in LDS, a few rows more than 4096 for one round of workgroups)
         if (RT * S < kNumCu || (pl.tiles_per_split == 1 && RT * S > kNumCu && (long long)T * S <= kNumCu)) {
             const int r2 = rows_one_round(m, (long long)T * S, kNumCu, 64, 64);
-            if (r2 < rows || (RT * S > kNumCu && r2 <= 8192)) rows = r2;
+            if (r2 < rows || (RT * S > kNumCu && r2 <= 8192 && r2 * (long long)biq_key_row_stride(n) < (1ll << 31))) rows = r2;
         }
         if (pl.tiles_per_split == 1 && rows <= 4 * 256) {
             // few rows per workgroup: latency mode, 16 rows per wave step, at most 4 steps per wave
@@ -1214,6 +1215,19 @@ biq_status biq_gemm_noalloc(const uint8_t* K, const float* alpha, const float* X
     if (need > kScratchBytes) {
         if (!plan_small_workspace(pl, m, n, q, batch, mu)) return BIQ_EWORKSPACE;   // use biq_gemm with a workspace
         need = plan_workspace(pl, m, batch);
+        // (where tables and digits are estimated close together, the one of them that fits)
+        biq_plan lut, digits;
+        double est;
+        if (need > kScratchBytes && q <= 4 && plan_digits(digits, m, n, q, batch, est) &&
+            plan_default(lut, m, n, q, batch, mu, true)) {
+            const double ratio = tables_estimate(lut, m, n, q, batch, mu) / est;
+            if (mu == 8 && ratio < 3.0 && plan_workspace(lut, m, batch) <= kScratchBytes) pl = lut;
+            else if (ratio > 0.3 && plan_workspace(digits, m, batch) <= kScratchBytes) pl = digits;
+            need = plan_workspace(pl, m, batch);
+        } else if (need > kScratchBytes && plan_unpack(digits, m, n, q, batch, mu, 3) && plan_workspace(digits, m, batch) <= kScratchBytes) {
+            pl = digits;                                  // (rows too long for digit plans)
+            need = plan_workspace(pl, m, batch);
+        }
         if (need > kScratchBytes) return BIQ_EWORKSPACE;
     }
     void* ws = nullptr;

@@ -22,3 +22,19 @@ def test_noalloc_takes_a_smaller_plan(oracle, m, n, q, b, mu):
     biq.biq_gemm_noalloc(K, ad, Xd, Y, m, n, q, b, mu)
     torch.cuda.synchronize()
     assert_within_tolerance(Y[:4].cpu().numpy(), oracle.gemm_dense(B, alpha, X[:4]), alpha, X[:4], "noalloc")
+
+
+@pytest.mark.parametrize("m,n,q,b,mu", [(20, 62289, 4, 193, 8), (16, 165265, 2, 82, 8)])
+def test_noalloc_few_rows(oracle, m, n, q, b, mu):
+    """Few rows of many columns: where the fitting plan is the table kernels', whose partial sums are small."""
+    import torch
+
+    import paper_2005_09904_amd as biq
+
+    print("noalloc m=%d n=%d q=%d b=%d mu=%d" % (m, n, q, b, mu), flush=True)
+    B, alpha, X = _inputs(m, n, q, b, 78)
+    Bd, ad, Xd = device_inputs(B, alpha, X)
+    Y = torch.full((b, m), float("nan"), dtype=torch.float32, device="cuda")
+    biq.biq_gemm_noalloc(gpu_pack(biq, Bd), ad, Xd, Y, m, n, q, b, mu)
+    torch.cuda.synchronize()
+    assert_within_tolerance(Y[:4].cpu().numpy(), oracle.gemm_dense(B, alpha, X[:4]), alpha, X[:4], "noalloc")
