@@ -459,6 +459,12 @@ bool plan_digits(biq_plan& pl, int m, int n, int q, int batch, double& est) {
     return best < 1e30 && plan_finish(pl, m, n, q, batch, 8);
 }
 
+// Estimated time (us) of a matrix product in three 16-bit terms: 2 * 3 flop per weight and padded input vector at 1.45e9
+// flop/us.
+double three_terms_estimate(int m, int n, int q, int batch) {
+    return 10.0 + 6.0 * ((double)q * m * n) * (ceil_div(batch, 32) * 32.0) / 1.45e9;
+}
+
 // Default mapping.  Algorithm 2 leaves the tile sizes open; the choices here are:
 //  - batch tile: as many input vectors as one lookup can serve with a single wide LDS read
 //  - tile width: the largest power-of-two number of key units whose tables fit the LDS budget
@@ -697,10 +703,8 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
         biq_plan d;
         double est;
         if (!plan_digits(d, m, n, q, batch, est)) {
-            // rows too long for those plans: the exact three-term split, 2 * 3 flop per weight and padded
-            // input vector at 1.45e9 flop/us
-            est = 10.0 + 6.0 * ((double)q * m * n) * (ceil_div(batch, 32) * 32.0) / 1.45e9;
-            if (est < few && plan_unpack(d, m, n, q, batch, mu, 3)) {
+            // rows too long for those plans: the exact three-term split
+            if (three_terms_estimate(m, n, q, batch) < few && plan_unpack(d, m, n, q, batch, mu, 3)) {
                 pl = d;
                 return true;
             }
@@ -1019,15 +1023,31 @@ biq_status unpack_keys_any(const uint8_t* K, KEY* keys, int m, int n, int q, int
 // The plan of biq_gemm_noalloc where the digit plan does not fit its buffer (digits and partial sums of
 // wide batches): the tables, or - where a three-term matrix product is faster than they are - that one, from
 // lookups/s (13e12 for the conflict-free kernels, 6.5e12 and no more than 0.25 TB/s of keys for the generic
-// one, plus 6 us) against 2 * 3 flop per weight and padded vector at 1.45e15 flop/s plus 10 us.
+// one, plus 6 us).
 bool plan_small_workspace(biq_plan& pl, int m, int n, int q, int batch, int mu) {
     const double weights = (double)q * m * n;
     const bool tuned = mu == 8 || mu <= 5 || (mu == 6 && batch <= 4);
-    double t_lut = weights / mu * batch / (tuned ? 13e12 : 6.5e12);
-    if (!tuned && t_lut < weights / 8 / 0.25e12) t_lut = weights / 8 / 0.25e12;
-    const double t_mfma = 10e-6 + 6.0 * weights * (ceil_div(batch, 32) * 32.0) / 1.45e15;
-    if (q <= 4 && t_mfma < t_lut + 6e-6) return plan_unpack(pl, m, n, q, batch, mu, 3);
+    double t_lut = weights / mu * batch / (tuned ? 13e6 : 6.5e6);
+    if (!tuned && t_lut < weights / 8 / 0.25e6) t_lut = weights / 8 / 0.25e6;
+    if (q <= 4 && three_terms_estimate(m, n, q, batch) < t_lut + 6.0) return plan_unpack(pl, m, n, q, batch, mu, 3);
     return plan_default(pl, m, n, q, batch, mu, true);
+}
+// ... and where that one does not fit either: of the tables' plan and the matrix cores' (digits; three terms for rows too long
+// for those) the one that fits, the faster one by the estimates if both do.  Many vectors on the tables, which often need
+// no workspace at all, are left to the caller from kNoallocSlower times the matrix cores' time on: biq_gemm with a
+// workspace is the better call, and BIQ_EWORKSPACE says so (16384 x 16384, 2 planes, 512 vectors: 6.4 times).
+constexpr double kNoallocSlower = 4.0;
+bool plan_fitting(biq_plan& pl, int m, int n, int q, int batch, int mu, size_t limit) {
+    biq_plan lut, cores;
+    double t_cores = 1e300;
+    const bool have_lut = plan_default(lut, m, n, q, batch, mu, true);
+    if (!plan_digits(cores, m, n, q, batch, t_cores))
+        t_cores = plan_unpack(cores, m, n, q, batch, mu, 3) ? three_terms_estimate(m, n, q, batch) : 1e300;
+    const double t_lut = have_lut ? tables_estimate(lut, m, n, q, batch, mu) : 1e300;
+    const bool cores_fit = t_cores < 1e300 && plan_workspace(cores, m, batch) <= limit;
+    const bool lut_fits = have_lut && plan_workspace(lut, m, batch) <= limit && t_lut < kNoallocSlower * t_cores;
+    pl = cores_fit && (!lut_fits || t_cores < t_lut) ? cores : lut;
+    return cores_fit || lut_fits;
 }
 
 // Workspace of biq_gemm_noalloc: device memory that belongs to the library's code object, one
@@ -1213,22 +1233,10 @@ biq_status biq_gemm_noalloc(const uint8_t* K, const float* alpha, const float* X
     if (!plan_default(pl, m, n, q, batch, mu, false)) return BIQ_EUNSUPPORTED;
     size_t need = plan_workspace(pl, m, batch);
     if (need > kScratchBytes) {
-        if (!plan_small_workspace(pl, m, n, q, batch, mu)) return BIQ_EWORKSPACE;   // use biq_gemm with a workspace
+        if ((!plan_small_workspace(pl, m, n, q, batch, mu) || plan_workspace(pl, m, batch) > kScratchBytes) &&
+            !plan_fitting(pl, m, n, q, batch, mu, kScratchBytes))
+            return BIQ_EWORKSPACE;                        // use biq_gemm with a workspace
         need = plan_workspace(pl, m, batch);
-        // (where tables and digits are estimated close together, the one of them that fits)
-        biq_plan lut, digits;
-        double est;
-        if (need > kScratchBytes && q <= 4 && plan_digits(digits, m, n, q, batch, est) &&
-            plan_default(lut, m, n, q, batch, mu, true)) {
-            const double ratio = tables_estimate(lut, m, n, q, batch, mu) / est;
-            if (mu == 8 && ratio < 3.0 && plan_workspace(lut, m, batch) <= kScratchBytes) pl = lut;
-            else if (ratio > 0.3 && plan_workspace(digits, m, batch) <= kScratchBytes) pl = digits;
-            need = plan_workspace(pl, m, batch);
-        } else if (need > kScratchBytes && plan_unpack(digits, m, n, q, batch, mu, 3) && plan_workspace(digits, m, batch) <= kScratchBytes) {
-            pl = digits;                                  // (rows too long for digit plans)
-            need = plan_workspace(pl, m, batch);
-        }
-        if (need > kScratchBytes) return BIQ_EWORKSPACE;
     }
     void* ws = nullptr;
     if (need > 0 && scratch_address(&ws) != hipSuccess) return BIQ_EHIP;
