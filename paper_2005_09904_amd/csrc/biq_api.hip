@@ -16,6 +16,7 @@
 #include "biq_grouped.h"
 #include "biq_digit_mfma.h"
 #include "biq_direct.h"
+#include "biq_direct_rule.h"
 #include "biq_gather.h"
 
 namespace {
@@ -25,6 +26,7 @@ using namespace biq;
 // gfx950 (MI355X) limits the planner is written for.
 constexpr int kLdsTableBudget = 128 * 1024;  // tables of one tile (leaves room for 1 WG/CU extras)
 constexpr int kNumCu = 256;
+static_assert(kDirectCus == kNumCu && kDirectLds == kLdsPerCu, "as biq_direct_rule.h counts them");
 constexpr int kNumXcd = 8;
 
 enum KernelId { KERNEL_GENERIC = 0, KERNEL_GEMV8 = 1, KERNEL_GEMM8X2 = 2, KERNEL_UNPACK_MFMA = 3, KERNEL_GEMV8H = 4, KERNEL_GEMM8X2H = 5, KERNEL_WIDE = 6, KERNEL_COUNT };
@@ -130,91 +132,6 @@ inline int plan_lds_bytes(const biq_plan& pl, int mu) {
     long long b = (long long)pl.chunks_per_tile * (1 << mu) * pl.batch_tile * 4;
     if (pl.tiles_per_split > 1) b += (long long)pl.rows_per_wg * pl.batch_tile * 4;
     return b > (1ll << 30) ? (1 << 30) : (int)b;
-}
-
-// Mapping of the direct kernel (biq_direct.h) for a shape, with its estimated time (us); false if its
-// operands do not fit the LDS.  Candidates: the many-rows instantiation, and one row tile per wave with 1 .. 8
-// groups of waves along the row; as many row steps per workgroup as leave at most 256 workgroups.  A row step costs
-// its chunks (matrix pipe, expansion or LDS of the two waves per SIMD, or the latency of the next keys) and an
-// epilogue; keys stream at 3.3 TB/s; the split of the inputs 1.9 us per 512 blocks.  Fitted to 94 random
-// shapes (128 .. 280000 rows, 128 .. 16000 columns, 1 .. 48 vectors): 13 % rms; one vector on more than 2048 columns to
-// 2300 times of 298 shapes: 7 % rms, the mapping chosen 0.2 % slower in the mean than the best.  The estimate handed on
-// (not the choice of the mapping) has at least 0.85 us per row step where there are several: a step waits for its scales,
-// and short rows have nothing else to do meanwhile (1025348 x 111, 1 plane, 1 vector: 16 us without, measured 34).  All
-// are 8 % below what a replayed graph takes with keys from memory.
-struct DirectGeom {
-    int vecs, batch_tiles, chunks, ksplit, steps, row_blocks, lds;
-    int uc;                  // chunks requested together
-    int kind;                // DirectKind
-    double est;
-};
-// Input vectors of one workgroup whose digits fit the LDS beside the exchange buffers.
-int direct_max_vectors(int n) {
-    const long long spare = kLdsPerCu - 2 * kDirectWaves * 15 * 16 * 4;
-    const long long v = spare / direct_lds_bytes(ceil_div(n, 512), 1, 1, false);
-    return (int)(v < kDirectMaxVec ? v : kDirectMaxVec);
-}
-bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
-    if (q > 4 || biq_key_row_stride(n) > (1u << 26)) return false;
-    if (m > (1 << 30)) return false;                 // rows past the end of the last workgroup's steps stay in 32 bits
-    const long long chunks = ceil_div(n, 512);
-    const int vmax = direct_max_vectors(n);
-    if (vmax == 0) return false;
-    g.chunks = (int)chunks;
-    g.batch_tiles = ceil_div(batch, vmax);
-    g.vecs = ceil_div(batch, g.batch_tiles);
-    g.batch_tiles = ceil_div(batch, g.vecs);
-    if (g.batch_tiles > 65535) return false;
-    const int nt = ceil_div(g.vecs, 3);
-    double best = 1e30;
-    for (int kind : {DIRECT_MANY, DIRECT_LINES, DIRECT_FEW}) {
-        if (!direct_has_kind(kind, q, nt)) continue;
-        const int rpw = kind == DIRECT_MANY ? direct_rpw(q, nt) : 1, uc = kind == DIRECT_FEW ? 1 : direct_uc(nt);
-        // one vector on wide rows: costs of their own, and beyond 256 row tiles several groups of waves along whole lines,
-        // too (332 shapes: up to there those take 1.01 to 1.2 times as long, 0.97 with four row steps and 0.84 with five
-        // and more; with 2 to 6 vectors, 110 shapes, 1 % less at most)
-        const bool one = batch == 1 && n > 2048 && kind != DIRECT_MANY;
-        if (kind == DIRECT_LINES && (one ? m <= 16 * kNumCu : direct_rpw(q, nt) > 1)) continue;
-        const double rate = !one ? 3.3e6 : uc == 2 ? 4.35e6 : 3.72e6;
-        const double mem = (double)q * m * biq_key_row_stride(n) * g.batch_tiles / rate;
-        for (int ks = 1; ks <= (kind == DIRECT_FEW || (one && uc == 2) ? kDirectWaves : 1) && (ks - 1) * uc < g.chunks; ks *= 2) {
-            const long long all_steps = ceil_div(m, kDirectWaves / ks * rpw * 16);
-            long long steps = ceil_div_ll(all_steps * g.batch_tiles, kNumCu);
-            if (steps > all_steps) steps = all_steps;
-            const double rounds = (double)ceil_div_ll(ceil_div_ll(all_steps, steps) * g.batch_tiles, kNumCu);
-            const int rt = q * rpw, upg = ceil_div(ceil_div(g.chunks, uc), ks);
-            double clk, row_step, before;                // a chunk; the rest of a row step; what comes ahead of the first
-            if (one) {
-                clk = 727.0 * q;
-                const double least = uc == 2 ? 818.0 : 1132.0;
-                if (clk < least) clk = least;
-                row_step = ks > 1 ? 0.57 : 0.53;
-                before = 2.54 + 1.87 * g.chunks / (4 * kDirectWaves);
-            } else {
-                clk = 22.0 * rt * (16 * nt > 32 ? 16 * nt : 32);
-                if (clk < 860.0 * nt) clk = 860.0 * nt;
-                row_step = 0.012 * rt * nt + (ks > 1 ? 0.36 : 0.0);
-                before = 1.3 + 0.36 * (nt - 1) + 1.94 * rounds * ceil_div(g.chunks * g.vecs, 4 * kDirectWaves);
-            }
-            double work = rounds * steps * (upg * uc * clk / 2200.0 + row_step);
-            // (both together, smoothly: of two mappings that memory bounds, the one with less work)
-            const double t = before + cbrt(work * work * work + mem * mem * mem);
-            if (t < best) {
-                best = g.est = t;
-                if (steps > 1 && work < 0.85 * rounds * steps) {
-                    work = 0.85 * rounds * steps;
-                    g.est = before + cbrt(work * work * work + mem * mem * mem);
-                }
-                g.kind = kind;
-                g.ksplit = ks;
-                g.uc = uc;
-                g.steps = (int)steps;
-                g.row_blocks = (int)ceil_div_ll(all_steps, steps);
-            }
-        }
-    }
-    g.lds = (int)direct_lds_bytes(g.chunks, g.vecs, 1, g.ksplit > 1);
-    return best < 1e30;
 }
 
 // Completes the derived fields and checks a plan against the shape and device limits.

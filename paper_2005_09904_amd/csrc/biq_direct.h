@@ -41,22 +41,11 @@
 #pragma once
 
 #include "biq_digit_mfma.h"
+#include "biq_direct_rule.h"
 
 namespace biq {
 
-constexpr int kDirectThreads = 512;
-constexpr int kDirectWaves = kDirectThreads / 64;
-constexpr int kDirectMaxVec = 15;                 // vectors of a workgroup: five column tiles
-// The mappings: one row tile per wave and one chunk at a time (few rows); one row tile and two chunks requested
-// together, 128 bytes per row: a whole line (lines); more row tiles per wave, which share a step's operands in LDS, and
-// two chunks where the registers hold them beside RT x NT accumulators (many rows).
-enum DirectKind { DIRECT_FEW, DIRECT_MANY, DIRECT_LINES };
-constexpr int direct_rpw(int q, int nt) { return q == 1 ? (nt <= 2 ? 4 : 2) : q == 2 && nt <= 3 ? 2 : 1; }
-constexpr int direct_uc(int nt) { return nt <= 2 ? 2 : 1; }
-constexpr bool direct_has_kind(int kind, int q, int nt) {
-    return kind == DIRECT_FEW || (kind == DIRECT_MANY ? direct_rpw(q, nt) > 1
-                                                      : nt == 1 || (direct_rpw(q, nt) == 1 && direct_uc(nt) == 2));
-}
+static_assert(kDirectDigits == kDigits && kDirectWaves * 64 == kDirectThreads, "as the rule counts them");
 
 struct DirectParams {
     const uint8_t* K;        // [q][m][stride]
@@ -72,13 +61,6 @@ struct DirectParams {
     int units_per_group;     // units (UC chunks) of a group
     int steps;               // row steps of a workgroup; a step = (8 / ksplit) * RPW * 16 rows
 };
-
-inline long long direct_lds_bytes(long long chunks, int vecs, int rpw, bool exchange) {
-    const long long blocks = chunks * 16;
-    // digits, scale bytes, partial results of the waves (two buffers)
-    return (blocks * kDigits * 24 + 8) * vecs + blocks * vecs +
-           (exchange ? 2 * kDirectWaves * rpw * ((vecs + 2) / 3) * 3 * 16 * 4 : 0);
-}
 
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // 128-bit access, any float address
 typedef float f32x4v __attribute__((ext_vector_type(4)));

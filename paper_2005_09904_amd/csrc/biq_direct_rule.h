@@ -1,0 +1,123 @@
+// The mapping of the direct kernel (biq_direct.h) for a shape and its estimated time (plain C++: no kernel code).
+#pragma once
+
+#include <math.h>
+
+#include <initializer_list>
+
+namespace biq {
+
+constexpr int kDirectThreads = 512;
+constexpr int kDirectWaves = kDirectThreads / 64;
+constexpr int kDirectDigits = 5;                  // of an input element
+constexpr int kDirectCus = 256;
+constexpr int kDirectLds = 160 * 1024;            // of a CU, the most a workgroup can ask for
+constexpr int kDirectMaxVec = 15;                 // vectors of a workgroup: five column tiles
+// The mappings: one row tile per wave and one chunk at a time (few rows); one row tile and two chunks requested
+// together, 128 bytes per row: a whole line (lines); more row tiles per wave, which share a step's operands in LDS, and
+// two chunks where the registers hold them beside RT x NT accumulators (many rows).
+enum DirectKind { DIRECT_FEW, DIRECT_MANY, DIRECT_LINES };
+constexpr int direct_rpw(int q, int nt) { return q == 1 ? (nt <= 2 ? 4 : 2) : q == 2 && nt <= 3 ? 2 : 1; }
+constexpr int direct_uc(int nt) { return nt <= 2 ? 2 : 1; }
+constexpr bool direct_has_kind(int kind, int q, int nt) {
+    return kind == DIRECT_FEW || (kind == DIRECT_MANY ? direct_rpw(q, nt) > 1
+                                                      : nt == 1 || (direct_rpw(q, nt) == 1 && direct_uc(nt) == 2));
+}
+
+// quotients rounded up (a >= 0, b >= 1)
+inline int direct_div(int a, int b) { return (int)(((unsigned)a + (unsigned)b - 1u) / (unsigned)b); }
+inline long long direct_div_ll(long long a, long long b) { return (a + b - 1) / b; }
+inline unsigned direct_row_bytes(int n) { return (unsigned)direct_div(n, 128) * 16u; }   // keys of a row
+
+inline long long direct_lds_bytes(long long chunks, int vecs, int rpw, bool exchange) {
+    const long long blocks = chunks * 16;
+    // digits, scale bytes, partial results of the waves (two buffers)
+    return (blocks * kDirectDigits * 24 + 8) * vecs + blocks * vecs +
+           (exchange ? 2 * kDirectWaves * rpw * ((vecs + 2) / 3) * 3 * 16 * 4 : 0);
+}
+
+// Mapping of the direct kernel (biq_direct.h) for a shape, with its estimated time (us); false if its
+// operands do not fit the LDS.  Candidates: the many-rows instantiation, and one row tile per wave with 1 .. 8
+// groups of waves along the row; as many row steps per workgroup as leave at most 256 workgroups.  A row step costs
+// its chunks (matrix pipe, expansion or LDS of the two waves per SIMD, or the latency of the next keys) and an
+// epilogue; keys stream at 3.3 TB/s; the split of the inputs 1.9 us per 512 blocks.  Fitted to 94 random
+// shapes (128 .. 280000 rows, 128 .. 16000 columns, 1 .. 48 vectors): 13 % rms; one vector on more than 2048 columns to
+// 2300 times of 298 shapes: 7 % rms, the mapping chosen 0.2 % slower in the mean than the best.  The estimate handed on
+// (not the choice of the mapping) has at least 0.85 us per row step where there are several: a step waits for its scales,
+// and short rows have nothing else to do meanwhile (1025348 x 111, 1 plane, 1 vector: 16 us without, measured 34).  All
+// are 8 % below what a replayed graph takes with keys from memory.
+struct DirectGeom {
+    int vecs, batch_tiles, chunks, ksplit, steps, row_blocks, lds;
+    int uc;                  // chunks requested together
+    int kind;                // DirectKind
+    double est;
+};
+// Input vectors of one workgroup whose digits fit the LDS beside the exchange buffers.
+inline int direct_max_vectors(int n) {
+    const long long spare = kDirectLds - 2 * kDirectWaves * 15 * 16 * 4;
+    const long long v = spare / direct_lds_bytes(direct_div(n, 512), 1, 1, false);
+    return (int)(v < kDirectMaxVec ? v : kDirectMaxVec);
+}
+inline bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
+    if (q > 4 || direct_row_bytes(n) > (1u << 26)) return false;
+    if (m > (1 << 30)) return false;                 // rows past the end of the last workgroup's steps stay in 32 bits
+    const int vmax = direct_max_vectors(n);
+    if (vmax == 0) return false;
+    g.chunks = direct_div(n, 512);
+    g.batch_tiles = direct_div(batch, vmax);
+    g.vecs = direct_div(batch, g.batch_tiles);
+    g.batch_tiles = direct_div(batch, g.vecs);
+    if (g.batch_tiles > 65535) return false;
+    const int nt = direct_div(g.vecs, 3);
+    double best = 1e30;
+    for (int kind : {DIRECT_MANY, DIRECT_LINES, DIRECT_FEW}) {
+        if (!direct_has_kind(kind, q, nt)) continue;
+        const int rpw = kind == DIRECT_MANY ? direct_rpw(q, nt) : 1, uc = kind == DIRECT_FEW ? 1 : direct_uc(nt);
+        // one vector on wide rows: costs of their own, and beyond 256 row tiles several groups of waves along whole lines,
+        // too (332 shapes: up to there those take 1.01 to 1.2 times as long, 0.97 with four row steps and 0.84 with five
+        // and more; with 2 to 6 vectors, 110 shapes, 1 % less at most)
+        const bool one = batch == 1 && n > 2048 && kind != DIRECT_MANY;
+        if (kind == DIRECT_LINES && (one ? m <= 16 * kDirectCus : direct_rpw(q, nt) > 1)) continue;
+        const double rate = !one ? 3.3e6 : uc == 2 ? 4.35e6 : 3.72e6;
+        const double mem = (double)q * m * direct_row_bytes(n) * g.batch_tiles / rate;
+        for (int ks = 1; ks <= (kind == DIRECT_FEW || (one && uc == 2) ? kDirectWaves : 1) && (ks - 1) * uc < g.chunks; ks *= 2) {
+            const long long all_steps = direct_div(m, kDirectWaves / ks * rpw * 16);
+            long long steps = direct_div_ll(all_steps * g.batch_tiles, kDirectCus);
+            if (steps > all_steps) steps = all_steps;
+            const double rounds = (double)direct_div_ll(direct_div_ll(all_steps, steps) * g.batch_tiles, kDirectCus);
+            const int rt = q * rpw, upg = direct_div(direct_div(g.chunks, uc), ks);
+            double clk, row_step, before;                // a chunk; the rest of a row step; what comes ahead of the first
+            if (one) {
+                clk = 727.0 * q;
+                const double least = uc == 2 ? 818.0 : 1132.0;
+                if (clk < least) clk = least;
+                row_step = ks > 1 ? 0.57 : 0.53;
+                before = 2.54 + 1.87 * g.chunks / (4 * kDirectWaves);
+            } else {
+                clk = 22.0 * rt * (16 * nt > 32 ? 16 * nt : 32);
+                if (clk < 860.0 * nt) clk = 860.0 * nt;
+                row_step = 0.012 * rt * nt + (ks > 1 ? 0.36 : 0.0);
+                before = 1.3 + 0.36 * (nt - 1) + 1.94 * rounds * direct_div(g.chunks * g.vecs, 4 * kDirectWaves);
+            }
+            double work = rounds * steps * (upg * uc * clk / 2200.0 + row_step);
+            // (both together, smoothly: of two mappings that memory bounds, the one with less work)
+            const double t = before + cbrt(work * work * work + mem * mem * mem);
+            if (t < best) {
+                best = g.est = t;
+                if (steps > 1 && work < 0.85 * rounds * steps) {
+                    work = 0.85 * rounds * steps;
+                    g.est = before + cbrt(work * work * work + mem * mem * mem);
+                }
+                g.kind = kind;
+                g.ksplit = ks;
+                g.uc = uc;
+                g.steps = (int)steps;
+                g.row_blocks = (int)direct_div_ll(all_steps, steps);
+            }
+        }
+    }
+    g.lds = (int)direct_lds_bytes(g.chunks, g.vecs, 1, g.ksplit > 1);
+    return best < 1e30;
+}
+
+}  // namespace biq

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 from gpu_util import assert_within_tolerance, device_inputs, gpu_pack
+from test_direct_rule import WIDE_ROWS
 
 pytestmark = pytest.mark.gpu
 
@@ -76,13 +77,7 @@ def test_direct_parity(biq, oracle, m, n, q, b, mu):
     assert np.all(np.abs(Y[:, rows] - ref).max(axis=1) <= _bound(alpha[:, rows], X))
 
 
-@pytest.mark.parametrize("m,n,q", [
-    # whole lines of keys, 1 .. 8 groups of waves along the row; even and odd numbers of chunks, a last row tile of one row
-    # and a last row step that only some workgroups have
-    (16763, 2153, 3), (16513, 2590, 1), (8399, 2083, 1), (8677, 2591, 4), (4222, 3086, 1), (4193, 3772, 2), (8290, 7253, 2),
-    (8427, 15021, 1), (4097, 2049, 3),
-    # ... and one chunk at a time, up to 256 row tiles
-    (4096, 2049, 1), (4081, 4096, 2), (257, 5951, 3), (128, 2052, 4)])
+@pytest.mark.parametrize("m,n,q", [w[:3] for w in WIDE_ROWS])
 def test_one_vector_on_wide_rows(biq, oracle, m, n, q):
     """The mappings of one vector beyond the table workgroups' rows: against the oracle, and against the table kernels."""
     import torch
