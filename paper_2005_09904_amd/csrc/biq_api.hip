@@ -215,9 +215,9 @@ bool plan_finish(biq_plan& pl, int m, int n, int q, int batch, int mu) {
 // tables 5 %): per round of workgroups over the CUs and tile the lookups of its rows and two input vectors, more where rows
 // of the input are not read 16 bytes at a time, keys at 4.5 TB/s, a second kernel with 0.24 us per split.  (Estimated /
 // measured: 17856 x 14656, 3 planes, 2 vectors 38.3 / 38.3; 7360 x 1884, 2, 53 26.4 / 25.6; 960 x 14438, 2, 11 16.6 / 16.0.)
-// Narrow keys, fitted to 407 shapes, 10 % rms: 5.5 us per round and the lookups of
-// a whole tile, twice (mu = 5) and 3.2 times (mu = 6) the time where a pass serves one vector only; a second kernel
-// 3 us and 15 us per million partial results.  One vector in half tables, fitted to 275 shapes, 7 % rms: 0.8 us and a row's
+// Narrow keys, fitted to 319 shapes, 9 % rms: 5.1 us per round and the lookups of
+// a whole tile, 2.9 (mu = 5) and 4.1 times (mu = 6) the time where a pass serves one vector only; a second kernel
+// 3.3 us and 9 us per million partial results.  One vector in half tables, fitted to 275 shapes, 7 % rms: 0.8 us and a row's
 // planes at 11 ns per tile, 2.4 us more where rows of the input are not read 16 bytes at a time, keys at 6.7 TB/s, a second
 // kernel 1 us, 0.27 us per split and 13 us per million partial results.  The generic kernel: 6.5e12 lookups/s, keys at no more than 0.25 TB/s,
 // and 0.4 us per partial result a second kernel adds (320 x 12288, mu = 7, 4, 24: 38 / 33) - but one vector on rows of
@@ -238,9 +238,9 @@ double tables_estimate(const biq_plan& pl, int m, int n, int q, int batch, int m
                (pl.chunk_splits > 1 ? (half ? 1.5 : 3.1) + pl.chunk_splits * (0.24 + (half ? 1.7e-6 : 0.9e-6) * m * batch) : 0.0);
     }
     if (pl.kernel == KERNEL_WIDE) {
-        const double slower = mu == 6 ? 3.2 : mu == 5 ? 2.0 : 1.0;
-        return rounds * (5.5 + slower * rows * q * pl.chunks_per_tile * pl.batch_tile / 65e3) +
-               (pl.chunk_splits > 1 ? 3.0 + 15e-6 * pl.chunk_splits * (double)m * batch : 0.0);
+        const double slower = mu == 6 ? 4.1 : mu == 5 ? 2.9 : mu == 4 ? 1.14 : 1.0;
+        return rounds * (5.1 + slower * rows * q * pl.chunks_per_tile * pl.batch_tile / 65e3) +
+               (pl.chunk_splits > 1 ? 3.3 + 8.7e-6 * pl.chunk_splits * (double)m * batch : 0.0);
     }
     if (pl.kernel == KERNEL_GEMV8H) {
         const double rq = rows * q, tiles = pl.tiles_per_split;
@@ -332,6 +332,9 @@ bool plan_unpack(biq_plan& pl, int m, int n, int q, int batch, int mu, int terms
 // (50.0 instead of 48.1; with fewer than eight tiles per wave 10-25 %): they are chosen for eight tiles and long rows.
 // On 90 shapes (128 .. 16384 columns, 14 .. 256 vectors) the choice is 2.3 % (fp32) and 2.5 % (bf16 values) slower
 // than the fastest of up to 36 mappings on average, 19 % at most (one row step more or less of a short row).
+// The estimate handed on has constants of its own for keys from memory, fitted to 1630 shapes of 2 .. 256 vectors near the
+// crossovers: 6 % rms (with the constants that rank the mappings 13 %: from 0.85 of the time for one key group per wave to 1.3
+// for sixteen).
 bool plan_digits(biq_plan& pl, int m, int n, int q, int batch, double& est) {
     double best = 1e30;
     est = 1e30;
@@ -366,7 +369,10 @@ bool plan_digits(biq_plan& pl, int m, int n, int q, int batch, double& est) {
                     const double rank = ct == 1 ? t : tiles < kDigitMaxTiles ? 1.05 * t : gpw >= 6 ? 0.99 * t : t;
                     if (rank < best) {
                         best = rank;
-                        est = t;
+                        // (what a call takes with its keys from memory)
+                        const double cold = step < 620.0 ? 620.0 : step;
+                        est = 5.9 + 0.97 * bpad_mb * n + rounds * (4.0 * gpw * cold / 1470.0 + 0.23 * tiles) + 0.8e-6 * m * (double)batch +
+                              (S > 1 ? 2.3 + 0.62 * (S + 1.0) * bpad_mb * m : 0.0);
                         pl.batch_tile = bt;
                         pl.wave_splits = ws;
                         pl.rows_per_wg = rows;
@@ -595,20 +601,18 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
     }
     const double tables = ok ? tables_estimate(pl, m, n, q, batch, mu) : 1e30;
     const double direct = ok && m >= 128 && direct_geometry(g, m, n, q, batch) ? g.est : 1e30;
-    // (no digit plan is estimated below 8.3 us: small calls, where this search would show, skip it; the
-    // narrow-key kernel keeps calls below 5e6 multiply-adds that direct does not take: 129 x 5000, 2
-    // planes, 3 vectors at mu = 3 12.6 us with tables, 12.5 with digits)
-    // the batched mu = 8 table kernels keep what is not clearly slower (330 shapes of 2 to 64 vectors: the choice takes 1 %
-    // longer than the better of the two; 1145 x 7117, 4 planes, 7 vectors 12.0 us with tables, 12.8 without; 10240 x 1216, 2,
-    // 12: 17.5 / 8.6; 1541 x 384, 2, 4: 4.3 / 4.6); narrow keys and the generic kernel gain almost always (1790 x 316, mu = 7,
-    // 3, 5: 18.6 / 4.7)
-    const bool tuned = pl.kernel == KERNEL_GEMM8X2 || pl.kernel == KERNEL_GEMM8X2H;
-    // ... except one vector on a few short rows (982 x 144, 2: 3.7 / 4.0; but 68544 x 206, 3, mu = 6: 13.6 / 6.5), and
-    // with a margin against the narrow-key kernel where direct's estimate is the looser one: a single row step (221 x
-    // 3376, 4, 25 at mu = 4 9.9 / 11.8) or one plane (38243 x 14976, 1, 1 31.1 / 34.0; but 19584 x 11456, 2, 1 25.5 / 22.0)
+    // The one estimated faster; direct's errors are also the smaller ones (5-8e-8 against 1.0-1.3e-7), so it has the ties.  The
+    // generic kernel's estimate is the looser one, and misses on the low side: it keeps what it wins clearly, but one vector on rows
+    // of up to 128 columns, where direct's is 20 % low (80000 x 128, mu = 7, 1 plane 4.4 us tables / 5.9 direct).  Not for one vector
+    // on a few short rows (982 x 144, 2: 3.7 / 4.0; but 68544 x 206, 3, mu = 6: 13.6 / 6.5).  3700 shapes of 2 .. 256 vectors,
+    // mu = 8, drawn as in use and up to 5e7 operations: 0.6 % slower in the mean than the best of tables, direct and digits, 0.9 % of
+    // them by more than 10 %; 700 with other mu 0.5 %, none by more than 10 %.  Tables / direct: 1145 x 7117, 4, 7 12.2 / 12.7;
+    // 919 x 832, 3, 9 4.6 / 6.5; 1541 x 384, 2, 4 4.4 / 4.6; 512 x 512, 2, 2 4.3 / 3.8; 1024 x 512, 2, 3 4.5 / 3.9; 1536 x 128, 2, 3
+    // 4.3 / 3.8; 2048 x 1024, 2, 4 4.3 / 5.4; 10240 x 1216, 2, 12 12.4 / 8.8; 1088 x 510, 2, 181 7.7 / 6.8; mu = 7: 1790 x 316, 3, 5
+    // 18.6 / 4.7; mu = 4: 458 x 2061, 3, 15 7.9 / 11.5; 38243 x 14976, 1, 1 35.0 / 27.9.
     const bool brief = batch == 1 && n <= 512 && (long long)m * q < 4096;
-    const double margin = pl.kernel != KERNEL_WIDE ? 0.95 : g.steps == 1 ? 0.85 : q == 1 ? 0.8 : 0.95;
-    const bool use_direct = tuned ? direct < 0.9 * tables : !brief && direct < margin * tables;
+    const double margin = pl.kernel != KERNEL_GENERIC ? 1.0 : batch > 1 ? 1.2 : n > 128 ? 1.05 : 0.8;
+    const bool use_direct = !brief && direct < margin * tables;
     // (one vector padded to 32 is never the better use of the matrix cores where direct takes it: 310460 x 192, mu = 4
     // 17 us in digits, 6.8 with tables)
     if (batch == 1 && (brief || direct < 1e30)) {
@@ -616,6 +620,9 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
         return ok;
     }
     const double few = use_direct ? direct : tables;
+    // (no digit plan takes less than 8 us: small calls, where this search would show, skip it; the narrow-key kernel
+    // keeps calls below 5e6 multiply-adds that direct does not take: 129 x 5000, 2 planes, 3 vectors at mu = 3 12.6 us
+    // with tables, 12.5 with digits)
     if (few >= 8.3 && !(pl.kernel == KERNEL_WIDE && (double)q * m * n * batch < 5e6)) {
         biq_plan d;
         double est;
@@ -625,9 +632,8 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
                 pl = d;
                 return true;
             }
-        } else if (est < (use_direct ? 1.25 * few : few)) {
-            // (a margin against direct's estimate, which is the looser one and misses on the slow side for long
-            // rows with several tiles of vectors: 14464 x 10824, 2 planes, 20 vectors 101 us instead of 36)
+        } else if (est < 1.05 * few) {
+            // (digits for ties, too: 14464 x 10824, 2 planes, 20 vectors direct 101 us, digits 36)
             pl = d;
             return true;
         }

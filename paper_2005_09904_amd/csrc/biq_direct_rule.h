@@ -40,12 +40,15 @@ inline long long direct_lds_bytes(long long chunks, int vecs, int rpw, bool exch
 // operands do not fit the LDS.  Candidates: the many-rows instantiation, and one row tile per wave with 1 .. 8
 // groups of waves along the row; as many row steps per workgroup as leave at most 256 workgroups.  A row step costs
 // its chunks (matrix pipe, expansion or LDS of the two waves per SIMD, or the latency of the next keys) and an
-// epilogue; keys stream at 3.3 TB/s; the split of the inputs 1.9 us per 512 blocks.  Fitted to 94 random
-// shapes (128 .. 280000 rows, 128 .. 16000 columns, 1 .. 48 vectors): 13 % rms; one vector on more than 2048 columns to
-// 2300 times of 298 shapes: 7 % rms, the mapping chosen 0.2 % slower in the mean than the best.  The estimate handed on
-// (not the choice of the mapping) has at least 0.85 us per row step where there are several: a step waits for its scales,
-// and short rows have nothing else to do meanwhile (1025348 x 111, 1 plane, 1 vector: 16 us without, measured 34).  All
-// are 8 % below what a replayed graph takes with keys from memory.
+// epilogue; keys stream at 3.5 TB/s, results and scales at a third of that; the split of the inputs 2.2 us per round of 512
+// blocks over the eight waves, half of it in a last round of up to four waves (one per SIMD), a quarter for one.  Fitted to
+// 3700 shapes of 2 .. 256 vectors (128 .. 32768 rows, 128 .. 16384 columns, every mapping of each, a replayed graph, keys
+// from memory): 8 % rms where tables or digits are within a factor of two (without the last rounds, results and scales 12 %),
+// the mapping chosen 0.9 % slower in the mean than the best.  One vector on more than 2048 columns has costs of its own,
+// fitted to 2300 times of 298 shapes: 7 % rms, but 7 to 12 % below what a replayed graph takes with keys from memory; the mapping
+// chosen is 0.2 % slower in the mean than the best.  The estimate handed on (not the choice of the mapping) has at least
+// 0.81 us per row step where there are several: a step waits for its scales, and short rows have nothing else to do
+// meanwhile (1025348 x 111, 1 plane, 1 vector: 16 us without, measured 34).
 struct DirectGeom {
     int vecs, batch_tiles, chunks, ksplit, steps, row_blocks, lds;
     int uc;                  // chunks requested together
@@ -69,6 +72,9 @@ inline bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
     g.batch_tiles = direct_div(batch, g.vecs);
     if (g.batch_tiles > 65535) return false;
     const int nt = direct_div(g.vecs, 3);
+    // groups of 16 blocks of inputs, four to a wave at a time
+    const int groups = g.chunks * g.vecs, last = groups % (4 * kDirectWaves);
+    const double split_rounds = groups / (4 * kDirectWaves) + (last == 0 ? 0.0 : last <= 4 ? 0.25 : last <= 16 ? 0.47 : 1.0);
     double best = 1e30;
     for (int kind : {DIRECT_MANY, DIRECT_LINES, DIRECT_FEW}) {
         if (!direct_has_kind(kind, q, nt)) continue;
@@ -78,8 +84,8 @@ inline bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
         // and more; with 2 to 6 vectors, 110 shapes, 1 % less at most)
         const bool one = batch == 1 && n > 2048 && kind != DIRECT_MANY;
         if (kind == DIRECT_LINES && (one ? m <= 16 * kDirectCus : direct_rpw(q, nt) > 1)) continue;
-        const double rate = !one ? 3.3e6 : uc == 2 ? 4.35e6 : 3.72e6;
-        const double mem = (double)q * m * direct_row_bytes(n) * g.batch_tiles / rate;
+        const double keys = (double)q * m * direct_row_bytes(n) * g.batch_tiles;
+        const double mem = one ? keys / (uc == 2 ? 4.35e6 : 3.72e6) : (keys + 12.0 * m * ((double)q * g.batch_tiles + batch)) / 3.5e6;
         for (int ks = 1; ks <= (kind == DIRECT_FEW || (one && uc == 2) ? kDirectWaves : 1) && (ks - 1) * uc < g.chunks; ks *= 2) {
             const long long all_steps = direct_div(m, kDirectWaves / ks * rpw * 16);
             long long steps = direct_div_ll(all_steps * g.batch_tiles, kDirectCus);
@@ -94,18 +100,19 @@ inline bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
                 row_step = ks > 1 ? 0.57 : 0.53;
                 before = 2.54 + 1.87 * g.chunks / (4 * kDirectWaves);
             } else {
-                clk = 22.0 * rt * (16 * nt > 32 ? 16 * nt : 32);
-                if (clk < 860.0 * nt) clk = 860.0 * nt;
-                row_step = 0.012 * rt * nt + (ks > 1 ? 0.36 : 0.0);
-                before = 1.3 + 0.36 * (nt - 1) + 1.94 * rounds * direct_div(g.chunks * g.vecs, 4 * kDirectWaves);
+                clk = 17.5 * rt * (16 * nt > 32 ? 16 * nt : 32);
+                if (clk < 680.0 * nt) clk = 680.0 * nt;
+                if (clk < 850.0) clk = 850.0;
+                row_step = 0.008 * rt * nt + (ks > 1 ? 0.17 : 0.0);
+                before = 2.9 + 0.085 * (nt - 1) + 2.2 * rounds * split_rounds;
             }
             double work = rounds * steps * (upg * uc * clk / 2200.0 + row_step);
             // (both together, smoothly: of two mappings that memory bounds, the one with less work)
             const double t = before + cbrt(work * work * work + mem * mem * mem);
             if (t < best) {
                 best = g.est = t;
-                if (steps > 1 && work < 0.85 * rounds * steps) {
-                    work = 0.85 * rounds * steps;
+                if (steps > 1 && work < 0.81 * rounds * steps) {
+                    work = 0.81 * rounds * steps;
                     g.est = before + cbrt(work * work * work + mem * mem * mem);
                 }
                 g.kind = kind;

@@ -111,7 +111,7 @@ def test_direct_row_limit(biq):
 @pytest.mark.parametrize("m,n,q,b,mu", [
     (310460, 192, 1, 1, 4), (70016, 286, 1, 1, 4), (90816, 128, 1, 1, 6), (300000, 256, 1, 1, 5), (1 << 20, 128, 1, 1, 4),
     (320782, 131, 2, 1, 6), (367424, 154, 4, 1, 6), (209107, 128, 3, 1, 6), (145712, 512, 1, 1, 4), (65088, 128, 1, 1, 7),
-    (982, 144, 2, 1, 4), (221, 3376, 4, 25, 4), (150, 3086, 2, 51, 4), (38243, 14976, 1, 1, 4)])
+    (982, 144, 2, 1, 4), (221, 3376, 4, 25, 4), (150, 3086, 2, 51, 4), (458, 2061, 3, 15, 4), (133, 3208, 1, 10, 4)])
 def test_tables_where_they_are_faster(biq, m, n, q, b, mu):
     """Short rows with one vector and few rows of narrow keys: 1.1 to 5.7 times the tables' time without them.  (What runs is
     allowed to be the direct kernel for one vector on rows of several key units, never the 32-vector one.)"""
@@ -128,3 +128,21 @@ def test_two_column_tiles_for_long_rows_and_eight_tiles(biq):
         p = biq.biq_plan_get(m, n, q, b, 8)
         assert p.kernel == 3 and p.row_mode == 1 and p.batch_tile == 64
     assert biq.biq_plan_get(31424, 512, 2, 104, 8).batch_tile == 32
+
+
+@pytest.mark.parametrize("m,n,q,b,mu,tables,direct,digits", [
+    # us per call, keys from memory; digits: 0 where they are far behind
+    (174, 156, 4, 3, 8, 4.9, 4.1, 0), (184, 256, 4, 2, 8, 4.9, 4.2, 0), (512, 512, 2, 2, 8, 4.3, 3.8, 0), (1024, 512, 2, 3, 8, 4.5, 3.9, 0),
+    (3477, 349, 2, 162, 8, 10.6, 8.9, 0), (1088, 510, 2, 181, 8, 7.7, 6.8, 0), (17937, 160, 3, 11, 8, 7.4, 6.5, 0),
+    (7897, 2672, 1, 7, 8, 9.1, 8.0, 0), (10240, 128, 2, 64, 8, 10.2, 8.4, 8.1), (11450, 256, 3, 42, 8, 11.4, 9.1, 9.4),
+    (1599, 1167, 4, 30, 8, 12.2, 11.5, 10.9), (1918, 6208, 2, 17, 8, 13.5, 11.4, 13.9), (20066, 8492, 2, 7, 8, 42.0, 36.9, 52.1),
+    (766, 14080, 2, 13, 8, 13.8, 11.1, 15.6), (7342, 12160, 2, 4, 8, 21.9, 21.0, 32.3), (1145, 7117, 4, 7, 8, 12.2, 12.7, 0),
+    (16834, 4928, 1, 2, 8, 9.6, 11.2, 0), (160, 14656, 2, 4, 8, 9.0, 9.7, 0), (919, 832, 3, 9, 8, 4.6, 6.5, 0), (2048, 1024, 2, 4, 8, 4.3, 5.4, 0),
+    (291, 601, 2, 10, 8, 4.6, 6.4, 0), (1152, 704, 2, 10, 8, 4.1, 6.5, 0), (309, 1652, 3, 25, 8, 6.7, 8.9, 0),
+    (171670, 8874, 1, 1, 6, 78.7, 58.4, 0), (576, 16355, 4, 1, 6, 13.5, 10.9, 0), (38243, 14976, 1, 1, 4, 35.0, 27.9, 0),
+    (225, 3584, 2, 192, 4, 15.7, 11.4, 0), (965, 3317, 1, 106, 4, 16.3, 0, 13.6), (133, 3208, 1, 10, 4, 6.4, 9.7, 0), (80000, 128, 1, 1, 7, 4.4, 5.9, 0)])
+def test_choice_by_measured_times(biq, m, n, q, b, mu, tables, direct, digits):
+    """What the library chooses among tables, direct and digits takes at most 5 % longer than the best of them."""
+    p = biq.biq_plan_get(m, n, q, b, mu)
+    chosen = digits if p.kernel == 3 else direct if p.table_fill == 2 else tables
+    assert 0 < chosen <= 1.05 * min(t for t in (tables, direct, digits) if t)
