@@ -3,8 +3,6 @@
 
 #include <hip/hip_runtime.h>
 
-#include <math.h>
-
 #include "biq_launch.h"
 // kernel headers: only their geometry constants are used here (no kernel is instantiated in this file)
 #include "biq_gemv8.h"
@@ -228,7 +226,6 @@ double tables_estimate(const biq_plan& pl, int m, int n, int q, int batch, int m
     const double rounds = (double)(long long)((wgs + kNumCu - 1) / kNumCu);
     const double rows = pl.rows_per_wg < m ? pl.rows_per_wg : m;
     const double mem = (double)q * m * biq_key_row_stride(n);
-    auto together = [](double a, double b) { return cbrt(a * a * a + b * b * b); };
     if (pl.kernel == KERNEL_GEMM8X2 || pl.kernel == KERNEL_GEMM8X2H) {   // (a short row still takes its lanes' time)
         const bool half = pl.kernel == KERNEL_GEMM8X2H;
         const double lookups = rows * q * pl.chunks_per_tile * 2;

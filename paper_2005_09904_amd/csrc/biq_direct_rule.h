@@ -1,8 +1,6 @@
 // The mapping of the direct kernel (biq_direct.h) for a shape and its estimated time (plain C++: no kernel code).
 #pragma once
 
-#include <math.h>
-
 #include <initializer_list>
 
 namespace biq {
@@ -28,6 +26,13 @@ constexpr bool direct_has_kind(int kind, int q, int nt) {
 inline int direct_div(int a, int b) { return (int)(((unsigned)a + (unsigned)b - 1u) / (unsigned)b); }
 inline long long direct_div_ll(long long a, long long b) { return (a + b - 1) / b; }
 inline unsigned direct_row_bytes(int n) { return (unsigned)direct_div(n, 128) * 16u; }   // keys of a row
+
+// cbrt(a^3 + b^3) for a, b > 0, to 1.2e-5: of two costs that overlap, the larger one and some of the other.  (Polynomial for
+// (1 + u)^(1/3) on [0, 1]; plans are made on every call, and the library's root takes 37 ns.)
+inline double together(double a, double b) {
+    const double most = a > b ? a : b, r = (a > b ? b : a) / most, u = r * r * r;
+    return most * (1.0 + u * (0.3329064 + u * (-0.10635862 + u * (0.04417861 - 0.01081733 * u))));
+}
 
 inline long long direct_lds_bytes(long long chunks, int vecs, int rpw, bool exchange) {
     const long long blocks = chunks * 16;
@@ -75,7 +80,8 @@ inline bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
     // groups of 16 blocks of inputs, four to a wave at a time
     const int groups = g.chunks * g.vecs, last = groups % (4 * kDirectWaves);
     const double split_rounds = groups / (4 * kDirectWaves) + (last == 0 ? 0.0 : last <= 4 ? 0.25 : last <= 16 ? 0.47 : 1.0);
-    double best = 1e30;
+    double best = 1e30, least_work = 0.0, best_mem = 0.0;
+    // (plans are made on every call: quotients by powers of two are shifts)
     for (int kind : {DIRECT_MANY, DIRECT_LINES, DIRECT_FEW}) {
         if (!direct_has_kind(kind, q, nt)) continue;
         const int rpw = kind == DIRECT_MANY ? direct_rpw(q, nt) : 1, uc = kind == DIRECT_FEW ? 1 : direct_uc(nt);
@@ -85,44 +91,50 @@ inline bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
         const bool one = batch == 1 && n > 2048 && kind != DIRECT_MANY;
         if (kind == DIRECT_LINES && (one ? m <= 16 * kDirectCus : direct_rpw(q, nt) > 1)) continue;
         const double keys = (double)q * m * direct_row_bytes(n) * g.batch_tiles;
-        const double mem = one ? keys / (uc == 2 ? 4.35e6 : 3.72e6) : (keys + 12.0 * m * ((double)q * g.batch_tiles + batch)) / 3.5e6;
-        for (int ks = 1; ks <= (kind == DIRECT_FEW || (one && uc == 2) ? kDirectWaves : 1) && (ks - 1) * uc < g.chunks; ks *= 2) {
-            const long long all_steps = direct_div(m, kDirectWaves / ks * rpw * 16);
+        const double mem = one ? keys * (uc == 2 ? 1 / 4.35e6 : 1 / 3.72e6) : (keys + 12.0 * m * ((double)q * g.batch_tiles + batch)) * (1 / 3.5e6);
+        const int units = uc == 2 ? (g.chunks + 1) >> 1 : g.chunks;
+        const int rt = q * rpw;
+        double clk, before;                              // a chunk; what comes ahead of the first row step
+        if (one) {
+            clk = 727.0 * q;
+            const double least = uc == 2 ? 818.0 : 1132.0;
+            if (clk < least) clk = least;
+            before = 2.54 + 1.87 / (4 * kDirectWaves) * g.chunks;
+        } else {
+            clk = 17.5 * rt * (16 * nt > 32 ? 16 * nt : 32);
+            if (clk < 680.0 * nt) clk = 680.0 * nt;
+            if (clk < 850.0) clk = 850.0;
+            before = 2.9 + 0.085 * (nt - 1);
+        }
+        const double unit = uc * clk * (1 / 2200.0);
+        const int log_step_rows = 7 + (rpw >> 1);        // rows of a row step of the eight waves: rpw is 1, 2 or 4
+        for (int log_ks = 0; log_ks <= (kind == DIRECT_FEW || (one && uc == 2) ? 3 : 0) && ((1 << log_ks) - 1) * uc < g.chunks; ++log_ks) {
+            const int log_rows = log_step_rows - log_ks;
+            const long long all_steps = ((long long)m + (1 << log_rows) - 1) >> log_rows;
             long long steps = direct_div_ll(all_steps * g.batch_tiles, kDirectCus);
             if (steps > all_steps) steps = all_steps;
-            const double rounds = (double)direct_div_ll(direct_div_ll(all_steps, steps) * g.batch_tiles, kDirectCus);
-            const int rt = q * rpw, upg = direct_div(direct_div(g.chunks, uc), ks);
-            double clk, row_step, before;                // a chunk; the rest of a row step; what comes ahead of the first
-            if (one) {
-                clk = 727.0 * q;
-                const double least = uc == 2 ? 818.0 : 1132.0;
-                if (clk < least) clk = least;
-                row_step = ks > 1 ? 0.57 : 0.53;
-                before = 2.54 + 1.87 * g.chunks / (4 * kDirectWaves);
-            } else {
-                clk = 17.5 * rt * (16 * nt > 32 ? 16 * nt : 32);
-                if (clk < 680.0 * nt) clk = 680.0 * nt;
-                if (clk < 850.0) clk = 850.0;
-                row_step = 0.008 * rt * nt + (ks > 1 ? 0.17 : 0.0);
-                before = 2.9 + 0.085 * (nt - 1) + 2.2 * rounds * split_rounds;
-            }
-            double work = rounds * steps * (upg * uc * clk / 2200.0 + row_step);
-            // (both together, smoothly: of two mappings that memory bounds, the one with less work)
-            const double t = before + cbrt(work * work * work + mem * mem * mem);
+            const long long blocks = steps == 1 ? all_steps : direct_div_ll(all_steps, steps);
+            const double turns = (double)direct_div_ll(blocks * g.batch_tiles, kDirectCus);     // rounds of workgroups
+            const int upg = (units + (1 << log_ks) - 1) >> log_ks;
+            const double row_step = one ? (log_ks > 0 ? 0.57 : 0.53) : 0.008 * rt * nt + (log_ks > 0 ? 0.17 : 0.0);
+            const double ahead = one ? before : before + 2.2 * turns * split_rounds;
+            const double work = turns * steps * (upg * unit + row_step);
+            // (both together: of two mappings that memory bounds, the one with less work)
+            const double t = ahead + together(work, mem);
             if (t < best) {
-                best = g.est = t;
-                if (steps > 1 && work < 0.81 * rounds * steps) {
-                    work = 0.81 * rounds * steps;
-                    g.est = before + cbrt(work * work * work + mem * mem * mem);
-                }
+                best = t;
+                g.est = steps > 1 && work < 0.81 * turns * steps ? -ahead : t;
                 g.kind = kind;
-                g.ksplit = ks;
+                g.ksplit = 1 << log_ks;
                 g.uc = uc;
                 g.steps = (int)steps;
-                g.row_blocks = (int)direct_div_ll(all_steps, steps);
+                g.row_blocks = (int)blocks;
+                least_work = 0.81 * turns * steps;
+                best_mem = mem;
             }
         }
     }
+    if (g.est < 0.0) g.est = together(least_work, best_mem) - g.est;
     g.lds = (int)direct_lds_bytes(g.chunks, g.vecs, 1, g.ksplit > 1);
     return best < 1e30;
 }

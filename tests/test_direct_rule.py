@@ -75,3 +75,22 @@ def test_every_row_has_a_place(mapping):
         rows = steps * (8 // ks) * rpw * 16
         assert rows * blocks >= m > rows * (blocks - 1)
         assert (ks - 1) * uc < -(-n // 512)                                   # every group has a chunk
+
+
+def test_together(tmp_path):
+    """Costs of very different and of equal sizes, against the root itself."""
+    (tmp_path / "main.cpp").write_text("""
+#include <cmath>
+#include <cstdio>
+#include "biq_direct_rule.h"
+int main() {
+    double worst = 0.0;
+    for (double a = 1e-3; a < 1e9; a *= 1.37)
+        for (double b = 1e-3; b < 1e9; b *= 1.73) worst = std::fmax(worst, std::fabs(biq::together(a, b) / std::cbrt(a * a * a + b * b * b) - 1.0));
+    std::printf("%g\\n", worst);
+}
+""")
+    exe = str(tmp_path / "together")
+    subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-I" + os.path.join(ROOT, "paper_2005_09904_amd", "csrc"),
+                    str(tmp_path / "main.cpp"), "-o", exe], check=True)
+    assert float(subprocess.run([exe], check=True, capture_output=True, text=True).stdout) < 1.3e-5
