@@ -319,8 +319,8 @@ biq_status biq_lstm_cell(const uint8_t* K, const float* alpha, const float* bias
  *   - Where it does not (wide batches: prepared inputs, partial sums), a plan that may need less
  *     takes the call: the tables, or the matrix cores with three 16-bit terms or with block-scaled digits,
  *     whichever of them fits.  Same tolerance, not the same bits.
- *   - BIQ_EWORKSPACE if none of them fits either, or only the tables do and are estimated at four times the
- *     matrix cores' time or more (no kernel is launched; all five benchmark configurations fit): use
+ *   - BIQ_EWORKSPACE if none of them fits either, or only the tables do and are estimated at four times
+ *     biq_gemm's time or more (no kernel is launched; all five benchmark configurations fit): use
  *     biq_gemm with a caller workspace.
  *   - Every call on one GPU uses that GPU's single buffer: calls that may overlap in time on one
  *     GPU (different streams, different host threads) race on it and must be serialised by the

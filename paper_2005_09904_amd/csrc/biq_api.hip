@@ -211,7 +211,8 @@ bool plan_finish(biq_plan& pl, int m, int n, int q, int batch, int mu) {
 // Estimated time (us) of the lookup-table plan `pl`, from rates measured on MI355X: where the tables
 // stop paying off (the crossover of Sec. IV-B / Fig. 10).  The batched mu = 8 kernels, fitted to 330 shapes, 7 % rms (half
 // tables 5 %): per round of workgroups over the CUs and tile the lookups of its rows and two input vectors, more where rows
-// of the input are not read 16 bytes at a time, keys at 4.5 TB/s, a second kernel with 0.24 us per split.  (Estimated /
+// of the input are not read 16 bytes at a time, keys at 4.5 TB/s, a second kernel with 0.24 us per split, half of it
+// for up to ten results.  (Estimated /
 // measured: 17856 x 14656, 3 planes, 2 vectors 38.3 / 38.3; 7360 x 1884, 2, 53 26.4 / 25.6; 960 x 14438, 2, 11 16.6 / 16.0.)
 // Narrow keys, fitted to 319 shapes, 9 % rms: 5.1 us per round and the lookups of
 // a whole tile, 2.9 (mu = 5) and 4.1 times (mu = 6) the time where a pass serves one vector only; a second kernel
@@ -232,7 +233,8 @@ double tables_estimate(const biq_plan& pl, int m, int n, int q, int batch, int m
         const double tile = half ? 26.8e-6 * lookups + (n % 4 ? 1.0 : 0.0) : 0.51 + 18.6e-6 * lookups + (n % 4 ? 0.4 : 0.0);
         const double turns = rounds * pl.tiles_per_split;    // (the first one's tables are built beside the dispatch)
         return (half ? 3.65 : 2.8) + together(turns * tile + (turns - 1) * (half ? 1.3 : 1.5), mem / 4.5e6) +
-               (pl.chunk_splits > 1 ? (half ? 1.5 : 3.1) + pl.chunk_splits * (0.24 + (half ? 1.7e-6 : 0.9e-6) * m * batch) : 0.0);
+               (pl.chunk_splits > 1 ? (half ? 1.5 : 3.1) + pl.chunk_splits * (((long long)m * batch <= 10 ? 0.11 : 0.24) +
+                                                                              (half ? 1.7e-6 : 0.9e-6) * m * batch) : 0.0);
     }
     if (pl.kernel == KERNEL_WIDE) {
         const double slower = mu == 6 ? 4.1 : mu == 5 ? 2.9 : mu == 4 ? 1.14 : 1.0;
@@ -329,9 +331,9 @@ bool plan_unpack(biq_plan& pl, int m, int n, int q, int batch, int mu, int terms
 // (50.0 instead of 48.1; with fewer than eight tiles per wave 10-25 %): they are chosen for eight tiles and long rows.
 // On 90 shapes (128 .. 16384 columns, 14 .. 256 vectors) the choice is 2.3 % (fp32) and 2.5 % (bf16 values) slower
 // than the fastest of up to 36 mappings on average, 19 % at most (one row step more or less of a short row).
-// The estimate handed on has constants of its own for keys from memory, fitted to 1630 shapes of 2 .. 256 vectors near the
-// crossovers: 6 % rms (with the constants that rank the mappings 13 %: from 0.85 of the time for one key group per wave to 1.3
-// for sixteen).
+// The estimate handed on has constants of its own, for keys from memory and the 6.7 MB of padded X from which the split is
+// bound by bandwidth, fitted to 2600 shapes of 1 .. 1000000 rows near the crossovers: 7 % rms (with the constants that
+// rank the mappings 17 %: half the time for sixteen key groups per wave, twice for 50 MB of X).
 bool plan_digits(biq_plan& pl, int m, int n, int q, int batch, double& est) {
     double best = 1e30;
     est = 1e30;
@@ -367,9 +369,9 @@ bool plan_digits(biq_plan& pl, int m, int n, int q, int batch, double& est) {
                     if (rank < best) {
                         best = rank;
                         // (what a call takes with its keys from memory)
-                        const double cold = step < 620.0 ? 620.0 : step;
-                        est = 5.9 + 0.97 * bpad_mb * n + rounds * (4.0 * gpw * cold / 1470.0 + 0.23 * tiles) + 0.8e-6 * m * (double)batch +
-                              (S > 1 ? 2.3 + 0.62 * (S + 1.0) * bpad_mb * m : 0.0);
+                        const double cold = step < 622.0 ? 622.0 : step, x_mb = bpad_mb * n;
+                        est = 5.5 + (x_mb < 6.7 ? 0.96 * x_mb : 4.82 + 0.24 * x_mb) + rounds * (4.0 * gpw * cold / 1420.0 + 0.3 * tiles) +
+                              0.86e-6 * m * (double)batch + (S > 1 ? 2.3 + 0.71 * (S + 1.0) * bpad_mb * m : 0.0);
                         pl.batch_tile = bt;
                         pl.wave_splits = ws;
                         pl.rows_per_wg = rows;
@@ -428,7 +430,7 @@ bool plan_tables(biq_plan& pl, int m, int n, int q, int batch, int mu) {
             // walks all its tiles), wider than one full-table tile: half tables (256 chunks per
             // workgroup), so that rows up to n = 2048 need no split and no second kernel.  One workgroup per CU if the
             // rows allow it (a second round of workgroups pays the table build again), at least
-            // 8 rows each; 4 rows per wave step, at most 4 steps per wave.
+            // 8 rows each; 4 rows per wave step, up to 9 steps per wave (few blocks of many splits: 6896 x 36882, 3 planes).
             pl.kernel = KERNEL_GEMV8H;
             pl.chunks_per_tile = kGemvHalfTileChunks;
             pl.tiles_per_split = 1;
@@ -462,7 +464,7 @@ bool plan_tables(biq_plan& pl, int m, int n, int q, int batch, int mu) {
         // Small batched calls wider than one full-table tile: half tables (128 chunks x 2 input
         // vectors per workgroup) halve the number of row splits; up to n = 1024 there is none and
         // no second kernel.  One workgroup per CU if the rows allow it, at least 8 rows each;
-        // 8 rows per wave step, at most 4 steps per wave.
+        // 8 rows per wave step, up to 8 steps per wave (one block of all rows: 992 x 10379, 1 plane, 24 vectors).
         pl.kernel = KERNEL_GEMM8X2H;
         pl.threads = 1024;
         pl.chunks_per_tile = kGemmHalfTileChunks;
@@ -629,7 +631,7 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
                 pl = d;
                 return true;
             }
-        } else if (est < 1.05 * few) {
+        } else if (est < (use_direct ? 1.05 : 0.95) * few) {
             // (digits for ties, too: 14464 x 10824, 2 planes, 20 vectors direct 101 us, digits 36)
             pl = d;
             return true;
@@ -952,10 +954,12 @@ bool plan_small_workspace(biq_plan& pl, int m, int n, int q, int batch, int mu) 
     if (q <= 4 && three_terms_estimate(m, n, q, batch) < t_lut + 6.0) return plan_unpack(pl, m, n, q, batch, mu, 3);
     return plan_default(pl, m, n, q, batch, mu, true);
 }
-// ... and where that one does not fit either: of the tables' plan and the matrix cores' (digits; three terms for rows too long
-// for those) the one that fits, the faster one by the estimates if both do.  Many vectors on the tables, which often need
-// no workspace at all, are left to the caller from kNoallocSlower times the matrix cores' time on: biq_gemm with a
-// workspace is the better call, and BIQ_EWORKSPACE says so (16384 x 16384, 2 planes, 512 vectors: 6.4 times).
+// ... and where that one does not fit either: of the tables' plan (without tables, where direct is the faster one) and the
+// matrix cores' (digits; three terms for rows too long for those) the one that fits, the faster one by the estimates if
+// both do.  Many vectors on the tables, which often need no workspace at all, are left to the caller from kNoallocSlower
+// times the matrix cores' time on: biq_gemm with a workspace is the better call, and BIQ_EWORKSPACE says so (16384 x 16384,
+// 2 planes, 512 vectors: 4.4 times).  Few rows with many inputs, where the split of the inputs is most of a call, have 1 us
+// per MB of them on top.
 constexpr double kNoallocSlower = 4.0;
 bool plan_fitting(biq_plan& pl, int m, int n, int q, int batch, int mu, size_t limit) {
     biq_plan lut, cores;
@@ -963,9 +967,14 @@ bool plan_fitting(biq_plan& pl, int m, int n, int q, int batch, int mu, size_t l
     const bool have_lut = plan_default(lut, m, n, q, batch, mu, true);
     if (!plan_digits(cores, m, n, q, batch, t_cores))
         t_cores = plan_unpack(cores, m, n, q, batch, mu, 3) ? three_terms_estimate(m, n, q, batch) : 1e300;
-    const double t_lut = have_lut ? tables_estimate(lut, m, n, q, batch, mu) : 1e300;
+    double t_lut = have_lut ? tables_estimate(lut, m, n, q, batch, mu) : 1e300;
+    DirectGeom g;
+    if (have_lut && m >= 128 && direct_geometry(g, m, n, q, batch) && g.est < t_lut) {
+        t_lut = g.est;
+        lut.table_fill = 2;
+    }
     const bool cores_fit = t_cores < 1e300 && plan_workspace(cores, m, batch) <= limit;
-    const bool lut_fits = have_lut && plan_workspace(lut, m, batch) <= limit && t_lut < kNoallocSlower * t_cores;
+    const bool lut_fits = have_lut && plan_workspace(lut, m, batch) <= limit && t_lut < kNoallocSlower * (t_cores + 4e-6 * n * (double)batch);
     pl = cores_fit && (!lut_fits || t_cores < t_lut) ? cores : lut;
     return cores_fit || lut_fits;
 }

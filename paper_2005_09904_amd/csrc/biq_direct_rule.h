@@ -45,7 +45,7 @@ inline long long direct_lds_bytes(long long chunks, int vecs, int rpw, bool exch
 // operands do not fit the LDS.  Candidates: the many-rows instantiation, and one row tile per wave with 1 .. 8
 // groups of waves along the row; as many row steps per workgroup as leave at most 256 workgroups.  A row step costs
 // its chunks (matrix pipe, expansion or LDS of the two waves per SIMD, or the latency of the next keys) and an
-// epilogue; keys stream at 3.5 TB/s, results and scales at a third of that; the split of the inputs 2.2 us per round of 512
+// epilogue; keys stream at 3.5 TB/s, results and scales count 2.25 times; the split of the inputs 2.2 us per round of 512
 // blocks over the eight waves, half of it in a last round of up to four waves (one per SIMD), a quarter for one.  Fitted to
 // 3700 shapes of 2 .. 256 vectors (128 .. 32768 rows, 128 .. 16384 columns, every mapping of each, a replayed graph, keys
 // from memory): 8 % rms where tables or digits are within a factor of two (without the last rounds, results and scales 12 %),
@@ -91,7 +91,7 @@ inline bool direct_geometry(DirectGeom& g, int m, int n, int q, int batch) {
         const bool one = batch == 1 && n > 2048 && kind != DIRECT_MANY;
         if (kind == DIRECT_LINES && (one ? m <= 16 * kDirectCus : direct_rpw(q, nt) > 1)) continue;
         const double keys = (double)q * m * direct_row_bytes(n) * g.batch_tiles;
-        const double mem = one ? keys * (uc == 2 ? 1 / 4.35e6 : 1 / 3.72e6) : (keys + 12.0 * m * ((double)q * g.batch_tiles + batch)) * (1 / 3.5e6);
+        const double mem = one ? keys * (uc == 2 ? 1 / 4.35e6 : 1 / 3.72e6) : (keys + 9.0 * m * ((double)q * g.batch_tiles + batch)) * (1 / 3.5e6);
         const int units = uc == 2 ? (g.chunks + 1) >> 1 : g.chunks;
         const int rt = q * rpw;
         double clk, before;                              // a chunk; what comes ahead of the first row step
