@@ -588,11 +588,14 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
     DirectGeom& g = geom ? *geom : local;             // (a caller that launches the direct kernel has use for it)
     if (mu == 8 && batch == 1) {
         // One vector: rows beyond one half-table tile, i.e. where the tables take several builds or a second dispatch, if
-        // direct is estimated well below them (298 shapes, 128 .. 128128 rows, 2049 .. 40900 columns, keys from memory: 193
-        // of them, 23 % less in the mean over all, two longer by 4 %; the better one of the two everywhere: 24 %).  Tables /
-        // direct: 256 x 5952, 3 planes 9.3 / 5.9; 4096 x 4096, 2 6.7 / 5.0; 4096 x 11008, 2 12.6 / 7.9; 16384 x 4096, 2 8.7 /
-        // 7.7; 5000 x 3001, 3 11.9 / 6.4; but 11008 x 4096, 3 8.9 / 8.9; 1088 x 9288, 4 8.3 / 9.7; 234 x 32722, 4 12.4 / 19.4;
-        // 36294 x 3136, 2 12.7 / 15.4.  The full-table kernel (33 MB of keys and more) keeps its calls: 47993 x 6847, 3 35 / 40.
+        // direct, whose estimate is 7 to 12 % low, is estimated well below them (700 shapes, 128 .. 500000 rows, 2049 ..
+        // 16384 columns, keys from memory: 0.7 % slower in the mean than the better of both).  Even widths: 0.865 of the tables'
+        // (368 shapes: none takes 5 % longer than it would with tables; with 0.9 three do, for 0.1 % less in the mean).  Odd widths:
+        // 0.95 (332 shapes; with 0.865 0.3 % more in the mean, and five go to the tables that took direct before the tables' side
+        // was estimated here).  Tables / direct: 256 x 5952, 3 planes 8.6 / 5.6; 4096 x 4096, 2 6.6 / 5.0; 4096 x 11008, 2 9.5 / 8.2;
+        // 16384 x 4096, 2 8.6 / 7.7; 5000 x 3001, 3 12.2 / 6.4; 11008 x 4096, 3 (tables) 9.6 / 8.9; but 1088 x 9288, 4 8.4 / 9.7;
+        // 234 x 32722, 4 12.7 / 19.9; 36294 x 3136, 2 12.6 / 15.8.  The full-table kernel (33 MB of keys per plane and more) keeps its
+        // calls: 47993 x 6847, 3 37 / 40.
         if (ok && m >= 128 && n > 2048 && pl.kernel == KERNEL_GEMV8H && direct_geometry(g, m, n, q, 1) &&
             g.est < (n % 4 ? 0.95 : 0.865) * tables_estimate(pl, m, n, q, 1, mu))
             pl.table_fill = 2;
@@ -603,14 +606,14 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
     // The one estimated faster; direct's errors are also the smaller ones (5-8e-8 against 1.0-1.3e-7), so it has the ties.  The
     // generic kernel's estimate is the looser one, and misses on the low side: it keeps what it wins clearly, but one vector on rows
     // of up to 128 columns, where direct's is 20 % low (80000 x 128, mu = 7, 1 plane 4.4 us tables / 5.9 direct).  Not for one vector
-    // on a few short rows (982 x 144, 2: 3.7 / 4.0; but 68544 x 206, 3, mu = 6: 13.6 / 6.5).  3700 shapes of 2 .. 256 vectors,
-    // mu = 8, drawn as in use and up to 5e7 operations: 0.6 % slower in the mean than the best of tables, direct and digits, 0.9 % of
-    // them by more than 10 %; 700 with other mu 0.5 %, none by more than 10 %.  Tables / direct: 1145 x 7117, 4, 7 12.2 / 12.7;
+    // on a few short rows (982 x 144, 2: 3.7 / 4.0; but 68544 x 206, 3, mu = 6: 13.6 / 6.5).  3200 shapes of 2 .. 256 vectors,
+    // mu = 8: 0.6 % slower in the mean than the best of tables, direct and digits, 1.7 % of them by more than 10 % (up to 5e7
+    // operations 0.3 and 0.6 %); 700 with other mu 0.6 and 2 %.  Tables / direct: 1145 x 7117, 4, 7 12.2 / 12.7;
     // 919 x 832, 3, 9 4.6 / 6.5; 1541 x 384, 2, 4 4.4 / 4.6; 512 x 512, 2, 2 4.3 / 3.8; 1024 x 512, 2, 3 4.5 / 3.9; 1536 x 128, 2, 3
     // 4.3 / 3.8; 2048 x 1024, 2, 4 4.3 / 5.4; 10240 x 1216, 2, 12 12.4 / 8.8; 1088 x 510, 2, 181 7.7 / 6.8; mu = 7: 1790 x 316, 3, 5
     // 18.6 / 4.7; mu = 4: 458 x 2061, 3, 15 7.9 / 11.5; 38243 x 14976, 1, 1 35.0 / 27.9.
     const bool brief = batch == 1 && n <= 512 && (long long)m * q < 4096;
-    const double margin = pl.kernel != KERNEL_GENERIC ? 1.0 : batch > 1 ? 1.2 : n > 128 ? 1.05 : 0.8;
+    const double margin = pl.kernel != KERNEL_GENERIC ? 1.0 : batch > 1 ? 1.3 : n > 128 ? 1.05 : 0.8;
     const bool use_direct = !brief && direct < margin * tables;
     // (one vector padded to 32 is never the better use of the matrix cores where direct takes it: 310460 x 192, mu = 4
     // 17 us in digits, 6.8 with tables)
@@ -632,7 +635,8 @@ bool plan_default(biq_plan& pl, int m, int n, int q, int batch, int mu, bool tab
                 return true;
             }
         } else if (est < (use_direct ? 1.05 : 0.95) * few) {
-            // (digits for ties, too: 14464 x 10824, 2 planes, 20 vectors direct 101 us, digits 36)
+            // (3900 shapes: one margin for both, or direct's 1.0 or 1.1, has more that take 10 % longer; digits instead of direct
+            // at 14464 x 10824, 2 planes, 20 vectors 101 -> 36 us)
             pl = d;
             return true;
         }

@@ -26,11 +26,12 @@
 // before -> here: 5003 x 3001, 3 planes, 7 vectors at mu = 6 13.1 (three bf16 terms 16.3) -> 9.2; 5000 x 3001, 3, 1
 // 11.9 -> 6.4; 10240 x 1216, 2, 12 17.6 -> 8.6; 32000 x 1024, 3, 6 18.6 -> 7.0; 1790 x 316, 3, 5 at mu = 7 18.6 -> 4.7.
 // With 4 planes and 10-15 vectors, keys on chip: 20000 x 700 9.3, 10000 x 2000 10.3.
-// Errors 4-9e-8 instead of 0.8-1.2e-7 (tables).  One vector, 2 planes, tables / direct: 4096 x 4096 6.7 / 5.0, 16384 x 4096
-// 8.7 / 7.7 (keys on chip 7.2 / 5.4).  Not taken for one vector where a table workgroup covers the row (2048 x 2048, 2:
-// 4.0 / 4.6), nor for small layers with several vectors (919 x 832, 3, 9: 4.4 / 6.7).
+// Errors 4-9e-8 instead of 0.8-1.3e-7 (tables).  One vector, 2 planes, tables / direct: 4096 x 4096 6.6 / 5.0, 16384 x 4096
+// 8.6 / 7.7 (keys on chip 7.2 / 5.4).  Not taken for one vector where a table workgroup covers the row (2048 x 2048, 2:
+// 3.9 / 4.6).  Small layers with several vectors go either way (tables / direct: 919 x 832, 3, 9 4.6 / 6.5; 1024 x 512, 2, 3 4.5 / 3.9).
 // (Two chunks requested together with one row tile per wave, several groups of waves: 16384 x 4096 8.3 -> 7.7 us, but
-// 5000 x 3001 6.4 -> 7.8: only where a workgroup has several row steps.)
+// 5000 x 3001 6.4 -> 7.8, both with one row step per workgroup: a mapping for more than 256 row tiles, where it is
+// estimated faster.)
 //
 // Layout.  Operand lane 16 * kg + r: row / column r, the 32 elements of one key dword.  A lane loads
 // 16 key bytes, [64 j + 16 kg, +16) of its row ("chunk" j = 512 elements): four lanes cover 64
