@@ -249,8 +249,18 @@ biq_status biq_query(const uint8_t* K, const float* alpha, const float* LUT, flo
  * tile in fast memory instead of fetching them from DRAM), keys are streamed once,
  * partial sums are combined in a fixed order (deterministic: same inputs, same bits).
  *
+ * Which of three ways a call takes is chosen by estimated time and may differ between versions
+ * (biq_plan_get reports it).  Tables keep fp32 throughout.  For few input vectors - and for one
+ * on many rows of more than 2048 columns - the default is often table_fill 2, for many the
+ * unpack_mfma kernel with digits (row_mode 1): those round each input element to 2^-24 of the largest of its 32
+ * neighbours, and table_fill 2 rounds sums below 2^-120 to 2^-143.  Relative errors against 64 bits are
+ * 5e-8 to 9e-8 for ordinary inputs, against 1.0e-7 to 1.3e-7 with tables, and 1e-7 either way for heavy-tailed
+ * ones (Cauchy); where large elements cancel in a row's sum both lose what fp32 sums of them lose (two elements of 4096 among unit ones, 4096
+ * columns: 2e-6 to 1e-5 either way, but 1e-7 with tables where the two are the first elements of the row).  A caller
+ * that wants the tables' arithmetic whatever the shape passes biq_plan_get_lut's plan to biq_gemm_ex.
+ *
  * For many input vectors (see biq_plan_get / biq_plan_get_lut) the default plan is the
- * unpack_mfma kernel instead: the "GEMM with unpacking" alternative of Sec. IV-B
+ * unpack_mfma kernel: the "GEMM with unpacking" alternative of Sec. IV-B
  * (Algorithm 3), with the sign bits expanded to +-1 in registers and contracted on the
  * matrix cores against X in block-scaled digits (see biq_plan.row_mode; rounded to 2^-24 of the
  * largest of 32 elements), fp32 accumulation, same tolerance, same determinism.  (biq_plan_get_mfma + biq_gemm_ex give the faster two-term
